@@ -66,7 +66,7 @@ extern "C" {
 #define LBM_ADV_PAPER 0 /* advection half-step of Eqs. (16)-(17) as printed */
 #define LBM_ADV_FLUX 1  /* conservative face-upwind flux form of the same half-step */
 
-#define LBM_PATH_FUSED 0 /* one sweeping kernel per step (default) */
+#define LBM_PATH_FUSED 0 /* one kernel per step (default): a sweep over strips, or tiles for small lattices */
 #define LBM_PATH_SPLIT 1 /* lattice-Boltzmann kernel, then finite-difference kernel (reference layout) */
 #define LBM_PATH_WAVE 2  /* one sweeping kernel per step, one wavefront per strip, no workgroup barriers */
 
@@ -180,13 +180,16 @@ int lbm_debug_stage(lbm_ctx* ctx, int32_t inst, double* out);
 
 /* Kernel sequence used by lbm_step and lbm_debug_stage: LBM_PATH_FUSED (default), LBM_PATH_SPLIT or
  * LBM_PATH_WAVE.  All compute the same arithmetic; the split path stores u^n between its two kernels,
- * the wave path sweeps each strip with a single wavefront.  LBM_E_INVAL for another value. */
+ * the wave path sweeps each strip with a single wavefront.  The fused path covers small lattices (up to 512 x 512
+ * nodes in all, at most 16 droplets each) by tiles instead of strips, until the caller sets a strip height or width
+ * or the autotuner finds strips faster.  LBM_E_INVAL for another value. */
 int lbm_set_path(lbm_ctx* ctx, int32_t path);
 int32_t lbm_get_path(const lbm_ctx* ctx);
 
 /* Rows per strip segment of the sweeping kernels (fused and wave paths), LBM_SEG_ROWS_MIN ..
  * LBM_SEG_ROWS_MAX (default 64; LBM_E_INVAL outside).  Taller segments recompute fewer halo rows;
- * shorter ones give more workgroups.  Synchronous. */
+ * shorter ones give more workgroups.  Setting a height or a width makes the fused path use strips also for
+ * small lattices.  Synchronous. */
 #define LBM_SEG_ROWS_MIN 16
 #define LBM_SEG_ROWS_MAX 4096
 int lbm_set_seg_rows(lbm_ctx* ctx, int32_t rows);
@@ -212,7 +215,9 @@ const int32_t* lbm_tune_widths(void);
  * and height (heights giving the same number of segments as a smaller one at that width are skipped) -- for
  * both sweeping kernels (LBM_PATH_FUSED, LBM_PATH_WAVE) and the split pair (LBM_PATH_SPLIT, no width or
  * height) when both_paths != 0, else for the current sweeping path only -- and set the path, width and
- * height of the fastest (the width is then read with lbm_get_strip_width).
+ * height of the fastest (the width is then read with lbm_get_strip_width).  Where the fused path can cover the
+ * lattices by tiles, that is tried too, without an entry in ms_out; if it is the fastest, LBM_PATH_FUSED is set with
+ * the best strips' height and width.
  * The trial launches read the current state and write only scratch (the inactive halves of the ping-pong
  * buffers, the velocity planes and the centre-of-mass partials): the state, the droplet table and the step
  * counter are unchanged.  Called on the split path with both_paths == 0, nothing is tried.

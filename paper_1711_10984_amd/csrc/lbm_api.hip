@@ -62,11 +62,14 @@ struct Layout {
   std::vector<InstDev> inst;
   std::vector<TileDev> tiles;  // split-kernel tiles in launch order (XCD-aware), padded with inst = -1
   std::vector<TileDev> segs;   // fused-kernel strips in launch order
+  std::vector<TileDev> ttiles;  // tiles of the tiled fused step in launch order (none if it does not apply)
+  int tshape = -1, nttiles = 0;  // shape of the tiles (TILE_SHAPES)
+  int64_t tpart_elems = 0;  // one of its two buffers of sums
   int ntiles = 0, nsegs = 0, ndrop_total = 0, max_nd = 0, obs_stride = 0;
   int max_segs = 0, max_seg_launch = 0, seg_rows = 0, strip_w = FUSED_TX;
   int64_t max_nodes = 0;
   size_t off_pool = 0, off_inst = 0, off_tiles = 0, off_segs = 0, off_drops = 0, off_part = 0, off_mask = 0,
-         off_step = 0, off_obs = 0, off_dbg = 0, total = 0;
+         off_step = 0, off_obs = 0, off_dbg = 0, off_ttiles = 0, off_tcen = 0, off_tpart = 0, off_tmask = 0, total = 0;
 };
 
 int validate(int32_t ninst, const lbm_config* cfgs, const int32_t* ndrop) {
@@ -120,6 +123,20 @@ void set_model(const lbm_config& c, InstDev& d) {
   d.n0 = c.n0;
 }
 
+// The tile shape of the tiled fused step for these lattices (see TILE_SHAPES), -1 where it does not apply.
+int tile_shape(const std::vector<InstDev>& inst) {
+  for (int k = 0; k < TILE_NSHAPES; ++k) {
+    const TileShape& s = TILE_SHAPES[k];
+    int64_t tiles = 0;
+    for (const InstDev& d : inst) {
+      if (d.ndrop > TILE_DROPS || d.nx < s.ox + TILE_RINGS || d.ny < s.oy + TILE_RINGS) return -1;
+      tiles += (int64_t)((d.nx + s.ox - 1) / s.ox) * ((d.ny + s.oy - 1) / s.oy);
+    }
+    if (tiles <= s.most) return k;
+  }
+  return -1;
+}
+
 void make_layout(int32_t ninst, const lbm_config* cfgs, const int32_t* ndrop, Layout& L) {
   L.prec = cfgs[0].precision;
   L.elem = L.prec == LBM_FP64 ? 8 : 4;
@@ -170,6 +187,17 @@ void make_layout(int32_t ninst, const lbm_config* cfgs, const int32_t* ndrop, La
     L.max_nd = std::max(L.max_nd, (int)d.ndrop);
     L.max_nodes = std::max(L.max_nodes, (int64_t)c.nx * c.ny);
   }
+  L.tshape = tile_shape(L.inst);
+  if (L.tshape >= 0)
+    for (InstDev& d : L.inst) {
+      const TileShape& t = TILE_SHAPES[L.tshape];
+      d.tiles_x[TILING_TILE] = (d.nx + t.ox - 1) / t.ox;
+      d.tiles_y[TILING_TILE] = (d.ny + t.oy - 1) / t.oy;
+      d.tile_base[TILING_TILE] = L.nttiles;
+      d.part_base[TILING_TILE] = L.tpart_elems;
+      L.nttiles += d.tiles_x[TILING_TILE] * d.tiles_y[TILING_TILE];
+      L.tpart_elems += (int64_t)d.tiles_x[TILING_TILE] * d.tiles_y[TILING_TILE] * d.ndrop * 6;
+    }
   L.ntiles = tile_base;
   L.nsegs = seg_base;
   L.ndrop_total = drop_base;
@@ -191,9 +219,9 @@ void make_layout(int32_t ninst, const lbm_config* cfgs, const int32_t* ndrop, La
     for (int t = 0; t < count; ++t) out[(size_t)(t % chunk) * nxcd + t / chunk] = natural[t];
   };
   build_list(TILING_SPLIT, TILE_X, TILE_Y, L.ntiles, L.tiles);
+  if (L.tshape >= 0) build_list(TILING_TILE, TILE_SHAPES[L.tshape].ox, TILE_SHAPES[L.tshape].oy, L.nttiles, L.ttiles);
   L.max_segs = L.nsegs;  // strips of the narrowest width and smallest height: sizes the strip list and partials
   L.max_seg_launch = ((L.nsegs + 7) / 8) * 8;
-  (void)build_list;
   size_t off = 0;
   L.off_pool = off;  off = align_up(off + (size_t)pool_elems * L.elem, ALIGN);
   L.off_inst = off;  off = align_up(off + sizeof(InstDev) * ninst, ALIGN);
@@ -209,6 +237,10 @@ void make_layout(int32_t ninst, const lbm_config* cfgs, const int32_t* ndrop, La
   L.off_obs = off;   off = align_up(off + sizeof(double) * (size_t)L.obs_stride * L.ntiles, ALIGN);
   L.off_dbg = off;
   off = align_up(off + sizeof(double) * (size_t)LBM_NSTAGE * std::min(L.max_nodes, DEBUG_MAX_NODES), ALIGN);
+  L.off_ttiles = off; off = align_up(off + sizeof(TileDev) * L.ttiles.size(), ALIGN);
+  L.off_tcen = off;   off = align_up(off + sizeof(double) * 4 * (size_t)(L.tshape >= 0 ? L.ndrop_total : 0), ALIGN);
+  L.off_tpart = off;  off = align_up(off + sizeof(double) * 2 * (size_t)L.tpart_elems, ALIGN);
+  L.off_tmask = off;  off = align_up(off + sizeof(uint32_t) * 2 * (size_t)L.nttiles, ALIGN);
   L.total = off;
 }
 
@@ -292,6 +324,7 @@ struct lbm_ctx {
   int64_t step = 0;
   int graph_steps = 0;
   int path = LBM_PATH_FUSED;
+  bool tile = false;  // the fused path takes its tiled kernel
   hipGraphExec_t exec[2] = {nullptr, nullptr};
   hipGraph_t graph[2] = {nullptr, nullptr};
   // the last recorded forward pass of lbm_adjoint_forward (see lbm_adjoint_backward)
@@ -304,6 +337,7 @@ struct lbm_ctx {
   void* pool() const { return ws + L.off_pool; }
   InstDev* d_inst() const { return reinterpret_cast<InstDev*>(ws + L.off_inst); }
   TileDev* d_tiles() const { return reinterpret_cast<TileDev*>(ws + L.off_tiles); }
+  TileDev* d_ttiles() const { return reinterpret_cast<TileDev*>(ws + L.off_ttiles); }
   TileDev* d_segs() const { return reinterpret_cast<TileDev*>(ws + L.off_segs); }
   DropDev* d_drops() const { return reinterpret_cast<DropDev*>(ws + L.off_drops); }
   double* d_part() const { return reinterpret_cast<double*>(ws + L.off_part); }
@@ -311,6 +345,23 @@ struct lbm_ctx {
   int64_t* d_step() const { return reinterpret_cast<int64_t*>(ws + L.off_step); }
   double* d_obs() const { return reinterpret_cast<double*>(ws + L.off_obs); }
   double* d_dbg() const { return reinterpret_cast<double*>(ws + L.off_dbg); }
+  bool tiled() const { return path == LBM_PATH_FUSED && tile; }
+  // The buffers of step number `ahead` of a sequence of tiled steps.
+  TileSeq tile_seq(int64_t ahead) const {
+    double* const cen = reinterpret_cast<double*>(ws + L.off_tcen);
+    double* const tpart = reinterpret_cast<double*>(ws + L.off_tpart);
+    uint32_t* const tmask = reinterpret_cast<uint32_t*>(ws + L.off_tmask);
+    const int out = (int)(ahead & 1), in = out ^ 1;
+    TileSeq q;
+    q.cen_in = ahead == 0 ? nullptr : cen + (size_t)in * 2 * L.ndrop_total;
+    q.part_in = tpart + (size_t)in * L.tpart_elems;
+    q.mask_in = tmask + (size_t)in * L.nttiles;
+    q.cen_out = cen + (size_t)out * 2 * L.ndrop_total;
+    q.part_out = tpart + (size_t)out * L.tpart_elems;
+    q.mask_out = tmask + (size_t)out * L.nttiles;
+    q.ahead = (int32_t)ahead;
+    return q;
+  }
   int nlaunch() const { return (int)L.tiles.size(); }
   int nseglaunch() const { return (int)L.segs.size(); }
 };
@@ -358,10 +409,17 @@ bool all_plain(const std::vector<InstDev>& inst) {
   return true;
 }
 
-// The sweeping kernel of a strip path (LBM_PATH_FUSED or LBM_PATH_WAVE) over the strip list.
+// The single kernel of a step on the fused or wave path: over the strip list, or the tiled one (as step number
+// `ahead` of its sequence).
 template <typename T, typename P>
-hipError_t launch_sweep(lbm_ctx* c, int parity, double* dbg, int dbg_inst) {
+hipError_t launch_sweep(lbm_ctx* c, int parity, double* dbg, int dbg_inst, int64_t ahead = 0) {
   T* buf = reinterpret_cast<T*>(c->pool());
+  if (c->tiled()) {
+    const bool alone = c->L.inst.size() == 1;
+    return launch_tile<T, P>(c->stream, parity, c->L.tshape, alone ? c->L.nttiles : (int)c->L.ttiles.size(),
+                             alone ? c->L.inst.data() : nullptr, c->d_ttiles(), c->d_inst(), buf, c->d_drops(),
+                             c->tile_seq(ahead), c->d_step(), dbg, dbg_inst);
+  }
   if (c->path == LBM_PATH_WAVE)
     return launch_wave<T, P>(c->stream, parity, c->nseglaunch(), c->d_segs(), c->d_inst(), buf, c->d_drops(),
                              c->d_part(), c->d_mask(), c->d_step(), dbg, dbg_inst, all_plain(c->L.inst));
@@ -379,23 +437,30 @@ hipError_t launch_split(lbm_ctx* c, int parity) {
                       c->d_mask(), c->d_step(), nullptr, -1);
 }
 
-template <typename T, typename P>
-hipError_t enqueue_step(lbm_ctx* c, int parity) {
-  hipError_t e;
-  if (c->path != LBM_PATH_SPLIT) {
-    e = launch_sweep<T, P>(c, parity, nullptr, -1);
-    if (e != hipSuccess) return e;
-    return launch_reduce(c->stream, TILING_FUSED, c->L.ndrop_total, c->d_inst(), c->d_drops(), c->d_part(),
-                         c->d_mask(), c->d_step(), 1);
-  }
-  e = launch_split<T, P>(c, parity);
-  if (e != hipSuccess) return e;
-  return launch_reduce(c->stream, TILING_SPLIT, c->L.ndrop_total, c->d_inst(), c->d_drops(), c->d_part(),
-                       c->d_mask(), c->d_step(), 1);
+// The centre-of-mass reduction and step counter after the kernels of one step of a path, or with tiled steps after
+// the last one of a sequence of n.  write = false: the sums alone (timing).
+hipError_t enqueue_reduce(lbm_ctx* c, int64_t n, bool write = true) {
+  if (c->tiled())
+    return launch_tile_final(c->stream, c->L.ndrop_total, c->d_inst(), c->d_drops(), c->tile_seq(n), c->d_step(),
+                             write ? n : 0);
+  return launch_reduce(c->stream, c->path == LBM_PATH_SPLIT ? TILING_SPLIT : TILING_FUSED, c->L.ndrop_total, c->d_inst(),
+                       c->d_drops(), c->d_part(), c->d_mask(), c->d_step(), write ? 1 : -1);
 }
 
-hipError_t enqueue_step_any(lbm_ctx* c, int parity) {
-  return with_types(c->L.prec, [&](auto t, auto p) { return enqueue_step<decltype(t), decltype(p)>(c, parity); });
+// n steps from the given parity.
+template <typename T, typename P>
+hipError_t enqueue_steps(lbm_ctx* c, int parity, int64_t n) {
+  hipError_t e = hipSuccess;
+  for (int64_t k = 0; k < n && e == hipSuccess; ++k, parity ^= 1) {
+    e = c->path == LBM_PATH_SPLIT ? launch_split<T, P>(c, parity) : launch_sweep<T, P>(c, parity, nullptr, -1, k);
+    if (e == hipSuccess && !c->tiled()) e = enqueue_reduce(c, 1);
+  }
+  if (e == hipSuccess && c->tiled() && n > 0) e = enqueue_reduce(c, n);
+  return e;
+}
+
+hipError_t enqueue_steps_any(lbm_ctx* c, int parity, int64_t n) {
+  return with_types(c->L.prec, [&](auto t, auto p) { return enqueue_steps<decltype(t), decltype(p)>(c, parity, n); });
 }
 
 void destroy_graphs(lbm_ctx* c) {
@@ -409,8 +474,7 @@ void destroy_graphs(lbm_ctx* c) {
 
 int build_graph(lbm_ctx* c, int parity) {
   HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed));
-  hipError_t err = hipSuccess;
-  for (int s = 0; s < c->graph_steps && err == hipSuccess; ++s) err = enqueue_step_any(c, (parity + s) & 1);
+  const hipError_t err = enqueue_steps_any(c, parity, c->graph_steps);
   hipGraph_t g = nullptr;
   hipError_t e2 = hipStreamEndCapture(c->stream, &g);
   if (err != hipSuccess) {
@@ -565,9 +629,7 @@ hipError_t timed_step(lbm_ctx* c, hipEvent_t* ev, int* nk) {
   if (c->path != LBM_PATH_SPLIT) {
     e = launch_sweep<T, P>(c, p, nullptr, -1);
     (void)hipEventRecord(ev[1], c->stream);
-    if (e == hipSuccess)
-      e = launch_reduce(c->stream, TILING_FUSED, c->L.ndrop_total, c->d_inst(), c->d_drops(), c->d_part(), c->d_mask(),
-                        c->d_step(), 1);
+    if (e == hipSuccess) e = enqueue_reduce(c, 1);
     (void)hipEventRecord(ev[2], c->stream);
     *nk = 2;
   } else {
@@ -577,9 +639,7 @@ hipError_t timed_step(lbm_ctx* c, hipEvent_t* ev, int* nk) {
       e = launch_fd<T>(c->stream, 0, p, c->nlaunch(), c->d_tiles(), c->d_inst(), buf, c->d_drops(), c->d_part(),
                        c->d_mask(), c->d_step(), nullptr, -1);
     (void)hipEventRecord(ev[2], c->stream);
-    if (e == hipSuccess)
-      e = launch_reduce(c->stream, TILING_SPLIT, c->L.ndrop_total, c->d_inst(), c->d_drops(), c->d_part(), c->d_mask(),
-                        c->d_step(), 1);
+    if (e == hipSuccess) e = enqueue_reduce(c, 1);
     (void)hipEventRecord(ev[3], c->stream);
     *nk = 3;
   }
@@ -837,6 +897,7 @@ int lbm_init_batch(int32_t ninst, const lbm_config* cfgs, void* workspace, size_
   c->ws = static_cast<char*>(workspace);
   c->stream = static_cast<hipStream_t>(stream);
   c->step = step;
+  c->tile = c->L.tshape >= 0;
   c->graph_steps = stream ? 20 : 0;
 
   auto bail = [&](int code) {
@@ -865,6 +926,9 @@ int lbm_init_batch(int32_t ninst, const lbm_config* cfgs, void* workspace, size_
                           c->stream));
   INIT_CHK(hipMemcpyAsync(c->d_segs(), c->L.segs.data(), sizeof(TileDev) * c->L.segs.size(), hipMemcpyHostToDevice,
                           c->stream));
+  if (!c->L.ttiles.empty())
+    INIT_CHK(hipMemcpyAsync(c->d_ttiles(), c->L.ttiles.data(), sizeof(TileDev) * c->L.ttiles.size(),
+                            hipMemcpyHostToDevice, c->stream));
   INIT_CHK(hipMemcpyAsync(c->d_drops(), dd.data(), sizeof(DropDev) * dd.size(), hipMemcpyHostToDevice, c->stream));
   INIT_CHK(hipMemcpyAsync(c->d_step(), &c->step, sizeof(int64_t), hipMemcpyHostToDevice, c->stream));
   INIT_CHK(hipMemsetAsync(c->d_mask(), 0, sizeof(uint64_t) * MASK_WORDS * std::max(c->L.ntiles, c->L.max_segs),
@@ -922,12 +986,10 @@ int lbm_step(lbm_ctx* c, int64_t n) {
       c->step += c->graph_steps;
     }
   }
-  for (; left > 0; --left) {
-    hipError_t e = enqueue_step_any(c, c->parity);
-    if (e != hipSuccess) return fail(LBM_E_HIP, std::string("timestep launch: ") + hipGetErrorString(e));
-    c->parity ^= 1;
-    c->step += 1;
-  }
+  const hipError_t e = enqueue_steps_any(c, c->parity, left);
+  if (e != hipSuccess) return fail(LBM_E_HIP, std::string("timestep launch: ") + hipGetErrorString(e));
+  c->parity ^= (int)(left & 1);
+  c->step += left;
   return LBM_OK;
 }
 
@@ -1084,9 +1146,7 @@ int lbm_time_launches(lbm_ctx* c, int32_t launches, double* ms_out) {
   // reduction in its mode that writes nothing
   const int nk = split ? 3 : 2;
   auto one = [&](int k) -> hipError_t {
-    if (k == nk - 1)
-      return launch_reduce(c->stream, split ? TILING_SPLIT : TILING_FUSED, c->L.ndrop_total, c->d_inst(), c->d_drops(),
-                           c->d_part(), c->d_mask(), c->d_step(), -1);
+    if (k == nk - 1) return enqueue_reduce(c, 1, false);
     return with_types(c->L.prec, [&](auto t, auto p) -> hipError_t {
       using T = decltype(t);
       using P = decltype(p);
@@ -1133,7 +1193,9 @@ int lbm_set_seg_rows(lbm_ctx* c, int32_t rows) {
   if (rows < SEG_ROWS_MIN || rows > SEG_ROWS_MAX)
     return fail(LBM_E_INVAL, "segment height must lie in [" + std::to_string(SEG_ROWS_MIN) + ", " +
                                  std::to_string(SEG_ROWS_MAX) + "]");
-  return apply_segments(c, rows, c->L.strip_w);
+  const int rc = apply_segments(c, rows, c->L.strip_w);
+  if (rc == LBM_OK) c->tile = false;  // the caller asks for strips
+  return rc;
 }
 
 int32_t lbm_get_seg_rows(const lbm_ctx* c) { return c ? c->L.seg_rows : -1; }
@@ -1143,7 +1205,9 @@ int lbm_set_strip_width(lbm_ctx* c, int32_t width) {
   if (width < STRIP_W_MIN || width > FUSED_TX)
     return fail(LBM_E_INVAL, "strip width must lie in [" + std::to_string(STRIP_W_MIN) + ", " +
                                  std::to_string(FUSED_TX) + "]");
-  return apply_segments(c, c->L.seg_rows, width);
+  const int rc = apply_segments(c, c->L.seg_rows, width);
+  if (rc == LBM_OK) c->tile = false;
+  return rc;
 }
 
 int32_t lbm_get_strip_width(const lbm_ctx* c) { return c ? c->L.strip_w : -1; }
@@ -1167,6 +1231,8 @@ int lbm_autotune(lbm_ctx* c, int32_t launches, int32_t both_paths, int32_t* rows
   }
   const int paths[2] = {LBM_PATH_FUSED, LBM_PATH_WAVE};
   const int start_path = c->path;
+  const bool start_tile = c->tile;
+  c->tile = false;  // the strips first; the tiled kernel is tried after them
   hipEvent_t e0, e1;
   HIPCHK(hipEventCreate(&e0));
   HIPCHK(hipEventCreate(&e1));
@@ -1232,40 +1298,56 @@ int lbm_autotune(lbm_ctx* c, int32_t launches, int32_t both_paths, int32_t* rows
           best_path = paths[pi];
         }
       }
-  // the split path (two tile kernels, no strip height) competes with the step time of the sweeping kernels
-  if (both_paths && rc == LBM_OK) {
-    c->path = LBM_PATH_SPLIT;
-    double split_ms = 1e300;
-    for (int pass = 0; pass < 2 && rc == LBM_OK; ++pass) {
-      hipError_t e = hipSuccess;
-      auto one = [&]() {
-        return with_types(c->L.prec,
-                          [&](auto t, auto p) { return launch_split<decltype(t), decltype(p)>(c, c->parity); });
-      };
-      e = one();
+  // the split path (two tile kernels) and the tiled fused step, which have no strip height, compete with the
+  // best strips
+  auto compete = [&](auto one, double& ms_best) -> int {
+    for (int pass = 0; pass < 2; ++pass) {
+      hipError_t e = one();
       (void)hipEventRecord(e0, c->stream);
       for (int rep = 0; rep < launches && e == hipSuccess; ++rep) e = one();
       (void)hipEventRecord(e1, c->stream);
       if (e == hipSuccess) e = hipEventSynchronize(e1);
-      if (e != hipSuccess) {
-        rc = fail(LBM_E_HIP, std::string("autotune launch: ") + hipGetErrorString(e));
-        break;
-      }
+      if (e != hipSuccess) return fail(LBM_E_HIP, std::string("autotune launch: ") + hipGetErrorString(e));
       float ms = 0.f;
       (void)hipEventElapsedTime(&ms, e0, e1);
-      split_ms = std::min(split_ms, (double)ms / launches);
+      ms_best = std::min(ms_best, (double)ms / launches);
     }
+    return LBM_OK;
+  };
+  bool best_tile = false;
+  if (both_paths && rc == LBM_OK) {
+    c->path = LBM_PATH_SPLIT;
+    double split_ms = 1e300;
+    rc = compete(
+        [&] {
+          return with_types(c->L.prec,
+                            [&](auto t, auto p) { return launch_split<decltype(t), decltype(p)>(c, c->parity); });
+        },
+        split_ms);
     if (ms_out && split_ms < 1e299) ms_out[2 * NW * NR] = split_ms;
     if (split_ms < best_ms) {
       best_ms = split_ms;
       best_path = LBM_PATH_SPLIT;
     }
   }
+  if (c->L.tshape >= 0 && (both_paths || start_path == LBM_PATH_FUSED) && rc == LBM_OK) {
+    c->path = LBM_PATH_FUSED;
+    c->tile = true;
+    double tile_ms = 1e300;
+    rc = compete([&] { return trial(1); }, tile_ms);
+    if (tile_ms < best_ms) {
+      best_ms = tile_ms;
+      best_path = LBM_PATH_FUSED;
+      best_tile = true;
+    }
+  }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   c->path = start_path;
+  c->tile = start_tile;
   if (rc != LBM_OK) return rc;
   if ((rc = lbm_set_path(c, best_path)) != LBM_OK) return rc;
+  if (best_path == LBM_PATH_FUSED) c->tile = best_tile;
   if ((rc = apply_segments(c, best_rows, best_w)) != LBM_OK) return rc;
   if (rows_out) *rows_out = best_rows;
   if (path_out) *path_out = best_path;
@@ -1501,9 +1583,7 @@ int adj_backward(lbm_ctx* c, const AdjLayout& A, char* w, double* dA0, double* d
       HIPCHK((debug_launch<T, T>(c, 0, fwd_rec(k - k0), false)));
       // the stage-export launch has also written the next state and the centre-of-mass partials, so only
       // the reduction is left of the step
-      hipError_t e = launch_reduce(c->stream, c->path == LBM_PATH_SPLIT ? TILING_SPLIT : TILING_FUSED,
-                                   c->L.ndrop_total, c->d_inst(), c->d_drops(), c->d_part(), c->d_mask(),
-                                   c->d_step(), 1);
+      const hipError_t e = enqueue_reduce(c, 1);
       if (e != hipSuccess) return fail(LBM_E_HIP, std::string("adjoint recompute: ") + hipGetErrorString(e));
       c->parity ^= 1;
       c->step += 1;

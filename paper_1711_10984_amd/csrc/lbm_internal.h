@@ -33,23 +33,26 @@ constexpr int SEG_ROWS_DEFAULT = 64;
 // Heights tried by the autotuner (LBM_TUNE_NROWS of them).
 constexpr int32_t TUNE_ROWS[] = {16, 20, 24, 26, 28, 32, 36, 40, 44, 48, 54, 64, 80, 96, 128, 256};
 static_assert(sizeof(TUNE_ROWS) / sizeof(TUNE_ROWS[0]) == LBM_TUNE_NROWS, "tune list length");
-// Tilings: 0 = split-kernel tiles, 1 = fused-kernel strips.
+// Tilings: 0 = split-kernel tiles, 1 = fused-kernel strips, 2 = the tiles of the tiled fused step.
 constexpr int TILING_SPLIT = 0;
 constexpr int TILING_FUSED = 1;
+constexpr int TILING_TILE = 2;
+constexpr int NTILINGS = 3;
 constexpr int MAXDROP = 256;   // droplets per instance
 constexpr int MASK_WORDS = MAXDROP / 64;  // one presence bit per droplet and tile
 
 // Per-instance description read by every kernel (device copy in the workspace).
 struct InstDev {
   int32_t nx, ny, pitch, ndrop;
-  int32_t tiles_x[2], tiles_y[2], tile_base[2];  // per tiling: counts and first natural index
+  int32_t tiles_x[NTILINGS], tiles_y[NTILINGS], tile_base[NTILINGS];  // per tiling: counts and first natural index
   int32_t drop_base, seg_rows;  // seg_rows: rows per sweeping-kernel strip segment
   int64_t pstride;     // elements between consecutive planes of the pool (ny * pitch)
   int64_t off_f[2];    // element offsets of the two population buffers [9][ny][pitch], planes pstride apart
   int64_t off_phi[2];  // the two phi buffers [ny][pitch]
   int64_t off_c[2];    // the two c buffers
   int64_t off_ux, off_uy, off_n;  // velocity planes written by the LB kernel; density (diagnostics)
-  int64_t part_base[2];  // per tiling: offset (doubles) of the centre-of-mass partials [tiles][ndrop][3]
+  int64_t part_base[NTILINGS];  // per tiling: offset (doubles) of the centre-of-mass partials [tiles][ndrop][3]
+                                // (TILING_TILE: [tiles][ndrop][6], sums in two parts)
   int32_t advection, walls;  // walls: LBM_WALLS_NONE or LBM_WALLS_Y
   int32_t strip_w, reserved;  // strip_w: columns owned per sweeping-kernel strip
   double yper;                // period of y in droplet distances and centres: ny, or infinite with walls
@@ -105,6 +108,38 @@ template <typename T, typename P>
 hipError_t launch_wave(hipStream_t s, int parity, int nseg_launch, const TileDev* segs, const InstDev* inst,
                        T* buf, const DropDev* drops, double* part, uint64_t* mask, const int64_t* step,
                        double* dbg, int dbg_inst, bool plain);
+// Tiled fused step (lbm_tile_impl.h) of lattices with at most TILE_DROPS droplets, on tiles of one of the shapes.
+// A sequence of steps keeps its droplet centres and sums in two alternating buffers: its first step takes the
+// centres of the droplet table (cen_in null), every later one those of the step before from cen_in, part_in and
+// mask_in, and launch_tile_final ends it (the table and, by `count` steps, the counter).  one: the description of
+// a lattice alone (null for a batch, which goes by `tiles` and `insts`).
+constexpr int TILE_DROPS = 16;
+struct TileShape {
+  int ox, oy, threads;  // nodes of a tile in x and y, threads of its workgroup
+  int most;             // tiles of a launch up to which the shape is taken
+};
+// Ascending: the first shape that covers the lattices in `most` tiles is taken.  A workgroup per compute unit at
+// most, on the smallest tiles that allow it: 64 x 64 takes 8.5 us per step on 16 x 8 tiles, 9.9 on 16 x 16 and 12.3
+// on 32 x 16; 256 x 256 12.3, 10.8 and 13.2; 512 x 256 22, 15.7 and 14.4 (FP64).  Twice as many of the largest tiles
+// at 512 x 512 (27.4) still match the split pair (30); at 768 x 768 (64) every strip kernel is faster (46).
+constexpr int TILE_NSHAPES = 3;
+constexpr TileShape TILE_SHAPES[TILE_NSHAPES] = {{16, 8, 512, 256}, {16, 16, 512, 256}, {32, 16, 1024, 512}};
+constexpr int TILE_RINGS = 5;  // a lattice is at least a tile and its rings on one side wide and high
+struct TileSeq {
+  const double* cen_in;  // [ndrop][2] centres that the sums of part_in are relative to
+  double* cen_out;       // the centres of this step
+  const double* part_in;
+  const uint32_t* mask_in;  // one presence bit per droplet and tile
+  double* part_out;
+  uint32_t* mask_out;
+  int32_t ahead;  // steps since the device's step counter
+};
+template <typename T, typename P>
+hipError_t launch_tile(hipStream_t s, int parity, int shape, int ntiles_launch, const InstDev* one, const TileDev* tiles,
+                       const InstDev* insts, T* buf, const DropDev* drops, const TileSeq& q, const int64_t* step,
+                       double* dbg, int dbg_inst);
+hipError_t launch_tile_final(hipStream_t s, int ndrop_total, const InstDev* inst, DropDev* drops, const TileSeq& q,
+                             int64_t* step, int64_t count);
 template <typename T, typename P>
 hipError_t launch_obs(hipStream_t s, int parity, int ntiles_launch, const TileDev* tiles,
                       const InstDev* inst, T* buf, const DropDev* drops, double* obs_part,

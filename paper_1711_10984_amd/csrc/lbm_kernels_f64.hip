@@ -2,6 +2,7 @@
 // Built without floating-point contraction: every FP64 expression is evaluated term by term in the
 // order written, which is the order of the plain definitions.
 #include "lbm_kernels_impl.h"
+#include "lbm_tile_impl.h"
 
 namespace lbm {
 
@@ -12,7 +13,15 @@ hipError_t launch_reduce(hipStream_t s, int tiling, int ndrop_total, const InstD
   return hipGetLastError();
 }
 
+hipError_t launch_tile_final(hipStream_t s, int ndrop_total, const InstDev* inst, DropDev* drops, const TileSeq& q,
+                             int64_t* step, int64_t count) {
+  hipLaunchKernelGGL(k_tile_final, dim3(ndrop_total > 0 ? ndrop_total : 1), dim3(64), 0, s, ndrop_total, inst, drops, q,
+                     step, count);
+  return hipGetLastError();
+}
+
 LBM_INSTANTIATE_FIELDS(double)
 LBM_INSTANTIATE_POPS(double, double)
+LBM_INSTANTIATE_TILE(double, double)
 
 }  // namespace lbm

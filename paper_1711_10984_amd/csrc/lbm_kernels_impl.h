@@ -88,6 +88,7 @@ __device__ __forceinline__ double minimg(double d, double L) {
 
 __device__ __forceinline__ double wrapd(double v, double L) {
   if (isinf(L)) return v;  // not periodic (y with walls)
+  if (v >= 0.0 && v < L) return v;
   double r = fmod(v, L);
   if (r < 0.0) r += L;
   if (r >= L) r -= L;
