@@ -692,7 +692,46 @@ int apply_segments(lbm_ctx* c, int rows, int width) {
 static __device__ __align__(256) unsigned char scratch[LBM_NOALLOC_SCRATCH_BYTES];
 
 constexpr int NOALLOC_MAX_DEVICES = 64;
-constexpr int NOALLOC_SEG_ROWS = 40;
+constexpr int NOALLOC_ROWS_MIN = 4, NOALLOC_ROWS_MAX = 128;
+constexpr int NOALLOC_ROWS_FIT = 40;  // the height that decides whether a lattice fits the scratch array
+constexpr int SIMDS = 1024;           // 256 compute units
+
+int noalloc_segments(int nx, int ny, int rows) { return ((nx + FUSED_TX - 1) / FUSED_TX) * ((ny + rows - 1) / rows); }
+
+// Wavefronts per SIMD that k_wave's segments are planned for.
+int noalloc_waves(int prec) { return prec == LBM_FP64 ? 2 : 3; }
+
+// Strip height of lbm_step_noalloc, which has no autotuner.  A segment sweeps its rows and ten more, one iteration
+// each, and an iteration takes as long as its SIMD's wavefronts make it: the height with the least
+// iterations x time, for the wavefronts per SIMD that its segments make (an extra one up to the most that are
+// planned for, a further round of them beyond).  Times of an iteration with 1, 2 and 3 wavefronts per SIMD, in us,
+// from launches on 700^2 to 2048^2 lattices.  FP64 leaves a tenth of the slots free: 2048^2 takes 193 us with 1786
+// wavefronts (44 rows), 200 with 1976 (40 rows).  Lattices of several rounds are bound by memory, and there the
+// shortest strips are the best or within 4 % of it: their neighbours read the shared halo rows soon after one
+// another (4096^2 FP32 432 us at 16 rows, 461 at 40, 460 at 80; 4096^2 FP64 759, 780, 801; FP16 storage is bound by
+// arithmetic, and its rounds count throughout: 4096^2 315, 291 and, in two rounds of 54 rows, 287).
+// The centres' sums are rounded by strip: lattices below 256 x 256 nodes, whose sweeps leave the chip idle at any
+// height, keep the 40 rows at which lbm_step's centres are the same to the bit.
+int noalloc_rows(int nx, int ny, int prec) {
+  if ((int64_t)nx * ny < 256 * 256) return NOALLOC_ROWS_FIT;
+  static constexpr double ITER[3][3] = {{2.1, 3.4, 3.4}, {1.6, 1.65, 1.97}, {1.5, 1.6, 1.97}};
+  const int most = noalloc_waves(prec);
+  const double per_round = (prec == LBM_FP64 ? 0.9 : 1.0) * SIMDS;
+  constexpr int SHORT = 16;
+  if (prec != LBM_FP16 && noalloc_segments(nx, ny, SHORT) >= 4.5 * most * per_round) return SHORT;
+  int best = NOALLOC_ROWS_FIT;
+  double best_cost = 1e300;
+  for (int h = NOALLOC_ROWS_MIN; h <= NOALLOC_ROWS_MAX; ++h) {
+    const int waves = std::max(1, (int)std::ceil(noalloc_segments(nx, ny, h) / per_round));
+    const int rounds = (waves + most - 1) / most;
+    const double cost = rounds * (h + 10) * ITER[prec][std::min(waves, most) - 1];
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = h;
+    }
+  }
+  return best;
+}
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[NOALLOC_MAX_DEVICES] = {};
 
@@ -730,23 +769,21 @@ NoallocLayout noalloc_layout(int nsegs, int nslots, int ndrop) {
   return L;
 }
 
-// Fills the scratch regions: instance description, step counter, droplet table (from the caller's), the strip
-// list in the XCD-aware order of set_segments (natural strip t at slot (t mod chunk) * 8 + t / chunk), and the
-// presence masks cleared.
-__global__ __launch_bounds__(NTHREADS) void k_noalloc_setup(InstDev inst, int64_t step, NoallocLayout L, int nsegs,
-                                                            int nslots, int chunk, int ndrop,
-                                                            const lbm_droplet* __restrict__ drops, char* __restrict__ s) {
-  const int gid = blockIdx.x * blockDim.x + threadIdx.x;
-  const int stride = gridDim.x * blockDim.x;
+// Fills the scratch regions: instance description, step counter, droplet table (from the caller's), the presence
+// masks cleared, and the strip list in the XCD-aware order of set_segments: block j < 8 lists the run of natural
+// strips [j * chunk, (j + 1) * chunk) in the slots j, j + 8, ..., those near a droplet first if `order` is set (as
+// set_segments does: the longer-running strips do not end the launch).  Any table gives a permutation of the strips.
+constexpr int SETUP_THREADS = 1024;
+__global__ __launch_bounds__(SETUP_THREADS) void k_noalloc_setup(InstDev inst, int64_t step, NoallocLayout L, int nsegs,
+                                                                 int chunk, int ndrop, int order,
+                                                                 const lbm_droplet* __restrict__ drops,
+                                                                 char* __restrict__ s) {
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int gid = blockIdx.x * SETUP_THREADS + tid;
+  const int stride = gridDim.x * SETUP_THREADS;
   if (gid == 0) {
     *reinterpret_cast<InstDev*>(s + L.inst) = inst;
     *reinterpret_cast<int64_t*>(s + L.step) = step;
-  }
-  const int tx = inst.tiles_x[TILING_FUSED];
-  TileDev* segs = reinterpret_cast<TileDev*>(s + L.segs);
-  for (int b = gid; b < nslots; b += stride) {
-    const int t = (b % 8) * chunk + b / 8;
-    segs[b] = t < nsegs ? TileDev{0, (t % tx) * inst.strip_w, (t / tx) * inst.seg_rows, t} : TileDev{-1, 0, 0, -1};
   }
   uint64_t* mask = reinterpret_cast<uint64_t*>(s + L.mask);
   for (int m = gid; m < nsegs * MASK_WORDS; m += stride) mask[m] = 0ull;
@@ -755,6 +792,54 @@ __global__ __launch_bounds__(NTHREADS) void k_noalloc_setup(InstDev inst, int64_
     const lbm_droplet q = drops[k];
     dd[k] = DropDev{q.x, q.y, q.R, q.Rs, q.ex, q.ey, q.active ? 1 : 0, 0};
   }
+  if (blockIdx.x >= 8) return;
+  constexpr int NW = SETUP_THREADS / 64;
+  __shared__ double s_drop[MAXDROP][3];  // centre and reach
+  __shared__ int s_count[NW], s_done;
+  if (order)
+    for (int k = tid; k < ndrop; k += SETUP_THREADS) {
+      s_drop[k][0] = drops[k].x;
+      s_drop[k][1] = drops[k].y;
+      s_drop[k][2] = drops[k].R + 2.0;
+    }
+  if (tid == 0) s_done = 0;
+  __syncthreads();
+  const int tx = inst.tiles_x[TILING_FUSED];
+  const int t0 = blockIdx.x * chunk, t1 = min(nsegs, t0 + chunk);
+  TileDev* const run = reinterpret_cast<TileDev*>(s + L.segs) + blockIdx.x;  // every eighth slot
+  for (int pass = order ? 0 : 1; pass < 2; ++pass) {
+    for (int base = t0; base < t1; base += SETUP_THREADS) {
+      const int t = base + tid;
+      const TileDev e{0, (t % tx) * inst.strip_w, (t / tx) * inst.seg_rows, t};
+      bool near = false;
+      if (order && t < t1) {
+        const int x1 = min(e.x0 + inst.strip_w, inst.nx) - 1, y1 = min(e.y0 + inst.seg_rows, inst.ny) - 1;
+        const double xm = 0.5 * (e.x0 + x1), ym = 0.5 * (e.y0 + y1), hx = 0.5 * (x1 - e.x0), hy = 0.5 * (y1 - e.y0);
+        for (int k = 0; k < ndrop && !near; ++k) {
+          double dx = fabs(xm - s_drop[k][0]), dy = fabs(ym - s_drop[k][1]);
+          if (dx > 0.5 * inst.nx) dx = inst.nx - dx;
+          if (!inst.walls && dy > 0.5 * inst.ny) dy = inst.ny - dy;
+          dx = fmax(0.0, dx - hx);
+          dy = fmax(0.0, dy - hy);
+          near = dx * dx + dy * dy <= s_drop[k][2] * s_drop[k][2];
+        }
+      }
+      const bool mine = t < t1 && (!order || near == (pass == 0));
+      const unsigned long long b = __ballot(mine);
+      if (lane == 0) s_count[wv] = __popcll(b);
+      __syncthreads();
+      int at = s_done + __popcll(b & ((1ull << lane) - 1ull)), all = 0;
+      for (int w = 0; w < NW; ++w) {
+        at += w < wv ? s_count[w] : 0;
+        all += s_count[w];
+      }
+      if (mine) run[(size_t)at * 8] = e;
+      __syncthreads();
+      if (tid == 0) s_done += all;
+      __syncthreads();
+    }
+  }
+  for (int k = max(t1 - t0, 0) + tid; k < chunk; k += SETUP_THREADS) run[(size_t)k * 8] = TileDev{-1, 0, 0, -1};
 }
 
 // The new centres back into the caller's droplet table.
@@ -793,9 +878,15 @@ int lbm_step_noalloc(const lbm_config* cfg, void* stream, void* const f[2], void
   d.pstride = (int64_t)cf.nx * cf.ny;
   d.ndrop = ndrop;
   d.strip_w = FUSED_TX;
-  d.seg_rows = NOALLOC_SEG_ROWS;
+  // taller strips than the rule's where only those fit the scratch array
+  auto layout_of = [&](int rows) {
+    const int n = noalloc_segments(cf.nx, cf.ny, rows);
+    return noalloc_layout(n, (n + 7) / 8 * 8, ndrop);
+  };
+  d.seg_rows = noalloc_rows(cf.nx, cf.ny, cf.precision);
+  if (layout_of(d.seg_rows).total > LBM_NOALLOC_SCRATCH_BYTES) d.seg_rows = std::max(d.seg_rows, NOALLOC_ROWS_FIT);
   d.tiles_x[TILING_FUSED] = (cf.nx + FUSED_TX - 1) / FUSED_TX;
-  d.tiles_y[TILING_FUSED] = (cf.ny + NOALLOC_SEG_ROWS - 1) / NOALLOC_SEG_ROWS;
+  d.tiles_y[TILING_FUSED] = (cf.ny + d.seg_rows - 1) / d.seg_rows;
   // element offsets of the caller's buffers from f[0] (the pool base of the kernels); 256-byte alignment makes
   // every difference a whole number of elements
   const char* base = static_cast<const char*>(f[0]);
@@ -810,17 +901,20 @@ int lbm_step_noalloc(const lbm_config* cfg, void* stream, void* const f[2], void
   const int nsegs = d.tiles_x[TILING_FUSED] * d.tiles_y[TILING_FUSED];
   const int nslots = (nsegs + 7) / 8 * 8;
   const NoallocLayout L = noalloc_layout(nsegs, nslots, ndrop);
-  if (L.total > LBM_NOALLOC_SCRATCH_BYTES)
-    return fail(LBM_E_NOMEM, "this lattice and droplet count need " + std::to_string(L.total) +
+  const size_t need = layout_of(NOALLOC_ROWS_FIT).total;
+  if (need > LBM_NOALLOC_SCRATCH_BYTES)
+    return fail(LBM_E_NOMEM, "this lattice and droplet count need " + std::to_string(need) +
                                  " bytes of scratch, more than LBM_NOALLOC_SCRATCH_BYTES (" +
                                  std::to_string((size_t)LBM_NOALLOC_SCRATCH_BYTES) + ")");
   void* sp = nullptr;
   if ((rc = scratch_on_current_device(&sp)) != LBM_OK) return rc;
   char* s = static_cast<char*>(sp);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int work = std::max(std::max(nslots, nsegs * MASK_WORDS), ndrop);
-  hipLaunchKernelGGL(k_noalloc_setup, dim3((work + NTHREADS - 1) / NTHREADS), dim3(NTHREADS), 0, st, d, step, L, nsegs,
-                     nslots, nslots / 8, ndrop, drops, s);
+  // with strips for a second round and more, the order within a run no longer decides how the launch ends
+  const bool order = ndrop > 0 && nsegs <= 4 * SIMDS;
+  const int blocks = std::max(8, (nsegs * MASK_WORDS + SETUP_THREADS - 1) / SETUP_THREADS);
+  hipLaunchKernelGGL(k_noalloc_setup, dim3(blocks), dim3(SETUP_THREADS), 0, st, d, step, L, nsegs, nslots / 8, ndrop,
+                     order ? 1 : 0, drops, s);
   HIPCHK(hipGetLastError());
   const InstDev* di = reinterpret_cast<const InstDev*>(s + L.inst);
   const TileDev* segs = reinterpret_cast<const TileDev*>(s + L.segs);
