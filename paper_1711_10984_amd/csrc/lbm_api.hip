@@ -325,6 +325,11 @@ struct lbm_ctx {
   int graph_steps = 0;
   int path = LBM_PATH_FUSED;
   bool tile = false;  // the fused path takes its tiled kernel
+  // page-locked host memory that read-backs go through: allocated by the first of them, grown to what they need (at
+  // most 2 x READ_CHUNK and a little), freed with the context
+  char* pinned = nullptr;
+  size_t pinned_bytes = 0;
+  hipEvent_t read_ev[2] = {nullptr, nullptr};
   hipGraphExec_t exec[2] = {nullptr, nullptr};
   hipGraph_t graph[2] = {nullptr, nullptr};
   // the last recorded forward pass of lbm_adjoint_forward (see lbm_adjoint_backward)
@@ -390,18 +395,6 @@ P host_pop_store(double f, double wn) {
     return (P)((float)f - (float)wn);
   }
 }
-template <typename T, typename P>
-double host_pop_load(P s, double wn) {
-  if constexpr (sizeof(T) == 8) {
-    (void)wn;
-    return (double)s;
-  } else if constexpr (std::is_same<T, P>::value) {
-    return (double)s + (double)(float)wn;
-  } else {
-    return (double)((float)s + (float)wn);
-  }
-}
-
 // Whether every instance is periodic in y with the printed advection (the wave kernel's specialised case).
 bool all_plain(const std::vector<InstDev>& inst) {
   for (const InstDev& d : inst)
@@ -544,64 +537,83 @@ int check_inst(lbm_ctx* c, int32_t inst) {
   return LBM_OK;
 }
 
-// n, u planes of every instance from the current state (Eq. 11 with the force of Eq. 14).
-int run_diag(lbm_ctx* c) {
+// n, u planes of an instance from the current state (Eq. 11 with the force of Eq. 14).
+int run_diag(lbm_ctx* c, int inst) {
   const hipError_t e = with_types(c->L.prec, [&](auto t, auto p) {
     using T = decltype(t);
     return launch_lb<T, decltype(p)>(c->stream, 2, c->parity, c->nlaunch(), c->d_tiles(), c->d_inst(),
-                                     reinterpret_cast<T*>(c->pool()), nullptr, -1);
+                                     reinterpret_cast<T*>(c->pool()), nullptr, inst);
   });
   if (e != hipSuccess) return fail(LBM_E_HIP, std::string("diagnostic launch: ") + hipGetErrorString(e));
   return LBM_OK;
 }
 
-template <typename T>
-int download_plane(lbm_ctx* c, int64_t off, const InstDev& d, double* out) {
-  const size_t plane = (size_t)d.pstride;
-  std::vector<T> h(plane);
-  HIPCHK(hipMemcpyAsync(h.data(), reinterpret_cast<T*>(c->pool()) + off, plane * sizeof(T), hipMemcpyDeviceToHost,
-                        c->stream));
-  HIPCHK(hipStreamSynchronize(c->stream));
-  for (int y = 0; y < d.ny; ++y)
-    for (int x = 0; x < d.nx; ++x) out[(size_t)y * d.nx + x] = (double)h[(size_t)y * d.pitch + x];
+// Read-backs of more than READ_CHUNK bytes go in chunks, through the two halves of the page-locked memory: the host
+// copies one chunk out while the kernel fills the next.  Small chunks, because the memory is locked at 0.4 ms per MB by
+// a context's first read-back (2 MB chunks add 1.7 ms to it, and save 0.06 ms of a 256 x 256 read-back).
+constexpr size_t READ_CHUNK = 512u << 10;
+constexpr size_t READ_HEAD = 64;  // bytes before a chunk's values: its flag of non-finite ones
+
+int need_pinned(lbm_ctx* c, size_t bytes) {
+  if (bytes <= c->pinned_bytes) return LBM_OK;
+  bytes = align_up(bytes, 16384);  // a droplet table's worth at least
+  if (c->pinned) HIPCHK(hipHostFree(c->pinned));
+  c->pinned = nullptr;
+  c->pinned_bytes = 0;
+  void* p = nullptr;
+  HIPCHK(hipHostMalloc(&p, bytes, hipHostMallocCoherent));
+  c->pinned = static_cast<char*>(p);
+  c->pinned_bytes = bytes;
   return LBM_OK;
 }
 
+// The requested fields of an instance (null: not requested) as the caller's arrays hold them; `finite` tells whether
+// all their values are.
 template <typename T, typename P>
-int fields_impl(lbm_ctx* c, int inst, double* f_pre, double* phi, double* cc, double* n, double* ux,
-                double* uy) {
+int fields_impl(lbm_ctx* c, int inst, double* f_pre, double* phi, double* cc, double* n, double* ux, double* uy,
+                bool& finite) {
   const InstDev& d = c->L.inst[inst];
-  int rc;
-  if (n || ux || uy) {
-    if ((rc = run_diag(c)) != LBM_OK) return rc;
-  }
-  if (phi && (rc = download_plane<T>(c, d.off_phi[c->parity], d, phi)) != LBM_OK) return rc;
-  if (cc && (rc = download_plane<T>(c, d.off_c[c->parity], d, cc)) != LBM_OK) return rc;
-  if (n && (rc = download_plane<T>(c, d.off_n, d, n)) != LBM_OK) return rc;
-  if (ux && (rc = download_plane<T>(c, d.off_ux, d, ux)) != LBM_OK) return rc;
-  if (uy && (rc = download_plane<T>(c, d.off_uy, d, uy)) != LBM_OK) return rc;
-  if (f_pre) {
-    const size_t plane = (size_t)d.pstride;
-    std::vector<P> h(9 * plane);
-    HIPCHK(hipMemcpyAsync(h.data(), reinterpret_cast<P*>(reinterpret_cast<T*>(c->pool()) + d.off_f[c->parity]),
-                          9 * plane * sizeof(P), hipMemcpyDeviceToHost, c->stream));
+  const int64_t nodes = (int64_t)d.nx * d.ny;
+  double* dst[14];
+  int np = 0, rc;
+  finite = true;
+  for (int k = 0; f_pre && k < 9; ++k) dst[np++] = f_pre + k * nodes;
+  for (double* o : {phi, cc, n, ux, uy})
+    if (o) dst[np++] = o;
+  const int want = (f_pre ? FIELD_F : 0) | (phi ? FIELD_PHI : 0) | (cc ? FIELD_C : 0) | (n ? FIELD_N : 0) |
+                   (ux ? FIELD_UX : 0) | (uy ? FIELD_UY : 0);
+  if (np == 0) {
     HIPCHK(hipStreamSynchronize(c->stream));
-    const int nx = d.nx, ny = d.ny;
-    const bool walls = d.walls != 0;
-    for (int k = 0; k < 9; ++k)
-      for (int y = 0; y < ny; ++y)
-        for (int x = 0; x < nx; ++x) {
-          // pre-collision f_k(r) = f*_k(r - e_k), or with walls f*_OPP[k](r) when r - e_k is behind a plate
-          const int yf = y - EY[k];
-          size_t src;
-          if (walls && (yf < 0 || yf >= ny)) {
-            src = (size_t)OPP[k] * plane + (size_t)y * d.pitch + x;
-          } else {
-            const int xs = (x - EX[k] + nx) % nx, ys = (yf + ny) % ny;
-            src = (size_t)k * plane + (size_t)ys * d.pitch + xs;
-          }
-          f_pre[(size_t)k * nx * ny + (size_t)y * nx + x] = host_pop_load<T, P>(h[src], WGT[k] * c->cfg[inst].n0);
-        }
+    return LBM_OK;
+  }
+  const size_t node_bytes = sizeof(double) * np;
+  const int64_t per = (size_t)nodes * node_bytes <= READ_CHUNK ? nodes : (int64_t)(READ_CHUNK / node_bytes);
+  const int64_t chunks = (nodes + per - 1) / per;
+  const size_t half = align_up(READ_HEAD + (size_t)per * node_bytes, ALIGN);
+  if ((rc = need_pinned(c, chunks > 1 ? 2 * half : half)) != LBM_OK) return rc;
+  for (int k = 0; chunks > 1 && k < 2; ++k)
+    if (!c->read_ev[k]) HIPCHK(hipEventCreateWithFlags(&c->read_ev[k], hipEventDisableTiming));
+  if ((n || ux || uy) && (rc = run_diag(c, inst)) != LBM_OK) return rc;
+  for (int64_t k = 0; k <= chunks; ++k) {
+    if (k < chunks) {
+      char* const h = c->pinned + (k & 1) * half;
+      const int64_t first = k * per;
+      *reinterpret_cast<uint32_t*>(h) = 0u;
+      HIPCHK((launch_fields<T, P>(c->stream, d, c->parity, reinterpret_cast<const T*>(c->pool()), first,
+                                  std::min(per, nodes - first), want, reinterpret_cast<double*>(h + READ_HEAD),
+                                  reinterpret_cast<uint32_t*>(h))));
+      if (chunks > 1) HIPCHK(hipEventRecord(c->read_ev[k & 1], c->stream));
+    }
+    if (k == 0) continue;
+    if (chunks > 1)
+      HIPCHK(hipEventSynchronize(c->read_ev[(k - 1) & 1]));
+    else
+      HIPCHK(hipStreamSynchronize(c->stream));
+    const char* const h = c->pinned + ((k - 1) & 1) * half;
+    const int64_t first = (k - 1) * per, count = std::min(per, nodes - first);
+    const double* v = reinterpret_cast<const double*>(h + READ_HEAD);
+    for (int j = 0; j < np; ++j, v += count) memcpy(dst[j] + first, v, sizeof(double) * (size_t)count);
+    if (*reinterpret_cast<const uint32_t*>(h)) finite = false;
   }
   return LBM_OK;
 }
@@ -652,9 +664,12 @@ int read_drops(lbm_ctx* c, int inst, std::vector<DropDev>& out) {
   const InstDev& d = c->L.inst[inst];
   out.resize(d.ndrop);
   if (d.ndrop == 0) return LBM_OK;
-  HIPCHK(hipMemcpyAsync(out.data(), c->d_drops() + d.drop_base, sizeof(DropDev) * d.ndrop, hipMemcpyDeviceToHost,
-                        c->stream));
+  const size_t bytes = sizeof(DropDev) * d.ndrop;
+  const int rc = need_pinned(c, bytes);
+  if (rc != LBM_OK) return rc;
+  HIPCHK(hipMemcpyAsync(c->pinned, c->d_drops() + d.drop_base, bytes, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
+  memcpy(out.data(), c->pinned, bytes);
   return LBM_OK;
 }
 
@@ -1099,22 +1114,13 @@ int lbm_fields(lbm_ctx* c, int32_t inst, double* f_pre, double* phi, double* cc,
   Range range("lbm_fields");
   int rc = check_inst(c, inst);
   if (rc != LBM_OK) return rc;
-  HIPCHK(hipStreamSynchronize(c->stream));
+  bool finite = true;
   rc = with_types(c->L.prec, [&](auto t, auto p) {
-    return fields_impl<decltype(t), decltype(p)>(c, inst, f_pre, phi, cc, n, ux, uy);
+    return fields_impl<decltype(t), decltype(p)>(c, inst, f_pre, phi, cc, n, ux, uy, finite);
   });
   if (rc != LBM_OK) return rc;
   // a non-finite state surfaces here as well as in lbm_observables (the arrays are filled regardless)
-  const size_t np = (size_t)c->L.inst[inst].nx * c->L.inst[inst].ny;
-  const struct {
-    const double* a;
-    size_t n;
-  } outs[6] = {{f_pre, 9 * np}, {phi, np}, {cc, np}, {n, np}, {ux, np}, {uy, np}};
-  for (const auto& o : outs)
-    if (o.a)
-      for (size_t i = 0; i < o.n; ++i)
-        if (!std::isfinite(o.a[i])) return fail(LBM_E_UNSTABLE, "non-finite values in the state");
-  return LBM_OK;
+  return finite ? LBM_OK : fail(LBM_E_UNSTABLE, "non-finite values in the state");
 }
 
 int lbm_droplets(lbm_ctx* c, int32_t inst, lbm_droplet* out) {
@@ -1133,7 +1139,7 @@ int lbm_observables(lbm_ctx* c, int32_t inst, lbm_obs* obs, double* drop_out) {
   int rc = check_inst(c, inst);
   if (rc != LBM_OK) return rc;
   if (!obs) return fail(LBM_E_INVAL, "obs must not be NULL");
-  if ((rc = run_diag(c)) != LBM_OK) return rc;
+  if ((rc = run_diag(c, inst)) != LBM_OK) return rc;
   hipError_t e = with_types(c->L.prec, [&](auto t, auto p) {
     using T = decltype(t);
     return launch_obs<T, decltype(p)>(c->stream, c->parity, c->nlaunch(), c->d_tiles(), c->d_inst(),
@@ -1470,6 +1476,9 @@ int32_t lbm_get_path(const lbm_ctx* c) { return c ? c->path : -1; }
 void lbm_destroy(lbm_ctx* c) {
   if (!c) return;
   destroy_graphs(c);
+  if (c->pinned) (void)hipHostFree(c->pinned);
+  for (hipEvent_t e : c->read_ev)
+    if (e) (void)hipEventDestroy(e);
   delete c;
 }
 

@@ -76,8 +76,8 @@ struct TileDev {
 // Launch helpers, instantiated in lbm_kernels_f64.hip, lbm_kernels_f32.hip and lbm_kernels_f16.hip.
 // T is the arithmetic (and field) type, P the population storage type (T itself, or _Float16 deviations
 // from w_i n0 with T = float).  `buf` is the typed base pointer of the field pool, `parity` selects the
-// current buffers.  Modes: 0 step, 1 step + stage export, 2 diagnostics only.  An export names its instance
-// in dbg_inst: inst exports all LBM_NSTAGE planes, -2 - inst (export_planes()) only the first ADJ_EXPORT_PLANES
+// current buffers.  Modes: 0 step, 1 step + stage export, 2 diagnostics (n, u) of instance dbg_inst only.  An export
+// names its instance in dbg_inst: inst exports all LBM_NSTAGE planes, -2 - inst (export_planes()) only the first ADJ_EXPORT_PLANES
 // (mu .. X^{n+1/2}), which the reverse mode reads.
 constexpr int ADJ_EXPORT_PLANES = 11;
 inline int export_planes(int inst, bool all) { return all ? inst : -2 - inst; }
@@ -140,6 +140,11 @@ hipError_t launch_tile(hipStream_t s, int parity, int shape, int ntiles_launch, 
                        double* dbg, int dbg_inst);
 hipError_t launch_tile_final(hipStream_t s, int ndrop_total, const InstDev* inst, DropDev* drops, const TileSeq& q,
                              int64_t* step, int64_t count);
+// Fields of nodes [first, first + count) of a lattice to page-locked host memory (k_fields).
+constexpr int FIELD_F = 1, FIELD_PHI = 2, FIELD_C = 4, FIELD_N = 8, FIELD_UX = 16, FIELD_UY = 32;
+template <typename T, typename P>
+hipError_t launch_fields(hipStream_t s, const InstDev& inst, int parity, const T* buf, int64_t first, int64_t count,
+                         int want, double* out, uint32_t* bad);
 template <typename T, typename P>
 hipError_t launch_obs(hipStream_t s, int parity, int ntiles_launch, const TileDev* tiles,
                       const InstDev* inst, T* buf, const DropDev* drops, double* obs_part,
