@@ -201,7 +201,7 @@ void make_layout(int32_t ninst, const lbm_config* cfgs, const int32_t* ndrop, La
   L.ntiles = tile_base;
   L.nsegs = seg_base;
   L.ndrop_total = drop_base;
-  L.obs_stride = 6 + 3 * L.max_nd;
+  L.obs_stride = OBS_STRIDE(L.max_nd);
   // Work lists in launch order: workgroup b runs on XCD (b mod 8); give each XCD a contiguous run of
   // tiles (raster order within an instance) so that neighbouring tiles share that XCD's L2.
   auto build_list = [&](int tiling, int tw, int th, int count, std::vector<TileDev>& out) {
@@ -1139,52 +1139,36 @@ int lbm_observables(lbm_ctx* c, int32_t inst, lbm_obs* obs, double* drop_out) {
   int rc = check_inst(c, inst);
   if (rc != LBM_OK) return rc;
   if (!obs) return fail(LBM_E_INVAL, "obs must not be NULL");
-  if ((rc = run_diag(c, inst)) != LBM_OK) return rc;
+  const int nd = c->L.inst[inst].ndrop;
+  if ((rc = need_pinned(c, sizeof(double) * (6 + 5 * (size_t)nd))) != LBM_OK) return rc;
+  const double* const r = reinterpret_cast<const double*>(c->pinned);
   hipError_t e = with_types(c->L.prec, [&](auto t, auto p) {
     using T = decltype(t);
     return launch_obs<T, decltype(p)>(c->stream, c->parity, c->nlaunch(), c->d_tiles(), c->d_inst(),
-                                      reinterpret_cast<T*>(c->pool()), c->d_drops(), c->d_obs(), c->L.obs_stride);
+                                      reinterpret_cast<const T*>(c->pool()), c->d_drops(), inst, c->d_obs(),
+                                      c->L.obs_stride);
   });
+  if (e == hipSuccess)
+    e = launch_obs_final(c->stream, c->d_inst(), inst, nd, c->d_drops(), c->d_obs(), c->L.obs_stride,
+                         reinterpret_cast<double*>(c->pinned));
   if (e != hipSuccess) return fail(LBM_E_HIP, std::string("observables launch: ") + hipGetErrorString(e));
-  const InstDev& d = c->L.inst[inst];
-  const int nt = d.tiles_x[TILING_SPLIT] * d.tiles_y[TILING_SPLIT], S = c->L.obs_stride;
-  std::vector<double> h((size_t)nt * S);
-  HIPCHK(hipMemcpyAsync(h.data(), c->d_obs() + (size_t)d.tile_base[TILING_SPLIT] * S, h.size() * sizeof(double),
-                        hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
-  std::vector<DropDev> dd;
-  if ((rc = read_drops(c, inst, dd)) != LBM_OK) return rc;
-  double m = 0, sp = 0, sc = 0, mb = INFINITY, mu = 0, nf = 0;
-  std::vector<double> sw(d.ndrop, 0.0), su(d.ndrop, 0.0), sv(d.ndrop, 0.0);
-  for (int t = 0; t < nt; ++t) {
-    const double* o = &h[(size_t)t * S];
-    m += o[0];
-    sp += o[1];
-    sc += o[2];
-    mb = std::min(mb, o[3]);
-    mu = std::max(mu, o[4]);
-    nf = std::max(nf, o[5]);
-    for (int k = 0; k < d.ndrop; ++k) {
-      sw[k] += o[6 + 3 * k];
-      su[k] += o[7 + 3 * k];
-      sv[k] += o[8 + 3 * k];
-    }
-  }
   obs->step = c->step;
-  obs->mass = m;
-  obs->sum_phi = sp;
-  obs->sum_c = sc;
-  obs->min_B = mb;
-  obs->max_u = mu;
-  obs->nonfinite = (nf != 0.0 || !std::isfinite(m) || !std::isfinite(sp) || !std::isfinite(sc)) ? 1 : 0;
-  obs->ndrop = d.ndrop;
+  obs->mass = r[0];
+  obs->sum_phi = r[1];
+  obs->sum_c = r[2];
+  obs->min_B = r[3];
+  obs->max_u = r[4];
+  obs->nonfinite = (r[5] != 0.0 || !std::isfinite(r[0]) || !std::isfinite(r[1]) || !std::isfinite(r[2])) ? 1 : 0;
+  obs->ndrop = nd;
   if (drop_out) {
-    for (int k = 0; k < d.ndrop; ++k) {
-      drop_out[5 * k + 0] = dd[k].x;
-      drop_out[5 * k + 1] = dd[k].y;
-      drop_out[5 * k + 2] = sw[k] > 0.0 ? su[k] / sw[k] : 0.0;
-      drop_out[5 * k + 3] = sw[k] > 0.0 ? sv[k] / sw[k] : 0.0;
-      drop_out[5 * k + 4] = sw[k];
+    for (int k = 0; k < nd; ++k) {
+      const double* const d = r + 6 + 5 * k;  // x, y, sum phi, sum phi ux, sum phi uy
+      drop_out[5 * k + 0] = d[0];
+      drop_out[5 * k + 1] = d[1];
+      drop_out[5 * k + 2] = d[2] > 0.0 ? d[3] / d[2] : 0.0;
+      drop_out[5 * k + 3] = d[2] > 0.0 ? d[4] / d[2] : 0.0;
+      drop_out[5 * k + 4] = d[2];
     }
   }
   if (obs->nonfinite) return fail(LBM_E_UNSTABLE, "non-finite values in the state");

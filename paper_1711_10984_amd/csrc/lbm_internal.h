@@ -145,9 +145,13 @@ constexpr int FIELD_F = 1, FIELD_PHI = 2, FIELD_C = 4, FIELD_N = 8, FIELD_UX = 1
 template <typename T, typename P>
 hipError_t launch_fields(hipStream_t s, const InstDev& inst, int parity, const T* buf, int64_t first, int64_t count,
                          int want, double* out, uint32_t* bad);
+// Observables of instance `inst`: per-tile partials (OBS_STRIDE(droplets) doubles per tile), then their sums to
+// page-locked host memory (6 + 5 ndrop doubles, see k_obs_final).
+constexpr int OBS_STRIDE(int ndrop) { return 6 + 3 * ndrop + MASK_WORDS; }
 template <typename T, typename P>
-hipError_t launch_obs(hipStream_t s, int parity, int ntiles_launch, const TileDev* tiles,
-                      const InstDev* inst, T* buf, const DropDev* drops, double* obs_part,
-                      int obs_stride);
+hipError_t launch_obs(hipStream_t s, int parity, int ntiles_launch, const TileDev* tiles, const InstDev* insts,
+                      const T* buf, const DropDev* drops, int inst, double* part, int stride);
+hipError_t launch_obs_final(hipStream_t s, const InstDev* insts, int inst, int ndrop, const DropDev* drops,
+                            const double* part, int stride, double* res);
 
 }  // namespace lbm

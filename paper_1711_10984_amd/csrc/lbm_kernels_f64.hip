@@ -20,6 +20,12 @@ hipError_t launch_tile_final(hipStream_t s, int ndrop_total, const InstDev* inst
   return hipGetLastError();
 }
 
+hipError_t launch_obs_final(hipStream_t s, const InstDev* insts, int inst, int ndrop, const DropDev* drops,
+                            const double* part, int stride, double* res) {
+  hipLaunchKernelGGL(k_obs_final, dim3(6 + ndrop), dim3(NTHREADS), 0, s, insts, inst, drops, part, stride, res);
+  return hipGetLastError();
+}
+
 LBM_INSTANTIATE_FIELDS(double)
 LBM_INSTANTIATE_POPS(double, double)
 LBM_INSTANTIATE_TILE(double, double)

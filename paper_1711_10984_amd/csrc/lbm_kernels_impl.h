@@ -269,6 +269,29 @@ __device__ __forceinline__ void lb_collide(const T (&d)[9], T dn, T nn, T ux, T 
   }
 }
 
+// A sum in twice the working precision: hi + lo, with the rounding errors of hi's additions in lo.  The sums of
+// the same numbers in another order give the same double, so results do not depend on the tiling.
+struct Dd {
+  double hi, lo;
+};
+__device__ __forceinline__ void dd_add(Dd& s, double v) {
+  const double t = s.hi + v, b = t - s.hi;
+  s.lo += (s.hi - (t - b)) + (v - b);
+  s.hi = t;
+}
+__device__ __forceinline__ void dd_add(Dd& s, const Dd& v) {
+  dd_add(s, v.hi);
+  s.lo += v.lo;
+}
+__device__ __forceinline__ double dd_value(const Dd& s) { return s.hi + s.lo; }
+__device__ __forceinline__ Dd dd_wave_sum(Dd s) {
+  for (int o = 32; o > 0; o >>= 1) {
+    const Dd v{__shfl_xor(s.hi, o, 64), __shfl_xor(s.lo, o, 64)};
+    dd_add(s, v);
+  }
+  return s;
+}
+
 // Sum (or min/max) over the workgroup in a fixed order; every thread receives lane 0's result.
 struct OpAdd {
   __device__ double operator()(double a, double b) const { return a + b; }
@@ -833,90 +856,218 @@ __global__ __launch_bounds__(NTHREADS) void k_fields(InstDev I, int parity, cons
   if (__ballot(!finite) != 0ull && (threadIdx.x & 63) == 0) *bad = 1u;
 }
 
-// Observables of the current state from the n, u planes written by k_lb<MODE 2>:
-// per-tile {mass, sum phi, sum c, min B, max |u|, nonfinite, per droplet (phi, phi ux, phi uy)}.
+// Observables of the current state of instance `inst`, per tile: {mass, sum phi, sum c, min B, max |u|, nonfinite,
+// per droplet (phi, phi ux, phi uy)} and one presence bit per droplet (droplets without a bit have no sums written).
+// n and u are formed here as k_lb forms them, from one read of the state, and only the droplets that a tile holds
+// are summed.  k_obs_final adds the tiles up.  Bound by latency (loads, stencil, one chain of reductions).  1024 x
+// 1024 FP32 with 16 droplets, the whole call: 54 us; with the velocity planes written and read back, three workgroup
+// sums per droplet and tile, and 0.9 MB of partials added up on the host 200 us.
 template <typename T, typename P>
 __global__ __launch_bounds__(NTHREADS) void k_obs(int parity, const TileDev* __restrict__ tiles,
                                                   const InstDev* __restrict__ insts, const T* __restrict__ buf,
-                                                  const DropDev* __restrict__ drops,
+                                                  const DropDev* __restrict__ drops, int inst,
                                                   double* __restrict__ out, int stride) {
+  constexpr int TX = TILE_X, TY = TILE_Y, NW = NTHREADS / 64;
+  constexpr int W2 = TX + 4, H2 = TY + 4, W1 = TX + 2, H1 = TY + 2;
+  __shared__ T s_phi[W2 * H2], s_c[W2 * H2], s_mu[W1 * H1], s_X[W1 * H1];
+  __shared__ int s_col[W2], s_row[H2];
+  __shared__ double s_red[NW][6];
   __shared__ DropShared sh;
   const TileDev td = tiles[blockIdx.x];
-  if (td.inst < 0) return;
+  if (td.inst != inst) return;
   const InstDev& I = insts[td.inst];
   const int nx = I.nx, ny = I.ny, pitch = I.pitch;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int64_t plane = I.pstride;
-  const int bx1 = min(td.x0 + TILE_X, nx) - 1, by1 = min(td.y0 + TILE_Y, ny) - 1;
-  if (I.ndrop > 0) {
-    cull_droplets(I, drops, td.x0, bx1, td.y0, by1, sh);
-  } else {
-    if (threadIdx.x == 0) sh.n_near = sh.n_src = 0;
-    __syncthreads();
-  }
   const T* __restrict__ phi = buf + I.off_phi[parity];
   const T* __restrict__ cc = buf + I.off_c[parity];
-  const P* __restrict__ fst = reinterpret_cast<const P*>(buf + I.off_f[parity]);
-  double m = 0.0, sp = 0.0, sc = 0.0, mb = 1e300, mu = 0.0, nf = 0.0;
+  const P* __restrict__ fin = reinterpret_cast<const P*>(buf + I.off_f[parity]);
+
+  for (int i = tid; i < W2; i += NTHREADS) s_col[i] = wrap_idx(td.x0 + i - 2, nx);
+  for (int i = tid; i < H2; i += NTHREADS) s_row[i] = row_of(td.y0 + i - 2, ny, I.walls);
+  if (tid < MASK_WORDS) sh.mask[tid] = 0ull;
+  __syncthreads();
+  for (int idx = tid; idx < W2 * H2; idx += NTHREADS) {
+    const int ly = idx / W2, lx = idx - ly * W2;
+    const int64_t g = (int64_t)s_row[ly] * pitch + s_col[lx];
+    s_phi[idx] = phi[g];
+    s_c[idx] = cc[g];
+  }
+  // the nodes' pulled populations (each stored population is pulled by one node: together they tell whether all are
+  // finite)
+  P q[NPT][9];
+#pragma unroll
+  for (int j = 0; j < NPT; ++j) {
+    const int idx = tid + j * NTHREADS, ly = idx / TX, lx = idx - ly * TX, x = td.x0 + lx, y = td.y0 + ly;
+    if (x >= nx || y >= ny) continue;
+    const int xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
+    const int ym = y == 0 ? ny - 1 : y - 1, yp = y == ny - 1 ? 0 : y + 1;
+    const int64_t r0 = (int64_t)y * pitch, rm = (int64_t)ym * pitch, rp = (int64_t)yp * pitch;
+    const bool bb0 = I.walls && y == 0, bbn = I.walls && y == ny - 1;  // bounced back from a plate
+    q[j][0] = fin[r0 + x];
+    q[j][1] = fin[plane + r0 + xm];
+    q[j][2] = fin[bb0 ? 4 * plane + r0 + x : 2 * plane + rm + x];
+    q[j][3] = fin[3 * plane + r0 + xp];
+    q[j][4] = fin[bbn ? 2 * plane + r0 + x : 4 * plane + rp + x];
+    q[j][5] = fin[bb0 ? 7 * plane + r0 + x : 5 * plane + rm + xm];
+    q[j][6] = fin[bb0 ? 8 * plane + r0 + x : 6 * plane + rm + xp];
+    q[j][7] = fin[bbn ? 5 * plane + r0 + x : 7 * plane + rp + xp];
+    q[j][8] = fin[bbn ? 6 * plane + r0 + x : 8 * plane + rp + xm];
+  }
+  if (I.ndrop > 0) {
+    const int bx1 = min(td.x0 + TX, nx) - 1, by1 = min(td.y0 + TY, ny) - 1;
+    cull_droplets(I, drops, td.x0, bx1, td.y0, by1, sh);  // contains barriers
+  } else {
+    __syncthreads();
+  }
+  const T a = T(I.a), b = T(I.b), B0 = T(I.B0), B1 = T(I.B1), halfB1 = T(I.halfB1);
+  for (int idx = tid; idx < W1 * H1; idx += NTHREADS) {
+    const int ly = idx / W1, lx = idx - ly * W1;
+    const int i2 = (ly + 1) * W2 + (lx + 1);
+    T gpx, gpy, gcx, gcy;
+    grad9(s_phi, i2, W2, gpx, gpy);
+    grad9(s_c, i2, W2, gcx, gcy);
+    const T lp = lap9(s_phi, i2, W2);
+    const T ph = s_phi[i2];
+    const T B = B0 + B1 * s_c[i2];
+    s_mu[idx] = ((a * ph + b * (ph * ph * ph)) - B * lp) - B1 * (gpx * gcx + gpy * gcy);
+    s_X[idx] = halfB1 * (gpx * gpx + gpy * gpy);
+  }
+  __syncthreads();
+  const T omega = T(I.omega), coef = T(I.coef);
+  const T w0 = cst<T>(4.0 / 9.0), w1 = cst<T>(1.0 / 9.0), w5 = cst<T>(1.0 / 36.0);
+  const LbConst<T> lbk{w0, w1, w5, coef * w0, coef * w1, coef * w5, omega, T(I.wn[0]), T(I.wn[1]), T(I.wn[2]), T(I.n0)};
+  double r[6] = {0.0, 0.0, 0.0, 1e300, 0.0, 0.0};  // mass, sum phi, sum c, min B, max |u|, nonfinite
   int kd[NPT];
   double vv[NPT], vx[NPT], vy[NPT];
+#pragma unroll
   for (int j = 0; j < NPT; ++j) {
     kd[j] = -1;
     vv[j] = vx[j] = vy[j] = 0.0;
-    const int idx = threadIdx.x + j * NTHREADS;
-    const int ly = idx / TILE_X, lx = idx - ly * TILE_X;
-    const int x = td.x0 + lx, y = td.y0 + ly;
+    const int idx = tid + j * NTHREADS, ly = idx / TX, lx = idx - ly * TX, x = td.x0 + lx, y = td.y0 + ly;
     if (x >= nx || y >= ny) continue;
-    const int64_t o = (int64_t)y * pitch + x;
-    const double p = (double)phi[o], c = (double)cc[o];
-    const double n = (double)buf[I.off_n + o];
-    const double u = (double)buf[I.off_ux + o], v = (double)buf[I.off_uy + o];
-    m += n;
-    sp += p;
-    sc += c;
-    mb = fmin(mb, I.B0 + I.B1 * c);
-    mu = fmax(mu, sqrt(u * u + v * v));
-    bool fin = isfinite(p) && isfinite(c);
-    for (int i = 0; i < 9; ++i) fin = fin && isfinite((double)fst[i * plane + o]);
-    if (!fin) nf = 1.0;
+    const int i1 = (ly + 1) * W1 + (lx + 1), i2 = (ly + 2) * W2 + (lx + 2);
+    T gmx, gmy, gXx, gXy, gcx, gcy;
+    grad9(s_mu, i1, W1, gmx, gmy);
+    grad9(s_X, i1, W1, gXx, gXy);
+    grad9(s_c, i2, W2, gcx, gcy);
+    const T ph = s_phi[i2], cv = s_c[i2];
+    const T Fx = (-(ph * gmx) - gcx) - cv * gXx;
+    const T Fy = (-(ph * gmy) - gcy) - cv * gXy;
+    T d[9], dn, nn, ux, uy;
+    lb_moments<T, P>(q[j], lbk, Fx, Fy, d, dn, nn, ux, uy);
+    const double p = (double)ph, c = (double)cv, n = (double)nn, u = (double)ux, v = (double)uy;
+    r[0] += n;
+    r[1] += p;
+    r[2] += c;
+    r[3] = fmin(r[3], I.B0 + I.B1 * c);
+    r[4] = fmax(r[4], sqrt(u * u + v * v));
+    bool fin_ok = isfinite(p) && isfinite(c);
+    for (int i = 0; i < 9; ++i) fin_ok = fin_ok && isfinite((double)q[j][i]);
+    if (!fin_ok) r[5] = 1.0;
     if (p >= 0.0 && I.ndrop > 0) {
-      const int k = nearest_drop(I, drops, sh, (double)x, (double)y);
-      kd[j] = k;
+      kd[j] = nearest_drop(I, drops, sh, (double)x, (double)y);
       vv[j] = p;
       vx[j] = p * u;
       vy[j] = p * v;
+      atomicOr(&sh.mask[kd[j] >> 6], 1ull << (kd[j] & 63));
     }
   }
-  double* o = out + (int64_t)td.t * stride;
-  const double r0 = block_reduce(m, sh.red, OpAdd());
-  const double r1 = block_reduce(sp, sh.red, OpAdd());
-  const double r2 = block_reduce(sc, sh.red, OpAdd());
-  const double r3 = block_reduce(mb, sh.red, OpMin());
-  const double r4 = block_reduce(mu, sh.red, OpMax());
-  const double r5 = block_reduce(nf, sh.red, OpMax());
-  if (threadIdx.x == 0) {
-    o[0] = r0;
-    o[1] = r1;
-    o[2] = r2;
-    o[3] = r3;
-    o[4] = r4;
-    o[5] = r5;
+  for (int i = 0; i < 6; ++i) {
+    for (int o = 32; o > 0; o >>= 1) {
+      const double w = __shfl_xor(r[i], o, 64);
+      r[i] = i < 3 ? r[i] + w : i == 3 ? fmin(r[i], w) : fmax(r[i], w);
+    }
+    if (lane == 0) s_red[wv][i] = r[i];
   }
-  for (int k = 0; k < I.ndrop; ++k) {
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-    for (int j = 0; j < NPT; ++j)
-      if (kd[j] == k) {
-        a0 += vv[j];
-        a1 += vx[j];
-        a2 += vy[j];
+  __syncthreads();
+  double* const to = out + (int64_t)td.t * stride;
+  if (tid < 6) {
+    double w = s_red[0][tid];
+    for (int k = 1; k < NW; ++k)
+      w = tid < 3 ? w + s_red[k][tid] : tid == 3 ? fmin(w, s_red[k][tid]) : fmax(w, s_red[k][tid]);
+    to[tid] = w;
+  }
+  if (tid < MASK_WORDS) reinterpret_cast<unsigned long long*>(to + stride - MASK_WORDS)[tid] = sh.mask[tid];
+  for (int w = 0; w < MASK_WORDS; ++w) {
+    unsigned long long m = sh.mask[w];
+    while (m) {
+      const int k = w * 64 + __ffsll(m) - 1;
+      m &= m - 1;
+      double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+      for (int j = 0; j < NPT; ++j)
+        if (kd[j] == k) {
+          a0 += vv[j];
+          a1 += vx[j];
+          a2 += vy[j];
+        }
+      __syncthreads();  // s_red's earlier values are read
+      block_reduce3(a0, a1, a2, reinterpret_cast<double(*)[3]>(s_red));
+      if (tid == 0) {
+        to[6 + 3 * k] = a0;
+        to[7 + 3 * k] = a1;
+        to[8 + 3 * k] = a2;
       }
-    const double s0 = block_reduce(a0, sh.red, OpAdd());
-    const double s1 = block_reduce(a1, sh.red, OpAdd());
-    const double s2 = block_reduce(a2, sh.red, OpAdd());
-    if (threadIdx.x == 0) {
-      o[6 + 3 * k] = s0;
-      o[7 + 3 * k] = s1;
-      o[8 + 3 * k] = s2;
     }
+  }
+}
+
+// The observables of one instance from its tiles' partials (k_obs), to page-locked host memory: block b < 6 writes
+// quantity b, block 6 + k writes {x, y, sum phi, sum phi ux, sum phi uy} of droplet k to res + 6 + 5 k.  Sums in twice
+// the working precision.
+__global__ __launch_bounds__(NTHREADS) void k_obs_final(const InstDev* __restrict__ insts, int inst,
+                                                        const DropDev* __restrict__ drops,
+                                                        const double* __restrict__ part, int stride,
+                                                        double* __restrict__ res) {
+  constexpr int NW = NTHREADS / 64;
+  __shared__ Dd s_sum[NW][3];
+  const InstDev& I = insts[inst];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, b = blockIdx.x;
+  const int nt = I.tiles_x[TILING_SPLIT] * I.tiles_y[TILING_SPLIT];
+  const double* const p = part + (int64_t)I.tile_base[TILING_SPLIT] * stride;
+  const bool extreme = b >= 3 && b < 6;  // min B, max |u|, nonfinite
+  const int k = b - 6, word = stride - MASK_WORDS + (k >> 6);
+  Dd s[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
+  double e = b == 3 ? INFINITY : 0.0;
+  for (int t = tid; t < nt; t += NTHREADS) {
+    const double* const o = p + (int64_t)t * stride;
+    if (extreme) {
+      e = b == 3 ? fmin(e, o[b]) : fmax(e, o[b]);
+    } else if (b < 3) {
+      dd_add(s[0], o[b]);
+    } else if ((reinterpret_cast<const unsigned long long*>(o)[word] >> (k & 63)) & 1ull) {
+      for (int i = 0; i < 3; ++i) dd_add(s[i], o[6 + 3 * k + i]);
+    }
+  }
+  if (extreme) {
+    for (int o = 32; o > 0; o >>= 1) {
+      const double w = __shfl_xor(e, o, 64);
+      e = b == 3 ? fmin(e, w) : fmax(e, w);
+    }
+    s[0] = Dd{e, 0.0};
+  } else {
+    for (int i = 0; i < 3; ++i) s[i] = dd_wave_sum(s[i]);
+  }
+  if (lane == 0)
+    for (int i = 0; i < 3; ++i) s_sum[wv][i] = s[i];
+  __syncthreads();
+  if (tid != 0) return;
+  for (int w = 1; w < NW; ++w) {
+    if (extreme)
+      s[0].hi = b == 3 ? fmin(s[0].hi, s_sum[w][0].hi) : fmax(s[0].hi, s_sum[w][0].hi);
+    else
+      for (int i = 0; i < 3; ++i) dd_add(s[i], s_sum[w][i]);
+  }
+  // where a sum overflows or meets a non-finite value, hi is what a plain sum gives and lo is undefined
+  double v[3];
+  for (int i = 0; i < 3; ++i) v[i] = isfinite(s[i].hi) ? dd_value(s[i]) : s[i].hi;
+  if (b < 6) {
+    res[b] = v[0];
+  } else {
+    double* const o = res + 6 + 5 * k;
+    o[0] = drops[I.drop_base + k].x;
+    o[1] = drops[I.drop_base + k].y;
+    for (int i = 0; i < 3; ++i) o[2 + i] = v[i];
   }
 }
 
@@ -2154,11 +2305,11 @@ hipError_t launch_fields(hipStream_t s, const InstDev& inst, int parity, const T
 }
 
 template <typename T, typename P>
-hipError_t launch_obs(hipStream_t s, int parity, int ntiles_launch, const TileDev* tiles,
-                      const InstDev* inst, T* buf, const DropDev* drops, double* obs_part, int obs_stride) {
+hipError_t launch_obs(hipStream_t s, int parity, int ntiles_launch, const TileDev* tiles, const InstDev* insts,
+                      const T* buf, const DropDev* drops, int inst, double* part, int stride) {
   if (ntiles_launch <= 0) return hipSuccess;
-  hipLaunchKernelGGL((k_obs<T, P>), dim3(ntiles_launch), dim3(NTHREADS), 0, s, parity, tiles, inst, buf, drops,
-                     obs_part, obs_stride);
+  hipLaunchKernelGGL((k_obs<T, P>), dim3(ntiles_launch), dim3(NTHREADS), 0, s, parity, tiles, insts, buf, drops, inst,
+                     part, stride);
   return hipGetLastError();
 }
 
@@ -2209,8 +2360,8 @@ hipError_t launch_wave(hipStream_t s, int parity, int nseg_launch, const TileDev
                                       double*, int);                                                      \
   template hipError_t launch_fields<T, P>(hipStream_t, const InstDev&, int, const T*, int64_t, int64_t, int, \
                                           double*, uint32_t*);                                            \
-  template hipError_t launch_obs<T, P>(hipStream_t, int, int, const TileDev*, const InstDev*, T*,         \
-                                       const DropDev*, double*, int);                                     \
+  template hipError_t launch_obs<T, P>(hipStream_t, int, int, const TileDev*, const InstDev*, const T*,   \
+                                       const DropDev*, int, double*, int);                                \
   template hipError_t launch_step<T, P>(hipStream_t, int, int, const TileDev*, const InstDev*, T*,        \
                                         const DropDev*, double*, uint64_t*, const int64_t*, double*, int); \
   template hipError_t launch_wave<T, P>(hipStream_t, int, int, const TileDev*, const InstDev*, T*,        \

@@ -23,29 +23,6 @@
 namespace lbm {
 namespace {
 
-// A sum in twice the working precision: hi + lo, with the rounding errors of hi's additions in lo.  The sums of
-// the same numbers in another order give the same double, so the centres do not depend on the tiling.
-struct Dd {
-  double hi, lo;
-};
-__device__ __forceinline__ void dd_add(Dd& s, double v) {
-  const double t = s.hi + v, b = t - s.hi;
-  s.lo += (s.hi - (t - b)) + (v - b);
-  s.hi = t;
-}
-__device__ __forceinline__ void dd_add(Dd& s, const Dd& v) {
-  dd_add(s, v.hi);
-  s.lo += v.lo;
-}
-__device__ __forceinline__ double dd_value(const Dd& s) { return s.hi + s.lo; }
-__device__ __forceinline__ Dd dd_wave_sum(Dd s) {
-  for (int o = 32; o > 0; o >>= 1) {
-    const Dd v{__shfl_xor(s.hi, o, 64), __shfl_xor(s.lo, o, 64)};
-    dd_add(s, v);
-  }
-  return s;
-}
-
 // The centre of mass of droplet k of an instance from its tiles' sums, by one wavefront, in three parts so that its
 // loads run beside other work: begin() loads the tiles' presence bits, load() lists the tiles that hold the droplet
 // and loads the sums of the first 64 of them, finish() adds up.  Tiles are taken TILE_CHUNK at a time; one chunk
