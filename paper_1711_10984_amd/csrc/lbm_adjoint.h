@@ -32,20 +32,33 @@ struct AdjModel {
   double yper;
 };
 
+// The droplets as of one step: parameters from the table, centre k at cen[k * stride].
+struct AdjDrops {
+  const DropDev* table;
+  const double* cen;
+  int stride, n;
+};
+
 // One backward step: the adjoint at n + 1 -> the adjoint at n.  Each block adds its partial sum of
 // sum_r cb1(r) * ramp * count_n(r) over its tile (the step's contribution to d/dA0) to part[tile]; part holds
 // adj_blocks(nx, ny) running totals, zeroed before the first step.
 template <typename T>
 hipError_t launch_adjoint_step(hipStream_t s, const AdjModel& m, const AdjFwd& f, const AdjPlanes<T>& p,
-                               const DropDev* drops_n, int ndrop, double* part);
+                               const AdjDrops& drops_n, double* part);
 
-// Seed of the loss x_CM^N of droplet `drop`: pass 0 writes per-block partial sums of phi over the droplet's
-// nodes (phi^N >= 0, nearest centre of step N - 1) into part; pass 1 writes pb = (dx - delta) / sw on those
-// nodes and 0 elsewhere, and clears fb, cb.
+// Seed of the loss x_CM^N of droplet `drop`, whose table at N is drops_end: the sum sw of phi over the droplet's nodes
+// (phi^N >= 0, nearest centre of step N - 1), then pb = (dx - delta) / sw on those nodes and 0 elsewhere (delta: the
+// centre's last move), fb and cb cleared, and part (adj_blocks values) zeroed.
 template <typename T>
-hipError_t launch_adjoint_seed(hipStream_t s, int pass, const AdjModel& m, const T* phi, int pitch,
-                               const DropDev* drops_prev, int ndrop, int drop, double delta, double sw, T* fb,
-                               T* pb, T* cb, double* part);
+hipError_t launch_adjoint_seed(hipStream_t s, const AdjModel& m, const T* phi, int pitch, const AdjDrops& prev,
+                               const DropDev* drops_end, int drop, T* fb, T* pb, T* cb, double* part, double* sw);
+
+// *out = the sum of part[0 .. n), in twice the working precision.
+hipError_t launch_adjoint_total(hipStream_t s, const double* part, int n, double* out);
+
+// out[i] = src[i] for i < n, as doubles, to page-locked host memory.
+template <typename T>
+hipError_t launch_widen(hipStream_t s, const T* src, int64_t n, double* out);
 
 // Blocks of the adjoint kernels: one per tile of ADJ_TILE_X x ADJ_TILE_Y nodes (at least one per 256 nodes,
 // which the seed kernel's one-dimensional blocks need).

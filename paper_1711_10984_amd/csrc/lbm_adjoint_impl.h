@@ -150,12 +150,13 @@ __device__ __forceinline__ T G9y_T(const K& k, V v) {
 }
 
 // Number of active production disks containing node (x, y) (the forward's source count at step n).
-__device__ int source_count_at(double x, double y, const DropDev* drops, int ndrop, const AdjModel& m) {
+__device__ int source_count_at(double x, double y, const AdjDrops& q, const AdjModel& m) {
   int cnt = 0;
-  for (int k = 0; k < ndrop; ++k) {
-    const DropDev d = drops[k];
+  for (int k = 0; k < q.n; ++k) {
+    const DropDev d = q.table[k];
     if (!d.active) continue;
-    const double px = d.x + (d.R - d.Rs) * d.ex, py = d.y + (d.R - d.Rs) * d.ey;
+    const double cx = q.cen[(int64_t)k * q.stride], cy = q.cen[(int64_t)k * q.stride + 1];
+    const double px = cx + (d.R - d.Rs) * d.ex, py = cy + (d.R - d.Rs) * d.ey;
     const double dx = minimg(x - px, (double)m.nx), dy = minimg(y - py, m.yper);
     if (dx * dx + dy * dy <= d.Rs * d.Rs) ++cnt;
   }
@@ -260,8 +261,8 @@ __device__ __forceinline__ void link_adj(CB cb1, XH Xh, KD kD, T& kb, T& Xb) {
 // c^{n+1/2}.  K2 reads K1's M_bar and X^{n+1/2}_bar and the gradients of phi^{n+1/2}, c^{n+1/2} across the 3 x 3
 // neighbourhood: they are formed on the tile with a one-node ring.
 template <typename T>
-__global__ __launch_bounds__(ADJ_THREADS) void k_adj12(AdjModel m, AdjFwd f, AdjPlanes<T> p, const DropDev* drops,
-                                                       int ndrop, double* part) {
+__global__ __launch_bounds__(ADJ_THREADS) void k_adj12(AdjModel m, AdjFwd f, AdjPlanes<T> p, AdjDrops drops,
+                                                       double* part) {
   __shared__ double red[ADJ_THREADS / 64];
   __shared__ T s_ph[ADJ_N2], s_ch[ADJ_N2], s_pb1[ADJ_N2], s_cb1[ADJ_N2], s_Xh[ADJ_N2];
   __shared__ T s_Mb[ADJ_HN], s_Xhb[ADJ_HN], s_gphx[ADJ_HN], s_gphy[ADJ_HN], s_gchx[ADJ_HN], s_gchy[ADJ_HN];
@@ -329,8 +330,8 @@ __global__ __launch_bounds__(ADJ_THREADS) void k_adj12(AdjModel m, AdjFwd f, Adj
     const T cb0 = cb1(0, 0);
     T chb = (T(1) - T(m.gamma)) * cb0 + D * L9<T>(cb1) + D * kb;
     // d c^{n+1}(r) / d A0 = min(n, t*) count_n(r)
-    if (m.ramp != 0.0 && ndrop > 0) {
-      const int cnt = source_count_at((double)k.x, (double)k.y, drops, ndrop, m);
+    if (m.ramp != 0.0 && drops.n > 0) {
+      const int cnt = source_count_at((double)k.x, (double)k.y, drops, m);
       src = (double)cb0 * m.ramp * (double)cnt;
     }
     // K2: M = a phi^{1/2} + b (phi^n)^3 - B(c^{1/2}) lap9(phi^{1/2}) - B1 grad9 c^{1/2} . grad9 phi^{1/2};
@@ -547,10 +548,11 @@ __global__ __launch_bounds__(ADJ_THREADS) void k_adj45(AdjModel m, AdjFwd f, Adj
   p.cb[idx] = cb;
 }
 
+// The seed in two passes around the sum of the first one's partials (k_adj_total): see launch_adjoint_seed.
 template <typename T>
-__global__ __launch_bounds__(ADJ_THREADS) void k_adj_seed(int pass, AdjModel m, const T* phi, int pitch,
-                                                          const DropDev* drops, int ndrop, int drop, double delta,
-                                                          double sw, T* fb, T* pb, T* cb, double* part) {
+__global__ __launch_bounds__(ADJ_THREADS) void k_adj_seed(int pass, AdjModel m, const T* phi, int pitch, AdjDrops prev,
+                                                          const DropDev* drops_end, int drop, T* fb, T* pb, T* cb,
+                                                          double* part, const double* sw) {
   __shared__ double red[ADJ_THREADS / 64];
   const int N = m.nx * m.ny;
   const int idx = blockIdx.x * ADJ_THREADS + threadIdx.x;
@@ -561,8 +563,9 @@ __global__ __launch_bounds__(ADJ_THREADS) void k_adj_seed(int pass, AdjModel m, 
     int best = -1;
     double bd = 0.0, bdx = 0.0;
     if (v >= 0.0) {
-      for (int q = 0; q < ndrop; ++q) {
-        const double dx = minimg((double)x - drops[q].x, (double)m.nx), dy = minimg((double)y - drops[q].y, m.yper);
+      for (int q = 0; q < prev.n; ++q) {
+        const double* const c = prev.cen + (int64_t)q * prev.stride;
+        const double dx = minimg((double)x - c[0], (double)m.nx), dy = minimg((double)y - c[1], m.yper);
         const double d2 = dx * dx + dy * dy;
         if (best < 0 || d2 < bd) {
           best = q;
@@ -576,7 +579,8 @@ __global__ __launch_bounds__(ADJ_THREADS) void k_adj_seed(int pass, AdjModel m, 
       s = in ? v : 0.0;
     } else {
       // x_CM^N = x_CM^{N-1} + sum phi dx / sum phi over the droplet's nodes: d/d phi = (dx - delta) / sw
-      pb[idx] = in ? T((bdx - delta) / sw) : T(0);
+      const double delta = minimg(drops_end[drop].x - prev.cen[(int64_t)drop * prev.stride], (double)m.nx);
+      pb[idx] = in ? T((bdx - delta) / *sw) : T(0);
       cb[idx] = T(0);
       for (int i = 0; i < 9; ++i) fb[(size_t)i * N + idx] = T(0);
     }
@@ -590,35 +594,65 @@ __global__ __launch_bounds__(ADJ_THREADS) void k_adj_seed(int pass, AdjModel m, 
       for (int w = 0; w < ADJ_THREADS / 64; ++w) t += red[w];
       part[blockIdx.x] = t;
     }
+  } else if (threadIdx.x == 0) {
+    part[blockIdx.x] = 0.0;
   }
+}
+
+__global__ __launch_bounds__(ADJ_THREADS) void k_adj_total(const double* __restrict__ part, int n,
+                                                           double* __restrict__ out) {
+  __shared__ Dd red[ADJ_THREADS / 64];
+  Dd s{0.0, 0.0};
+  for (int i = threadIdx.x; i < n; i += ADJ_THREADS) dd_add(s, part[i]);
+  s = dd_wave_sum(s);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int w = 1; w < ADJ_THREADS / 64; ++w) dd_add(s, red[w]);
+  *out = isfinite(s.hi) ? dd_value(s) : s.hi;
+}
+
+template <typename T>
+__global__ __launch_bounds__(ADJ_THREADS) void k_widen(const T* __restrict__ src, int64_t n, double* __restrict__ out) {
+  const int64_t i = (int64_t)blockIdx.x * ADJ_THREADS + threadIdx.x;
+  if (i < n) out[i] = (double)src[i];
 }
 
 }  // namespace
 
 template <typename T>
+hipError_t launch_widen(hipStream_t s, const T* src, int64_t n, double* out) {
+  hipLaunchKernelGGL((k_widen<T>), dim3((unsigned)((n + ADJ_THREADS - 1) / ADJ_THREADS)), dim3(ADJ_THREADS), 0, s, src, n,
+                     out);
+  return hipGetLastError();
+}
+
+template <typename T>
 hipError_t launch_adjoint_step(hipStream_t s, const AdjModel& m, const AdjFwd& f, const AdjPlanes<T>& p,
-                               const DropDev* drops_n, int ndrop, double* part) {
+                               const AdjDrops& drops_n, double* part) {
   const int nb = adj_blocks(m.nx, m.ny);
-  hipLaunchKernelGGL((k_adj12<T>), dim3(nb), dim3(ADJ_THREADS), 0, s, m, f, p, drops_n, ndrop, part);
+  hipLaunchKernelGGL((k_adj12<T>), dim3(nb), dim3(ADJ_THREADS), 0, s, m, f, p, drops_n, part);
   hipLaunchKernelGGL((k_adj3<T>), dim3(nb), dim3(ADJ_THREADS), 0, s, m, f, p);
   hipLaunchKernelGGL((k_adj45<T>), dim3(nb), dim3(ADJ_THREADS), 0, s, m, f, p);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_adjoint_seed(hipStream_t s, int pass, const AdjModel& m, const T* phi, int pitch,
-                               const DropDev* drops_prev, int ndrop, int drop, double delta, double sw, T* fb,
-                               T* pb, T* cb, double* part) {
+hipError_t launch_adjoint_seed(hipStream_t s, const AdjModel& m, const T* phi, int pitch, const AdjDrops& prev,
+                               const DropDev* drops_end, int drop, T* fb, T* pb, T* cb, double* part, double* sw) {
   const int nb = adj_blocks(m.nx, m.ny);
-  hipLaunchKernelGGL((k_adj_seed<T>), dim3(nb), dim3(ADJ_THREADS), 0, s, pass, m, phi, pitch, drops_prev, ndrop, drop,
-                     delta, sw, fb, pb, cb, part);
+  const dim3 g(nb), b(ADJ_THREADS);
+  hipLaunchKernelGGL((k_adj_seed<T>), g, b, 0, s, 0, m, phi, pitch, prev, drops_end, drop, fb, pb, cb, part, sw);
+  hipLaunchKernelGGL(k_adj_total, dim3(1), b, 0, s, part, nb, sw);
+  hipLaunchKernelGGL((k_adj_seed<T>), g, b, 0, s, 1, m, phi, pitch, prev, drops_end, drop, fb, pb, cb, part, sw);
   return hipGetLastError();
 }
 
-#define LBM_INSTANTIATE_ADJOINT(T)                                                                           \
-  template hipError_t launch_adjoint_step<T>(hipStream_t, const AdjModel&, const AdjFwd&, const AdjPlanes<T>&, \
-                                             const DropDev*, int, double*);                                 \
-  template hipError_t launch_adjoint_seed<T>(hipStream_t, int, const AdjModel&, const T*, int, const DropDev*, \
-                                             int, int, double, double, T*, T*, T*, double*);
+#define LBM_INSTANTIATE_ADJOINT(T)                                                                                  \
+  template hipError_t launch_adjoint_step<T>(hipStream_t, const AdjModel&, const AdjFwd&, const AdjPlanes<T>&,      \
+                                             const AdjDrops&, double*);                                             \
+  template hipError_t launch_adjoint_seed<T>(hipStream_t, const AdjModel&, const T*, int, const AdjDrops&,          \
+                                             const DropDev*, int, T*, T*, T*, double*, double*);                    \
+  template hipError_t launch_widen<T>(hipStream_t, const T*, int64_t, double*);
 
 }  // namespace lbm

@@ -402,22 +402,27 @@ bool all_plain(const std::vector<InstDev>& inst) {
   return true;
 }
 
-// The single kernel of a step on the fused or wave path: over the strip list, or the tiled one (as step number
-// `ahead` of its sequence).
+// The single kernel of a step on the fused or wave path: over the strip list, or the tiled one with the buffers q of its
+// sequence.  insts (the device's) and one (a lattice alone) describe the lattices, drops is their droplet table.
+template <typename T, typename P>
+hipError_t launch_sweep_on(lbm_ctx* c, int parity, const InstDev* insts, const InstDev* one, const DropDev* drops,
+                           const TileSeq& q, double* dbg, int dbg_inst) {
+  T* buf = reinterpret_cast<T*>(c->pool());
+  if (c->tiled())
+    return launch_tile<T, P>(c->stream, parity, c->L.tshape, one ? c->L.nttiles : (int)c->L.ttiles.size(), one,
+                             c->d_ttiles(), insts, buf, drops, q, c->d_step(), dbg, dbg_inst);
+  if (c->path == LBM_PATH_WAVE)
+    return launch_wave<T, P>(c->stream, parity, c->nseglaunch(), c->d_segs(), insts, buf, drops, c->d_part(),
+                             c->d_mask(), c->d_step(), dbg, dbg_inst, all_plain(c->L.inst));
+  return launch_step<T, P>(c->stream, parity, c->nseglaunch(), c->d_segs(), insts, buf, drops, c->d_part(), c->d_mask(),
+                           c->d_step(), dbg, dbg_inst);
+}
+
+// The same on the context's own state, as step number `ahead` of its sequence.
 template <typename T, typename P>
 hipError_t launch_sweep(lbm_ctx* c, int parity, double* dbg, int dbg_inst, int64_t ahead = 0) {
-  T* buf = reinterpret_cast<T*>(c->pool());
-  if (c->tiled()) {
-    const bool alone = c->L.inst.size() == 1;
-    return launch_tile<T, P>(c->stream, parity, c->L.tshape, alone ? c->L.nttiles : (int)c->L.ttiles.size(),
-                             alone ? c->L.inst.data() : nullptr, c->d_ttiles(), c->d_inst(), buf, c->d_drops(),
-                             c->tile_seq(ahead), c->d_step(), dbg, dbg_inst);
-  }
-  if (c->path == LBM_PATH_WAVE)
-    return launch_wave<T, P>(c->stream, parity, c->nseglaunch(), c->d_segs(), c->d_inst(), buf, c->d_drops(),
-                             c->d_part(), c->d_mask(), c->d_step(), dbg, dbg_inst, all_plain(c->L.inst));
-  return launch_step<T, P>(c->stream, parity, c->nseglaunch(), c->d_segs(), c->d_inst(), buf, c->d_drops(),
-                           c->d_part(), c->d_mask(), c->d_step(), dbg, dbg_inst);
+  return launch_sweep_on<T, P>(c, parity, c->d_inst(), c->L.inst.size() == 1 ? c->L.inst.data() : nullptr, c->d_drops(),
+                               c->tile_seq(ahead), dbg, dbg_inst);
 }
 
 // The two tile kernels of the split path.
@@ -437,7 +442,7 @@ hipError_t enqueue_reduce(lbm_ctx* c, int64_t n, bool write = true) {
     return launch_tile_final(c->stream, c->L.ndrop_total, c->d_inst(), c->d_drops(), c->tile_seq(n), c->d_step(),
                              write ? n : 0);
   return launch_reduce(c->stream, c->path == LBM_PATH_SPLIT ? TILING_SPLIT : TILING_FUSED, c->L.ndrop_total, c->d_inst(),
-                       c->d_drops(), c->d_part(), c->d_mask(), c->d_step(), write ? 1 : -1);
+                       c->d_drops(), c->d_drops(), c->d_part(), c->d_mask(), c->d_step(), write ? 1 : -1);
 }
 
 // n steps from the given parity.
@@ -567,41 +572,34 @@ int need_pinned(lbm_ctx* c, size_t bytes) {
   return LBM_OK;
 }
 
-// The requested fields of an instance (null: not requested) as the caller's arrays hold them; `finite` tells whether
-// all their values are.
-template <typename T, typename P>
-int fields_impl(lbm_ctx* c, int inst, double* f_pre, double* phi, double* cc, double* n, double* ux, double* uy,
-                bool& finite) {
-  const InstDev& d = c->L.inst[inst];
-  const int64_t nodes = (int64_t)d.nx * d.ny;
-  double* dst[14];
-  int np = 0, rc;
-  finite = true;
-  for (int k = 0; f_pre && k < 9; ++k) dst[np++] = f_pre + k * nodes;
-  for (double* o : {phi, cc, n, ux, uy})
-    if (o) dst[np++] = o;
-  const int want = (f_pre ? FIELD_F : 0) | (phi ? FIELD_PHI : 0) | (cc ? FIELD_C : 0) | (n ? FIELD_N : 0) |
-                   (ux ? FIELD_UX : 0) | (uy ? FIELD_UY : 0);
-  if (np == 0) {
-    HIPCHK(hipStreamSynchronize(c->stream));
-    return LBM_OK;
-  }
+// Nodes of a chunk of a read-back of np planes, and the page-locked bytes that the read-back needs.
+int64_t read_chunk(int64_t nodes, int np) {
   const size_t node_bytes = sizeof(double) * np;
-  const int64_t per = (size_t)nodes * node_bytes <= READ_CHUNK ? nodes : (int64_t)(READ_CHUNK / node_bytes);
-  const int64_t chunks = (nodes + per - 1) / per;
-  const size_t half = align_up(READ_HEAD + (size_t)per * node_bytes, ALIGN);
-  if ((rc = need_pinned(c, chunks > 1 ? 2 * half : half)) != LBM_OK) return rc;
+  return (size_t)nodes * node_bytes <= READ_CHUNK ? nodes : (int64_t)(READ_CHUNK / node_bytes);
+}
+size_t read_half(int64_t nodes, int np) {
+  return align_up(READ_HEAD + (size_t)read_chunk(nodes, np) * sizeof(double) * np, ALIGN);
+}
+size_t read_bytes(int64_t nodes, int np) { return (read_chunk(nodes, np) < nodes ? 2 : 1) * read_half(nodes, np); }
+
+// np planes of `nodes` doubles to the caller's arrays dst, by launch(first, count, values, flag): it fills the planes'
+// nodes [first, first + count), one plane after another, and sets the flag where a value is not finite.
+template <class F>
+int read_planes(lbm_ctx* c, int64_t nodes, int np, double* const* dst, bool& finite, F launch) {
+  const int64_t per = read_chunk(nodes, np), chunks = (nodes + per - 1) / per;
+  const size_t half = read_half(nodes, np);
+  const int rc = need_pinned(c, read_bytes(nodes, np));
+  if (rc != LBM_OK) return rc;
   for (int k = 0; chunks > 1 && k < 2; ++k)
     if (!c->read_ev[k]) HIPCHK(hipEventCreateWithFlags(&c->read_ev[k], hipEventDisableTiming));
-  if ((n || ux || uy) && (rc = run_diag(c, inst)) != LBM_OK) return rc;
+  finite = true;
   for (int64_t k = 0; k <= chunks; ++k) {
     if (k < chunks) {
       char* const h = c->pinned + (k & 1) * half;
       const int64_t first = k * per;
       *reinterpret_cast<uint32_t*>(h) = 0u;
-      HIPCHK((launch_fields<T, P>(c->stream, d, c->parity, reinterpret_cast<const T*>(c->pool()), first,
-                                  std::min(per, nodes - first), want, reinterpret_cast<double*>(h + READ_HEAD),
-                                  reinterpret_cast<uint32_t*>(h))));
+      HIPCHK(launch(first, std::min(per, nodes - first), reinterpret_cast<double*>(h + READ_HEAD),
+                    reinterpret_cast<uint32_t*>(h)));
       if (chunks > 1) HIPCHK(hipEventRecord(c->read_ev[k & 1], c->stream));
     }
     if (k == 0) continue;
@@ -618,17 +616,46 @@ int fields_impl(lbm_ctx* c, int inst, double* f_pre, double* phi, double* cc, do
   return LBM_OK;
 }
 
-// Stage planes of the next step of instance `inst` from the kernels of the current path: all LBM_NSTAGE, or only
-// the first ADJ_EXPORT_PLANES (all = false).
+// The requested fields of an instance (null: not requested) as the caller's arrays hold them; `finite` tells whether
+// all their values are.
 template <typename T, typename P>
-hipError_t debug_launch(lbm_ctx* c, int inst, double* dbg, bool all = true) {
+int fields_impl(lbm_ctx* c, int inst, double* f_pre, double* phi, double* cc, double* n, double* ux, double* uy,
+                bool& finite) {
+  const InstDev& d = c->L.inst[inst];
+  const int64_t nodes = (int64_t)d.nx * d.ny;
+  double* dst[14];
+  int np = 0, rc;
+  for (int k = 0; f_pre && k < 9; ++k) dst[np++] = f_pre + k * nodes;
+  for (double* o : {phi, cc, n, ux, uy})
+    if (o) dst[np++] = o;
+  if (np == 0) {
+    HIPCHK(hipStreamSynchronize(c->stream));
+    return LBM_OK;
+  }
+  const int want = (f_pre ? FIELD_F : 0) | (phi ? FIELD_PHI : 0) | (cc ? FIELD_C : 0) | (n ? FIELD_N : 0) |
+                   (ux ? FIELD_UX : 0) | (uy ? FIELD_UY : 0);
+  if ((n || ux || uy) && (rc = run_diag(c, inst)) != LBM_OK) return rc;
+  return read_planes(c, nodes, np, dst, finite, [&](int64_t first, int64_t count, double* v, uint32_t* bad) {
+    return launch_fields<T, P>(c->stream, d, c->parity, reinterpret_cast<const T*>(c->pool()), first, count, want, v,
+                               bad);
+  });
+}
+
+// Stage planes of the next step of instance `inst` from the kernels of the current path.
+template <typename T, typename P>
+hipError_t launch_split_export(lbm_ctx* c, int parity, const InstDev* insts, const DropDev* drops, double* dbg,
+                               int dbg_inst) {
   T* buf = reinterpret_cast<T*>(c->pool());
-  const int di = export_planes(inst, all);
-  if (c->path != LBM_PATH_SPLIT) return launch_sweep<T, P>(c, c->parity, dbg, di);
-  hipError_t e = launch_lb<T, P>(c->stream, 1, c->parity, c->nlaunch(), c->d_tiles(), c->d_inst(), buf, dbg, di);
+  hipError_t e = launch_lb<T, P>(c->stream, 1, parity, c->nlaunch(), c->d_tiles(), insts, buf, dbg, dbg_inst);
   if (e != hipSuccess) return e;
-  return launch_fd<T>(c->stream, 1, c->parity, c->nlaunch(), c->d_tiles(), c->d_inst(), buf, c->d_drops(), c->d_part(),
-                      c->d_mask(), c->d_step(), dbg, di);
+  return launch_fd<T>(c->stream, 1, parity, c->nlaunch(), c->d_tiles(), insts, buf, drops, c->d_part(), c->d_mask(),
+                      c->d_step(), dbg, dbg_inst);
+}
+template <typename T, typename P>
+hipError_t debug_launch(lbm_ctx* c, int inst, double* dbg) {
+  const int di = export_planes(inst, true);
+  if (c->path != LBM_PATH_SPLIT) return launch_sweep<T, P>(c, c->parity, dbg, di);
+  return launch_split_export<T, P>(c, c->parity, c->d_inst(), c->d_drops(), dbg, di);
 }
 
 // One eager step with hipEvents between its kernels: ev[0..nk] bracket nk launches.
@@ -945,7 +972,7 @@ int lbm_step_noalloc(const lbm_config* cfg, void* stream, void* const f[2], void
                                          part, mask, dstep, nullptr, -1,
                                          cf.walls == LBM_WALLS_NONE && cf.advection == LBM_ADV_PAPER);
     });
-    if (e == hipSuccess) e = launch_reduce(st, TILING_FUSED, ndrop, di, dd, part, mask, dstep, 1);
+    if (e == hipSuccess) e = launch_reduce(st, TILING_FUSED, ndrop, di, dd, dd, part, mask, dstep, 1);
     if (e != hipSuccess) return fail(LBM_E_HIP, std::string("timestep launch: ") + hipGetErrorString(e));
   }
   if (ndrop > 0) {
@@ -1048,8 +1075,8 @@ int lbm_init_batch(int32_t ninst, const lbm_config* cfgs, void* workspace, size_
     return launch_cm_partials<T>(c->stream, 0, c->nlaunch(), c->d_tiles(), c->d_inst(), reinterpret_cast<T*>(c->pool()),
                                  c->d_drops(), c->d_part(), c->d_mask());
   }));
-  INIT_CHK(launch_reduce(c->stream, TILING_SPLIT, c->L.ndrop_total, c->d_inst(), c->d_drops(), c->d_part(),
-                         c->d_mask(), c->d_step(), 0));
+  INIT_CHK(launch_reduce(c->stream, TILING_SPLIT, c->L.ndrop_total, c->d_inst(), c->d_drops(), c->d_drops(),
+                         c->d_part(), c->d_mask(), c->d_step(), 0));
   INIT_CHK(hipStreamSynchronize(c->stream));
 #undef INIT_CHK
   *out = c;
@@ -1477,10 +1504,10 @@ namespace {
 struct AdjLayout {
   size_t pop = 0, field = 0, dropb = 0;  // bytes of the parts of a saved state
   size_t slot = 0;   // a whole state: populations, phi, c, droplet table, step counter
-  size_t sslot = 0;  // what the adjoint step reads of a recomputed state: phi, c, droplet table
+  size_t sslot = 0;  // what the adjoint step reads of a recomputed state: phi, c, droplet table, tiled steps' centres
   int64_t ncp = 0, nodes = 0;
   int every = 0, nb = 0;
-  size_t off_cp = 0, off_seg = 0, off_final = 0, off_fwd = 0, off_adj = 0, off_part = 0, total = 0;
+  size_t off_cp = 0, off_seg = 0, off_final = 0, off_fwd = 0, off_adj = 0, off_part = 0, off_inst = 0, total = 0;
 };
 
 constexpr int ADJ_TMP_PLANES = 4;  // intermediate adjoints of one backward step
@@ -1544,15 +1571,16 @@ AdjLayout adj_layout(const lbm_ctx* c, int64_t nsteps, int every) {
   A.field = (size_t)d.pstride * c->L.elem;
   A.dropb = sizeof(DropDev) * (size_t)std::max(1, (int)d.ndrop);
   A.slot = align_up(A.pop + 2 * A.field + A.dropb + sizeof(int64_t), ALIGN);
-  A.sslot = align_up(2 * A.field + A.dropb, ALIGN);
+  A.sslot = align_up(2 * A.field + A.dropb + sizeof(double) * 2 * (size_t)d.ndrop, ALIGN);
   size_t off = 0;
   A.off_cp = off;    off += A.slot * (size_t)A.ncp;
-  A.off_seg = off;   off += A.sslot * (size_t)every;
+  A.off_seg = off;   off += A.sslot * ((size_t)every + 1);
   A.off_final = off; off += A.slot;
   A.off_fwd = off;
   off = align_up(off + sizeof(double) * ADJ_FWD_PLANES * (size_t)every * (size_t)A.nodes, ALIGN);
   A.off_adj = off;   off = align_up(off + c->L.elem * (size_t)(22 + ADJ_TMP_PLANES) * A.nodes, ALIGN);
-  A.off_part = off;  off = align_up(off + sizeof(double) * (size_t)A.nb * 2, ALIGN);  // seed sums, dA0 totals
+  A.off_part = off;  off = align_up(off + sizeof(double) * ((size_t)A.nb + 1), ALIGN);
+  A.off_inst = off;  off = align_up(off + sizeof(InstDev) * (size_t)every, ALIGN);
   A.total = off;
   return A;
 }
@@ -1573,36 +1601,40 @@ int adj_save(lbm_ctx* c, const AdjLayout& A, char* slot) {
   return LBM_OK;
 }
 
-int adj_load(lbm_ctx* c, const AdjLayout& A, const char* slot, int64_t step) {
+// A whole slot back into the current buffers, or (sslot not null) its phi and c into a segment slot and only the
+// populations into the current buffers.  The droplet table goes to the context, and to the segment slot.
+int adj_load(lbm_ctx* c, const AdjLayout& A, const char* slot, int64_t step, char* sslot) {
   const InstDev& d = c->L.inst[0];
   char* pool = static_cast<char*>(c->pool());
   const size_t e = c->L.elem;
   CopyBuilder b;
   b.add(slot, pool + d.off_f[c->parity] * e, A.pop);
-  b.add(slot + A.pop, pool + d.off_phi[c->parity] * e, A.field);
-  b.add(slot + A.pop + A.field, pool + d.off_c[c->parity] * e, A.field);
-  b.add(slot + A.pop + 2 * A.field, c->d_drops(), sizeof(DropDev) * d.ndrop);
+  b.add(slot + A.pop, sslot ? sslot : pool + d.off_phi[c->parity] * e, A.field);
+  b.add(slot + A.pop + A.field, sslot ? sslot + A.field : pool + d.off_c[c->parity] * e, A.field);
+  b.add(slot + A.pop + 2 * A.field, sslot ? sslot + 2 * A.field : reinterpret_cast<char*>(c->d_drops()),
+        sizeof(DropDev) * d.ndrop);
   b.add(slot + A.pop + 2 * A.field + A.dropb, c->d_step(), sizeof(int64_t));
   HIPCHK(b.launch(c->stream));
   c->step = step;
   return LBM_OK;
 }
 
-// phi, c and the droplet table of the current state into a segment slot (what the adjoint step reads).
-int adj_save_seg(lbm_ctx* c, const AdjLayout& A, char* sslot) {
-  const InstDev& d = c->L.inst[0];
-  char* pool = static_cast<char*>(c->pool());
-  const size_t e = c->L.elem;
-  CopyBuilder b;
-  b.add(pool + d.off_phi[c->parity] * e, sslot, A.field);
-  b.add(pool + d.off_c[c->parity] * e, sslot + A.field, A.field);
-  b.add(c->d_drops(), sslot + 2 * A.field, sizeof(DropDev) * d.ndrop);
-  HIPCHK(b.launch(c->stream));
-  return LBM_OK;
+DropDev* adj_seg_drops(const AdjLayout& A, char* sslot) { return reinterpret_cast<DropDev*>(sslot + 2 * A.field); }
+double* adj_seg_centres(const AdjLayout& A, char* sslot) {
+  return reinterpret_cast<double*>(sslot + 2 * A.field + A.dropb);
 }
 
-const DropDev* adj_seg_drops(const AdjLayout& A, const char* sslot) {
-  return reinterpret_cast<const DropDev*>(sslot + 2 * A.field);
+// Description of the lattice for recomputed step j of an interval (of parity j & 1): phi and c are read from segment
+// slot j and written to slot j + 1, so that the record of an interval needs no copies.  The populations alternate
+// between the context's own buffers.
+InstDev adj_inst(const InstDev& d, int64_t seg, int64_t sslot, int64_t field, int64_t j) {
+  InstDev v = d;
+  const int in = (int)(j & 1);
+  v.off_phi[in] = seg + j * sslot;
+  v.off_phi[in ^ 1] = seg + (j + 1) * sslot;
+  v.off_c[in] = seg + j * sslot + field;
+  v.off_c[in ^ 1] = seg + (j + 1) * sslot + field;
+  return v;
 }
 
 template <typename T>
@@ -1612,7 +1644,21 @@ int adj_backward(lbm_ctx* c, const AdjLayout& A, char* w, double* dA0, double* d
   const int64_t n0 = c->adj.n0, N = c->adj.nsteps, M = A.nodes;
   const int every = c->adj.every, drop = c->adj.drop, nd = d.ndrop;
   int rc;
+  if ((rc = need_pinned(c, read_bytes(A.nodes, 1))) != LBM_OK) return rc;  // what the gradient's read-back needs
   if ((rc = adj_save(c, A, w + A.off_final)) != LBM_OK) return rc;
+  const int parity = c->parity;  // of the final state, which comes back at the end
+  char* const segs = w + A.off_seg;
+  // the descriptions of an interval's steps, in elements from the pool
+  const int64_t e = (int64_t)c->L.elem;
+  const int64_t seg0 = (segs - static_cast<char*>(c->pool())) / e, sslot = (int64_t)A.sslot / e;
+  const int64_t field = (int64_t)A.field / e;
+  InstDev* const d_insts = reinterpret_cast<InstDev*>(w + A.off_inst);
+  if (!c->tiled()) {
+    std::vector<InstDev> h((size_t)every);
+    for (int j = 0; j < every; ++j) h[j] = adj_inst(d, seg0, sslot, field, j);
+    HIPCHK(hipMemcpyAsync(d_insts, h.data(), sizeof(InstDev) * h.size(), hipMemcpyHostToDevice, c->stream));
+    HIPCHK(hipStreamSynchronize(c->stream));
+  }
   // stage planes of step k0 + j of the current interval start ADJ_FWD_PLANES * j planes into the record
   double* fwd = reinterpret_cast<double*>(w + A.off_fwd);
   auto fwd_rec = [&](int64_t j) { return fwd + (size_t)ADJ_FWD_PLANES * (size_t)j * (size_t)M; };
@@ -1624,9 +1670,9 @@ int adj_backward(lbm_ctx* c, const AdjLayout& A, char* w, double* dA0, double* d
   T* adj = reinterpret_cast<T*>(w + A.off_adj);
   T* lam[2] = {adj, adj + 11 * M};  // adjoint state (f 9 planes, phi, c) at n and at n + 1
   T* tmp = adj + 22 * M;
-  double* part = reinterpret_cast<double*>(w + A.off_part);  // seed partial sums (nb)
-  double* dA0_part = part + A.nb;                             // per-block dA0 totals over all steps (nb)
-  HIPCHK(hipMemsetAsync(dA0_part, 0, sizeof(double) * A.nb, c->stream));
+  double* part = reinterpret_cast<double*>(w + A.off_part);  // the seed's partial sums, then per-block dA0 totals
+  double* const sw = part + A.nb;                            // the seed's sum of phi
+  double* const result = reinterpret_cast<double*>(c->pinned);  // that sum, dA0
   AdjModel m;
   m.nx = d.nx;
   m.ny = d.ny;
@@ -1658,76 +1704,69 @@ int adj_backward(lbm_ctx* c, const AdjLayout& A, char* w, double* dA0, double* d
     for (int i = 0; i < ADJ_TMP_PLANES; ++i) *t[i] = tmp + (size_t)i * M;
     return p;
   };
+  auto slot_of = [&](int64_t j) { return segs + (size_t)j * A.sslot; };
+  // the droplets at step j of the interval: tiled steps leave the centres alone, the others a table
+  static_assert(sizeof(DropDev) % sizeof(double) == 0, "centres of a table as an array of doubles");
+  auto drops_at = [&](int64_t j) {
+    if (c->tiled()) return AdjDrops{adj_seg_drops(A, segs), adj_seg_centres(A, slot_of(j)), 2, nd};
+    DropDev* const t = adj_seg_drops(A, slot_of(j));
+    return AdjDrops{t, &t->x, (int)(sizeof(DropDev) / sizeof(double)), nd};
+  };
+  const int dbg_inst = export_planes(0, false);
   int cur = 1;  // lam[cur] holds the adjoint of the latest state
-  bool seeded = false;
   for (int64_t s = A.ncp - 1; s >= 0; --s) {
     const int64_t k0 = s * every, k1 = std::min<int64_t>(N, k0 + every);
-    // recompute the interval from its checkpoint, keeping phi, c, the droplet table and the stage planes
-    // of every step
-    if ((rc = adj_load(c, A, w + A.off_cp + (size_t)s * A.slot, n0 + k0)) != LBM_OK) return rc;
-    for (int64_t k = k0; k < k1; ++k) {
-      if ((rc = adj_save_seg(c, A, w + A.off_seg + (size_t)(k - k0) * A.sslot)) != LBM_OK) return rc;
-      HIPCHK((debug_launch<T, T>(c, 0, fwd_rec(k - k0), false)));
-      // the stage-export launch has also written the next state and the centre-of-mass partials, so only
-      // the reduction is left of the step
-      const hipError_t e = enqueue_reduce(c, 1);
-      if (e != hipSuccess) return fail(LBM_E_HIP, std::string("adjoint recompute: ") + hipGetErrorString(e));
-      c->parity ^= 1;
-      c->step += 1;
+    // recompute the interval from its checkpoint: phi, c, the droplets and the stage planes of every step stay in the
+    // interval's record.  The export launch is a whole step but for the centres.
+    c->parity = 0;
+    if ((rc = adj_load(c, A, w + A.off_cp + (size_t)s * A.slot, n0 + k0, segs)) != LBM_OK) return rc;
+    for (int64_t j = 0; j < k1 - k0; ++j) {
+      DropDev* const table = adj_seg_drops(A, slot_of(j));
+      const int par = (int)(j & 1);
+      if (c->tiled()) {
+        TileSeq q = c->tile_seq(j);
+        if (j > 0) q.cen_in = adj_seg_centres(A, slot_of(j - 1));
+        q.cen_out = adj_seg_centres(A, slot_of(j));
+        const InstDev one = adj_inst(d, seg0, sslot, field, j);
+        HIPCHK((launch_sweep_on<T, T>(c, par, nullptr, &one, adj_seg_drops(A, segs), q, fwd_rec(j), dbg_inst)));
+        continue;
+      }
+      if (c->path == LBM_PATH_SPLIT)
+        HIPCHK((launch_split_export<T, T>(c, par, d_insts + j, table, fwd_rec(j), dbg_inst)));
+      else
+        HIPCHK((launch_sweep_on<T, T>(c, par, d_insts + j, nullptr, table, TileSeq{}, fwd_rec(j), dbg_inst)));
+      HIPCHK(launch_reduce(c->stream, c->path == LBM_PATH_SPLIT ? TILING_SPLIT : TILING_FUSED, nd, d_insts + j, table,
+                           adj_seg_drops(A, slot_of(j + 1)), c->d_part(), c->d_mask(), c->d_step(), 1));
     }
-    if (!seeded) {
-      // loss x_CM^N - x_CM^{n0}: seed d/d phi^N over the droplet's nodes (centres of step N - 1)
-      const char* last = w + A.off_seg + (size_t)(k1 - 1 - k0) * A.sslot;
-      std::vector<DropDev> prev(nd), now(nd);
-      HIPCHK(hipMemcpyAsync(prev.data(), adj_seg_drops(A, last), sizeof(DropDev) * nd, hipMemcpyDeviceToHost,
-                            c->stream));
-      HIPCHK(hipMemcpyAsync(now.data(), c->d_drops(), sizeof(DropDev) * nd, hipMemcpyDeviceToHost, c->stream));
-      HIPCHK(hipStreamSynchronize(c->stream));
-      double dx = now[drop].x - prev[drop].x;
-      if (dx >= 0.5 * d.nx) dx -= d.nx;
-      if (dx < -0.5 * d.nx) dx += d.nx;
-      const T* phiN = reinterpret_cast<const T*>(c->pool()) + d.off_phi[c->parity];
-      HIPCHK(launch_adjoint_seed<T>(c->stream, 0, m, phiN, d.pitch, adj_seg_drops(A, last), nd, drop, 0.0, 1.0,
-                                    lam[cur], lam[cur] + 9 * M, lam[cur] + 10 * M, part));
-      std::vector<double> hp(A.nb);
-      HIPCHK(hipMemcpyAsync(hp.data(), part, sizeof(double) * A.nb, hipMemcpyDeviceToHost, c->stream));
-      HIPCHK(hipStreamSynchronize(c->stream));
-      double sw = 0.0;
-      for (double v : hp) sw += v;
-      if (!(sw > 0.0)) return fail(LBM_E_STATE, "the droplet has no nodes with phi >= 0 at the end of the run");
-      HIPCHK(launch_adjoint_seed<T>(c->stream, 1, m, phiN, d.pitch, adj_seg_drops(A, last), nd, drop, dx, sw,
-                                    lam[cur], lam[cur] + 9 * M, lam[cur] + 10 * M, part));
-      seeded = true;
-    }
+    // loss x_CM^N - x_CM^{n0}: seed d/d phi^N over the droplet's nodes (centres of step N - 1)
+    if (s == A.ncp - 1)
+      HIPCHK(launch_adjoint_seed<T>(c->stream, m, reinterpret_cast<const T*>(slot_of(k1 - k0)), d.pitch,
+                                    drops_at(k1 - k0 - 1),
+                                    reinterpret_cast<const DropDev*>(w + A.off_final + A.pop + 2 * A.field), drop,
+                                    lam[cur], lam[cur] + 9 * M, lam[cur] + 10 * M, part, sw));
     // backward through the segment, latest step first
     for (int64_t k = k1 - 1; k >= k0; --k) {
-      const char* sslot = w + A.off_seg + (size_t)(k - k0) * A.sslot;
       const double tn = (double)(n0 + k);
       m.ramp = tn < g.t_star ? tn : g.t_star;
-      const AdjPlanes<T> p = planes(sslot, lam[cur], lam[cur ^ 1]);
-      HIPCHK(launch_adjoint_step<T>(c->stream, m, fwd_at(k - k0), p, adj_seg_drops(A, sslot), nd, dA0_part));
+      const AdjPlanes<T> p = planes(slot_of(k - k0), lam[cur], lam[cur ^ 1]);
+      HIPCHK(launch_adjoint_step<T>(c->stream, m, fwd_at(k - k0), p, drops_at(k - k0), part));
       cur ^= 1;
     }
   }
-  // results: d/d c^{n0} and the production-rate derivative summed in a fixed order
-  if (dc0) {
-    std::vector<T> h((size_t)M);
-    HIPCHK(hipMemcpyAsync(h.data(), lam[cur] + 10 * M, sizeof(T) * M, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    for (int64_t i = 0; i < M; ++i) dc0[i] = (double)h[(size_t)i];
-  }
-  if (dA0) {
-    std::vector<double> hp((size_t)A.nb);
-    HIPCHK(hipMemcpyAsync(hp.data(), dA0_part, sizeof(double) * hp.size(), hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
-    double s = 0.0;
-    for (double v : hp) s += v;
-    *dA0 = s;
-  }
+  HIPCHK(hipMemcpyAsync(result, sw, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(launch_adjoint_total(c->stream, part, A.nb, result + 1));
   // back to the state at the end of the forward pass
-  if ((rc = adj_load(c, A, w + A.off_final, n0 + N)) != LBM_OK) return rc;
+  c->parity = parity;
+  if ((rc = adj_load(c, A, w + A.off_final, n0 + N, nullptr)) != LBM_OK) return rc;
   HIPCHK(hipStreamSynchronize(c->stream));
-  return LBM_OK;
+  if (!(result[0] > 0.0)) return fail(LBM_E_STATE, "the droplet has no nodes with phi >= 0 at the end of the run");
+  if (dA0) *dA0 = result[1];
+  if (!dc0) return LBM_OK;
+  bool finite;
+  const T* const cb = lam[cur] + 10 * M;
+  return read_planes(c, M, 1, &dc0, finite, [&](int64_t first, int64_t count, double* v, uint32_t*) {
+    return launch_widen<T>(c->stream, cb + first, count, v);
+  });
 }
 
 }  // namespace
@@ -1752,10 +1791,13 @@ int lbm_adjoint_forward(lbm_ctx* c, void* ws, size_t bytes, int32_t drop, int64_
   if (bytes < A.total) return fail(LBM_E_NOMEM, "adjoint workspace too small (see lbm_adjoint_bytes)");
   char* w = static_cast<char*>(ws);
   const InstDev& d = c->L.inst[0];
-  std::vector<DropDev> dd(d.ndrop);
-  HIPCHK(hipMemcpyAsync(dd.data(), c->d_drops(), sizeof(DropDev) * d.ndrop, hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(hipStreamSynchronize(c->stream));
-  const double x0 = dd[drop].x;
+  if ((rc = need_pinned(c, read_bytes(A.nodes, 1))) != LBM_OK) return rc;  // what the gradient's read-back needs
+  volatile double* const at = reinterpret_cast<double*>(c->pinned);  // x of the droplet before and after
+  auto read_x = [&](int i) {
+    return hipMemcpyAsync(c->pinned + i * sizeof(double), &(c->d_drops() + drop)->x, sizeof(double),
+                          hipMemcpyDeviceToHost, c->stream);
+  };
+  HIPCHK(read_x(0));
   c->adj.valid = false;
   c->adj.n0 = c->step;
   c->adj.nsteps = nsteps;
@@ -1765,9 +1807,9 @@ int lbm_adjoint_forward(lbm_ctx* c, void* ws, size_t bytes, int32_t drop, int64_
     if ((rc = adj_save(c, A, w + A.off_cp + (size_t)(k / every) * A.slot)) != LBM_OK) return rc;
     if ((rc = lbm_step(c, std::min<int64_t>(every, nsteps - k))) != LBM_OK) return rc;
   }
-  HIPCHK(hipMemcpyAsync(dd.data(), c->d_drops(), sizeof(DropDev) * d.ndrop, hipMemcpyDeviceToHost, c->stream));
+  HIPCHK(read_x(1));
   HIPCHK(hipStreamSynchronize(c->stream));
-  double dx = dd[drop].x - x0;
+  double dx = at[1] - at[0];
   if (dx >= 0.5 * d.nx) dx -= d.nx;
   if (dx < -0.5 * d.nx) dx += d.nx;
   if (J) *J = dx;

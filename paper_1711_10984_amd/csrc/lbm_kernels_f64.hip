@@ -6,10 +6,10 @@
 
 namespace lbm {
 
-hipError_t launch_reduce(hipStream_t s, int tiling, int ndrop_total, const InstDev* inst, DropDev* drops,
-                         const double* part, const uint64_t* mask, int64_t* step, int increment) {
+hipError_t launch_reduce(hipStream_t s, int tiling, int ndrop_total, const InstDev* inst, const DropDev* drops,
+                         DropDev* out, const double* part, const uint64_t* mask, int64_t* step, int increment) {
   hipLaunchKernelGGL(k_reduce, dim3(ndrop_total > 0 ? ndrop_total : 1), dim3(NTHREADS), 0, s, tiling,
-                     ndrop_total, inst, drops, part, mask, step, increment);
+                     ndrop_total, inst, drops, out, part, mask, step, increment);
   return hipGetLastError();
 }
 

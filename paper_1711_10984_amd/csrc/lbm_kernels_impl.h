@@ -760,10 +760,10 @@ __global__ __launch_bounds__(NTHREADS) void k_cm_partials(int parity, const Tile
 }
 
 // One workgroup per droplet: fixed-order sum of the tile partials of one tiling, new centre of mass
-// (Sec. 4), and the step counter.  increment 1: new centres and step + 1; 0: new centres only (the first pass);
+// (Sec. 4) into the table `out` (which may be the table read, `drops`), and the step counter.  increment 1: new centres and step + 1; 0: new centres only (the first pass);
 // -1: computes the sums and writes nothing (timing).
 __global__ __launch_bounds__(NTHREADS) void k_reduce(int tiling, int ndrop_total, const InstDev* __restrict__ insts,
-                                                     DropDev* __restrict__ drops,
+                                                     const DropDev* drops, DropDev* out,
                                                      const double* __restrict__ part,
                                                      const uint64_t* __restrict__ mask,
                                                      int64_t* __restrict__ step, int increment) {
@@ -798,9 +798,13 @@ __global__ __launch_bounds__(NTHREADS) void k_reduce(int tiling, int ndrop_total
       }
   }
   block_reduce3(a0, a1, a2, red);
-  if (threadIdx.x == 0 && a0 > 0.0 && increment >= 0) {
-    drops[g].x = wrapd(d.x + a1 / a0, (double)I.nx);
-    drops[g].y = wrapd(d.y + a2 / a0, I.yper);
+  if (threadIdx.x == 0 && increment >= 0) {
+    DropDev n = d;
+    if (a0 > 0.0) {
+      n.x = wrapd(d.x + a1 / a0, (double)I.nx);
+      n.y = wrapd(d.y + a2 / a0, I.yper);
+    }
+    out[g] = n;
   }
 }
 
