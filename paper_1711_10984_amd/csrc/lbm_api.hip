@@ -1506,7 +1506,7 @@ struct AdjLayout {
   size_t slot = 0;   // a whole state: populations, phi, c, droplet table, step counter
   size_t sslot = 0;  // what the adjoint step reads of a recomputed state: phi, c, droplet table, tiled steps' centres
   int64_t ncp = 0, nodes = 0;
-  int every = 0, nb = 0;
+  int every = 0, nparts = 0;  // nparts: running totals of dA0
   size_t off_cp = 0, off_seg = 0, off_final = 0, off_fwd = 0, off_adj = 0, off_part = 0, off_inst = 0, total = 0;
 };
 
@@ -1564,7 +1564,7 @@ AdjLayout adj_layout(const lbm_ctx* c, int64_t nsteps, int every) {
   AdjLayout A;
   const InstDev& d = c->L.inst[0];
   A.nodes = (int64_t)d.nx * d.ny;
-  A.nb = adj_blocks(d.nx, d.ny);
+  A.nparts = adj_parts(d.nx, d.ny);
   A.every = every;
   A.ncp = (nsteps + every - 1) / every;
   A.pop = (size_t)9 * d.pstride * c->L.elem;
@@ -1579,7 +1579,8 @@ AdjLayout adj_layout(const lbm_ctx* c, int64_t nsteps, int every) {
   A.off_fwd = off;
   off = align_up(off + sizeof(double) * ADJ_FWD_PLANES * (size_t)every * (size_t)A.nodes, ALIGN);
   A.off_adj = off;   off = align_up(off + c->L.elem * (size_t)(22 + ADJ_TMP_PLANES) * A.nodes, ALIGN);
-  A.off_part = off;  off = align_up(off + sizeof(double) * ((size_t)A.nb + 1), ALIGN);
+  A.off_part = off;  
+  off = align_up(off + sizeof(double) * (1 + (size_t)std::max(A.nparts, adj_blocks(d.nx, d.ny))), ALIGN);
   A.off_inst = off;  off = align_up(off + sizeof(InstDev) * (size_t)every, ALIGN);
   A.total = off;
   return A;
@@ -1664,14 +1665,14 @@ int adj_backward(lbm_ctx* c, const AdjLayout& A, char* w, double* dA0, double* d
   auto fwd_rec = [&](int64_t j) { return fwd + (size_t)ADJ_FWD_PLANES * (size_t)j * (size_t)M; };
   auto fwd_at = [&](int64_t j) {
     const double* f = fwd_rec(j);
-    return AdjFwd{f + 0 * M, f + 1 * M, f + 2 * M, f + 3 * M, f + 4 * M,  f + 5 * M,
-                  f + 6 * M, f + 7 * M, f + 8 * M, f + 9 * M, f + 10 * M};
+    return AdjFwd{f + 0 * M, f + 1 * M, f + 2 * M, f + 3 * M, f + 4 * M,
+                  f + 5 * M, f + 6 * M, f + 7 * M, f + 8 * M, f + 10 * M};  // plane 9 (M) is not read
   };
   T* adj = reinterpret_cast<T*>(w + A.off_adj);
   T* lam[2] = {adj, adj + 11 * M};  // adjoint state (f 9 planes, phi, c) at n and at n + 1
   T* tmp = adj + 22 * M;
-  double* part = reinterpret_cast<double*>(w + A.off_part);  // the seed's partial sums, then per-block dA0 totals
-  double* const sw = part + A.nb;                            // the seed's sum of phi
+  double* const sw = reinterpret_cast<double*>(w + A.off_part);  // the seed's sum of phi
+  double* const part = sw + 1;                                   // its partial sums, then per-block dA0 totals
   double* const result = reinterpret_cast<double*>(c->pinned);  // that sum, dA0
   AdjModel m;
   m.nx = d.nx;
@@ -1754,7 +1755,7 @@ int adj_backward(lbm_ctx* c, const AdjLayout& A, char* w, double* dA0, double* d
     }
   }
   HIPCHK(hipMemcpyAsync(result, sw, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(launch_adjoint_total(c->stream, part, A.nb, result + 1));
+  HIPCHK(launch_adjoint_total(c->stream, part, A.nparts, result + 1));
   // back to the state at the end of the forward pass
   c->parity = parity;
   if ((rc = adj_load(c, A, w + A.off_final, n0 + N, nullptr)) != LBM_OK) return rc;

@@ -78,7 +78,7 @@ struct TileDev {
 // from w_i n0 with T = float).  `buf` is the typed base pointer of the field pool, `parity` selects the
 // current buffers.  Modes: 0 step, 1 step + stage export, 2 diagnostics (n, u) of instance dbg_inst only.  An export
 // names its instance in dbg_inst: inst exports all LBM_NSTAGE planes, -2 - inst (export_planes()) only the first ADJ_EXPORT_PLANES
-// (mu .. X^{n+1/2}), which the reverse mode reads.
+// (mu .. X^{n+1/2}, M's left as it was), which the reverse mode reads.
 constexpr int ADJ_EXPORT_PLANES = 11;
 inline int export_planes(int inst, bool all) { return all ? inst : -2 - inst; }
 template <typename T, typename P>

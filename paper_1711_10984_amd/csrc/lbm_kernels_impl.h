@@ -269,6 +269,34 @@ __device__ __forceinline__ void lb_collide(const T (&d)[9], T dn, T nn, T ux, T 
   }
 }
 
+// Index v within one lattice width of [0, n), wrapped.
+__device__ __forceinline__ int near_index(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
+
+// Position in a W x H region of its node number i, its inner IX x IY nodes (`ring` rings inside the edge) first: the
+// nodes that collide are then whole wavefronts, and the others skip the collision.
+template <int IX, int IY, int RING_>
+__device__ __forceinline__ void inner_first(int i, int& lx, int& ly) {
+  constexpr int W = IX + 2 * RING_, BAND = W * RING_;
+  if (i < IX * IY) {
+    ly = i / IX;
+    lx = i - ly * IX + RING_;
+    ly += RING_;
+  } else {
+    i -= IX * IY;
+    if (i < 2 * BAND) {  // the rows below and above
+      ly = i / W;
+      lx = i - ly * W;
+      ly += ly >= RING_ ? IY : 0;
+    } else {  // the columns beside
+      i -= 2 * BAND;
+      ly = i / (2 * RING_);
+      lx = i - ly * (2 * RING_);
+      lx += lx >= RING_ ? IX : 0;
+      ly += RING_;
+    }
+  }
+}
+
 // A sum in twice the working precision: hi + lo, with the rounding errors of hi's additions in lo.  The sums of
 // the same numbers in another order give the same double, so results do not depend on the tiling.
 struct Dd {
@@ -474,7 +502,7 @@ __device__ void tile_cm_sums(const InstDev& I, int t_local, int t_global, const 
 // ------------------------------------------------------------------------------------------------
 // k_lb: mu, X, F; pull + moments; collision.  MODE 0: step, 1: step + stage planes, 2: n and u of dbg_inst only.
 // Export launches name their instance in dbg_inst: inst for all LBM_NSTAGE stage planes, -2 - inst for the
-// first eleven (mu .. X^{n+1/2}) only, which is what the reverse mode reads.
+// first eleven but M (mu .. X^{n+1/2}) only, which is what the reverse mode reads.
 __device__ __forceinline__ int export_inst(int dbg_inst) { return dbg_inst >= 0 ? dbg_inst : -2 - dbg_inst; }
 __device__ __forceinline__ bool export_all(int dbg_inst) { return dbg_inst >= 0; }
 
@@ -707,7 +735,7 @@ __global__ __launch_bounds__(NTHREADS) void k_fd(int parity, const TileDev* __re
       const int64_t q = (int64_t)y * nx + x;
       dbg[7 * nplane + q] = (double)s_ph[i2];
       dbg[8 * nplane + q] = (double)ch;
-      dbg[9 * nplane + q] = (double)s_M[i1];
+      if (export_all(dbg_inst)) dbg[9 * nplane + q] = (double)s_M[i1];
       dbg[10 * nplane + q] = (double)s_Xh[i1];
       if (export_all(dbg_inst)) {
         dbg[11 * nplane + q] = (double)phn;
@@ -1408,7 +1436,7 @@ __global__ __launch_bounds__(NTHREADS) void k_step(int parity, const TileDev* __
         r_Xh[sm][lane] = Xh;
         if (DBG && own_col && r >= y0 && r < yend) {
           const int64_t q = (int64_t)r * nx + (x0 + col);
-          dbg[9 * nplane + q] = (double)M;
+          if (export_all(dbg_inst)) dbg[9 * nplane + q] = (double)M;
           dbg[10 * nplane + q] = (double)Xh;
         }
       }
@@ -2104,7 +2132,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
       XH4 = halfB1 * (gphx * gphx + gphy * gphy);
       if (DBG && own_col && q - 4 >= y0 && q - 4 < yend) {
         const int64_t qq = (int64_t)(q - 4) * nx + (x0 + col);
-        dbg[9 * nplane + qq] = (double)M4;
+        if (export_all(dbg_inst)) dbg[9 * nplane + qq] = (double)M4;
         dbg[10 * nplane + qq] = (double)XH4;
       }
     }

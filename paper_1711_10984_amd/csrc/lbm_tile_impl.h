@@ -95,34 +95,6 @@ struct TileCentre {
   }
 };
 
-// Index v within one lattice width of [0, n), wrapped.
-__device__ __forceinline__ int near_index(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
-
-// Position in a W x H region of its node number i, its inner IX x IY nodes (`ring` rings inside the edge) first: the
-// nodes that collide are then whole wavefronts, and the others skip the collision.
-template <int IX, int IY, int RING_>
-__device__ __forceinline__ void inner_first(int i, int& lx, int& ly) {
-  constexpr int W = IX + 2 * RING_, BAND = W * RING_;
-  if (i < IX * IY) {
-    ly = i / IX;
-    lx = i - ly * IX + RING_;
-    ly += RING_;
-  } else {
-    i -= IX * IY;
-    if (i < 2 * BAND) {  // the rows below and above
-      ly = i / W;
-      lx = i - ly * W;
-      ly += ly >= RING_ ? IY : 0;
-    } else {  // the columns beside
-      i -= 2 * BAND;
-      ly = i / (2 * RING_);
-      lx = i - ly * (2 * RING_);
-      lx += lx >= RING_ ? IX : 0;
-      ly += RING_;
-    }
-  }
-}
-
 // One step on tiles.  MULTI: a batch, with the list of its tiles; else the lattice is `one` and block b has tile
 // xcd_block() of it.  DBG: also export the stage planes of instance dbg_inst (the others are skipped), as k_step.
 template <typename T, typename P, int OX, int OY, int NT, bool DBG, bool MULTI>
@@ -397,7 +369,7 @@ __global__ __launch_bounds__(NT) void k_tile(int parity, InstDev one, const Tile
     s_Xh[i] = Xh;
     if (DBG && owned(lx, ly, 1)) {
       const int64_t o = (int64_t)r * nx + (x0 + lx - 1);
-      dbg[9 * nplane + o] = (double)M;
+      if (export_all(dbg_inst)) dbg[9 * nplane + o] = (double)M;
       dbg[10 * nplane + o] = (double)Xh;
     }
   }
