@@ -908,14 +908,14 @@ __global__ __launch_bounds__(ADJ_THREADS) void k_adj_seed(int pass, AdjModel m, 
 __global__ __launch_bounds__(ADJ_THREADS) void k_adj_total(const double* __restrict__ part, int n,
                                                            double* __restrict__ out) {
   __shared__ Dd red[ADJ_THREADS / 64];
-  Dd s{0.0, 0.0};
-  for (int i = threadIdx.x; i < n; i += ADJ_THREADS) dd_add(s, part[i]);
-  s = dd_wave_sum(s);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  Dd s[1] = {{0.0, 0.0}};
+  for (int i = threadIdx.x; i < n; i += ADJ_THREADS) dd_add(s[0], part[i]);
+  dd_wave_sum(s);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s[0];
   __syncthreads();
   if (threadIdx.x != 0) return;
-  for (int w = 1; w < ADJ_THREADS / 64; ++w) dd_add(s, red[w]);
-  *out = isfinite(s.hi) ? dd_value(s) : s.hi;
+  for (int w = 1; w < ADJ_THREADS / 64; ++w) dd_add(s[0], red[w]);
+  *out = isfinite(s[0].hi) ? dd_value(s[0]) : s[0].hi;
 }
 
 template <typename T>

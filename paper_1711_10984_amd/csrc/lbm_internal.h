@@ -119,11 +119,11 @@ struct TileShape {
   int most;             // tiles of a launch up to which the shape is taken
 };
 // Ascending: the first shape that covers the lattices in `most` tiles is taken.  A workgroup per compute unit at
-// most, on the smallest tiles that allow it: 64 x 64 takes 8.5 us per step on 16 x 8 tiles, 9.9 on 16 x 16 and 12.3
-// on 32 x 16; 256 x 256 12.3, 10.8 and 13.2; 512 x 256 22, 15.7 and 14.4 (FP64).  Twice as many of the largest tiles
-// at 512 x 512 (27.4) still match the split pair (30); at 768 x 768 (64) every strip kernel is faster (46).
+// most, on the smallest tiles that allow it: a 64 x 64 step takes 6.5 us on 16 x 8 tiles, 7.8 on 16 x 16 and 10.2 on
+// 32 x 16; 256 x 256 9.8, 8.6 and 10.8; 512 x 256 18.9, 16.2 and 11.8 (FP64).  Twice as many of the largest tiles at
+// 512 x 512 (23.6) still beat the split pair (30); at 768 x 768 every strip kernel is faster.
 constexpr int TILE_NSHAPES = 3;
-constexpr TileShape TILE_SHAPES[TILE_NSHAPES] = {{16, 8, 512, 256}, {16, 16, 512, 256}, {32, 16, 1024, 512}};
+constexpr TileShape TILE_SHAPES[TILE_NSHAPES] = {{16, 8, 512, 256}, {16, 16, 1024, 256}, {32, 16, 1024, 512}};
 constexpr int TILE_RINGS = 5;  // a lattice is at least a tile and its rings on one side wide and high
 struct TileSeq {
   const double* cen_in;  // [ndrop][2] centres that the sums of part_in are relative to

@@ -312,12 +312,41 @@ __device__ __forceinline__ void dd_add(Dd& s, const Dd& v) {
   s.lo += v.lo;
 }
 __device__ __forceinline__ double dd_value(const Dd& s) { return s.hi + s.lo; }
-__device__ __forceinline__ Dd dd_wave_sum(Dd s) {
-  for (int o = 32; o > 0; o >>= 1) {
-    const Dd v{__shfl_xor(s.hi, o, 64), __shfl_xor(s.lo, o, 64)};
-    dd_add(s, v);
+// v of another lane by DPP (0 where the control has no source or masks the row).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_get(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+template <int CTRL, int ROWS, int N>
+__device__ __forceinline__ void dd_dpp_add(Dd (&s)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const Dd v{dpp_get<CTRL, ROWS>(s[i].hi), dpp_get<CTRL, ROWS>(s[i].lo)};
+    dd_add(s[i], v);
   }
-  return s;
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+// Sums over each row of 16 lanes, into its last lane.
+template <int N>
+__device__ __forceinline__ void dd_row_sum(Dd (&s)[N]) {
+  dd_dpp_add<0x111, 0xf>(s);  // row_shr:1, 2, 4, 8
+  dd_dpp_add<0x112, 0xf>(s);
+  dd_dpp_add<0x114, 0xf>(s);
+  dd_dpp_add<0x118, 0xf>(s);
+}
+// Sums over the wavefront; every lane receives them.
+template <int N>
+__device__ __forceinline__ void dd_wave_sum(Dd (&s)[N]) {
+  dd_row_sum(s);
+  dd_dpp_add<0x142, 0xa>(s);  // row_bcast:15 into rows 1 and 3
+  dd_dpp_add<0x143, 0xc>(s);  // row_bcast:31 into rows 2 and 3
+#pragma unroll
+  for (int i = 0; i < N; ++i) s[i] = Dd{lane_value(s[i].hi, 63), lane_value(s[i].lo, 63)};
 }
 
 // Sum (or min/max) over the workgroup in a fixed order; every thread receives lane 0's result.
@@ -1078,7 +1107,7 @@ __global__ __launch_bounds__(NTHREADS) void k_obs_final(const InstDev* __restric
     }
     s[0] = Dd{e, 0.0};
   } else {
-    for (int i = 0; i < 3; ++i) s[i] = dd_wave_sum(s[i]);
+    dd_wave_sum(s);
   }
   if (lane == 0)
     for (int i = 0; i < 3; ++i) s_sum[wv][i] = s[i];

@@ -9,7 +9,11 @@
 // Here a step is a chain of six stages whatever the size, bound by latency (loads, barriers, dependent arithmetic)
 // while there is a workgroup per compute unit at most, and by instruction issue beyond.  One step, FP64, in us
 // (centres of mass included), tiles / k_step of 64 rows / k_lb and k_fd:
-//   64 x 64  8.5 / 73 / 21;   256 x 256  10.7 / 78 / 22;   512 x 256  14.3 / 78 / 23;   512 x 512  27.4 / 81 / 30
+//   64 x 64  6.6 / 73 / 21;   256 x 256  8.5 / 78 / 22;   512 x 256  11.8 / 78 / 23;   512 x 512  23.6 / 81 / 30
+// Of the 64 x 64 step's 5.9 us inside the kernel, 1.4 are the loads, 0.6 to 1 each of the six stages and 0.9 the sums.
+// What a stage leaves idle takes the work that is not on the chain: the collision runs beside s3, c^{n+1} beside
+// phi^{n+1}, and the centres on a wavefront that has no part in s3 (before, the collision lengthened s2, c followed phi
+// and the centres held up s4: 8.6, 10.7 and 14.2 us).
 //
 // The centres of mass need a sum over the whole lattice after every step.  It is taken without a launch of its
 // own: a step leaves each tile's sums in memory, and the workgroups of the next step each add them up (in the
@@ -23,10 +27,12 @@
 namespace lbm {
 namespace {
 
-// The centre of mass of droplet k of an instance from its tiles' sums, by one wavefront, in three parts so that its
-// loads run beside other work: begin() loads the tiles' presence bits, load() lists the tiles that hold the droplet
-// and loads the sums of the first 64 of them, finish() adds up.  Tiles are taken TILE_CHUNK at a time; one chunk
-// covers every lattice whose tiles fit the chip at once.
+// The centre of mass of droplet k of an instance from its tiles' sums, by one wavefront, in parts so that each runs
+// while the wavefront would wait for others: begin() loads the tiles' presence bits, load() lists the tiles that hold
+// the droplet and loads the sums of the first 64 of them, sum() adds up, move() gives the centre.  Tiles are taken TILE_CHUNK at a time; one chunk
+// covers every lattice whose tiles fit the chip at once.  Each of the three sums has a row of 16 lanes (the last row
+// repeats the third), one tile's entry to a lane: additions in twice the working precision are chains of dependent
+// FP64 operations, and all three sums over all 64 lanes took the whole stage beside them (1.4 us) and more.
 constexpr int TILE_UNR = 4, TILE_CHUNK = 64 * TILE_UNR;
 struct TileCentre {
   const double* part;
@@ -34,7 +40,8 @@ struct TileCentre {
   uint16_t* list;  // LDS, TILE_CHUNK entries of the wavefront's own
   int nt, nd, n;
   uint32_t m[TILE_UNR];
-  Dd s[3];
+  Dd e[4];
+  double v;  // the row's sum, in its last lane
 
   __device__ __forceinline__ void bits(int c0) {
 #pragma unroll
@@ -63,34 +70,40 @@ struct TileCentre {
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
-  __device__ __forceinline__ void entry(int c0, int j, int k, Dd (&e)[3]) const {
-    const double* const p = part + ((int64_t)(c0 + list[j]) * nd + k) * 6;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) e[i] = Dd{p[2 * i], p[2 * i + 1]};
+  // entry j of the list, this lane's sum of it
+  __device__ __forceinline__ Dd entry(int c0, int j, int k) const {
+    const double* const p = part + ((int64_t)(c0 + list[j]) * nd + k) * 6 + 2 * min((int)(threadIdx.x & 63) >> 4, 2);
+    return Dd{p[0], p[1]};
   }
   __device__ __forceinline__ void load(int k) {
     collect(k);
-    s[0] = s[1] = s[2] = Dd{0.0, 0.0};
-    if ((int)(threadIdx.x & 63) < n) entry(0, threadIdx.x & 63, k, s);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = u * 16 + (int)(threadIdx.x & 15);
+      e[u] = j < n ? entry(0, j, k) : Dd{0.0, 0.0};
+    }
   }
-  __device__ __forceinline__ void finish(const InstDev& I, int k, double& cx, double& cy) {
+  __device__ __forceinline__ void sum(int k) {
+    Dd s[1] = {e[0]};
+#pragma unroll
+    for (int u = 1; u < 4; ++u)
+      if (u * 16 < n) dd_add(s[0], e[u]);
     for (int c0 = 0;;) {
-      for (int j = (threadIdx.x & 63) + (c0 == 0 ? 64 : 0); j < n; j += 64) {
-        Dd e[3];
-        entry(c0, j, k, e);
-        for (int i = 0; i < 3; ++i) dd_add(s[i], e[i]);
-      }
+      for (int j = (int)(threadIdx.x & 15) + (c0 == 0 ? 64 : 0); j < n; j += 16) dd_add(s[0], entry(c0, j, k));
       c0 += TILE_CHUNK;
       if (c0 >= nt) break;
       bits(c0);
       collect(k);
     }
-    if (__ballot(s[0].hi > 0.0) == 0ull) return;  // no node of the droplet: its centre stays
-    for (int i = 0; i < 3; ++i) s[i] = dd_wave_sum(s[i]);
-    const double w = dd_value(s[0]);
-    if (w > 0.0) {
-      cx = wrapd(cx + dd_value(s[1]) / w, (double)I.nx);
-      cy = wrapd(cy + dd_value(s[2]) / w, I.yper);
+    dd_row_sum(s);
+    v = dd_value(s[0]);
+  }
+  __device__ __forceinline__ void move(const InstDev& I, double& cx, double& cy) const {
+    const double w = lane_value(v, 15);
+    if (w > 0.0) {  // without a node of the droplet its centre stays
+      const double d = v / w;
+      cx = wrapd(cx + lane_value(d, 31), (double)I.nx);
+      cy = wrapd(cy + lane_value(d, 47), I.yper);
     }
   }
 };
@@ -114,6 +127,7 @@ __global__ __launch_bounds__(NT) void k_tile(int parity, InstDev one, const Tile
   __shared__ int s_src[TILE_DROPS];      // the droplet's production disk may reach the tile
   __shared__ double s_sum[NWO][TILE_DROPS][6];  // sums of the wavefronts that own nodes
   __shared__ uint32_t s_here[NWO];              // and the droplets that they met
+  __shared__ double s_cv[NWO][3][64];           // a wavefront's terms of one droplet's sums
   __shared__ uint16_t s_list[NW][TILE_CHUNK];
   T* const s_mu = s_a[0];
   T* const s_X = s_a[1];
@@ -254,11 +268,12 @@ __global__ __launch_bounds__(NT) void k_tile(int parity, InstDev one, const Tile
   }
   __syncthreads();
 
-  // ---- s2: force (Eq. 14), density and velocity (Eq. 11) on the tile and three rings; collision on the tile
+  // ---- s2: force (Eq. 14), density and velocity (Eq. 11) on the tile and three rings
   const T omega = T(I.omega), coef = T(I.coef);
   const T w0 = cst<T>(4.0 / 9.0), w1 = cst<T>(1.0 / 9.0), w5 = cst<T>(1.0 / 36.0);
   const T cw0 = coef * w0, cw1 = coef * w1, cw5 = coef * w5;
   const LbConst<T> lbk{w0, w1, w5, cw0, cw1, cw5, omega, T(I.wn[0]), T(I.wn[1]), T(I.wn[2]), T(I.n0)};
+  T d0[9], dn0, nn0, ux0, uy0, Fx0, Fy0;
 #pragma unroll
   for (int j = 0; j < R3; ++j) {
     if (tid + j * NT >= W3 * H3) continue;
@@ -275,49 +290,22 @@ __global__ __launch_bounds__(NT) void k_tile(int parity, InstDev one, const Tile
     lb_moments<T, P>(pf[j], lbk, Fx, Fy, d, dn, nn, ux, uy);
     s_ux[i] = ux;
     s_uy[i] = uy;
-    const int x = x0 + lx - 3, y = y0 + ly - 3;
-    if (tid + j * NT < OX * OY && x < nx && y < ny) {
-      P out[9];
-      double sv[9];
-      lb_collide<T, P>(d, dn, nn, ux, uy, Fx, Fy, lbk, out, sv);
-      const unsigned o = (unsigned)(y * pitch + x) * (unsigned)sizeof(P);
-      for (int k = 0; k < 9; ++k) st_col(fout + k * plane, o, out[k]);
-      if (DBG) {
-        const int64_t g = (int64_t)y * nx + x;
-        dbg[2 * nplane + g] = (double)Fx;
-        dbg[3 * nplane + g] = (double)Fy;
-        dbg[4 * nplane + g] = (double)nn;
-        dbg[5 * nplane + g] = (double)ux;
-        dbg[6 * nplane + g] = (double)uy;
-        if (export_all(dbg_inst))
-          for (int k = 0; k < 9; ++k) dbg[(13 + k) * nplane + g] = sv[k];
-      }
+    if (j == 0) {  // an own node's, for the collision
+      for (int k = 0; k < 9; ++k) d0[k] = d[k];
+      dn0 = dn;
+      nn0 = nn;
+      ux0 = ux;
+      uy0 = uy;
+      Fx0 = Fx;
+      Fy0 = Fy;
     }
   }
+  if (follow) tc.sum(k0);
   __syncthreads();
 
-  // ---- s3: advection half-step (Eqs. 16-17) on the tile and two rings
-  const int adv = I.advection;
-  for (int i = tid; i < W2 * H2; i += NT) {
-    const int ly = i / W2, lx = i - ly * W2;
-    const int c3 = (ly + 1) * W3 + lx + 1, c5 = (ly + 3) * W5 + lx + 3;
-    const int r = y0 + ly - 2;
-    const T uc = s_ux[c3], ue = s_ux[c3 + 1], uw = s_ux[c3 - 1], vc = s_uy[c3];
-    // beyond a plate: the mirror image of the boundary row, with u_y reversed
-    const T vn = (walls && r == ny - 1) ? -vc : s_uy[c3 + W3];
-    const T vs = (walls && r == 0) ? -vc : s_uy[c3 - W3];
-    s_ph[i] = advect_n(s_phi[c5], s_phi[c5 + 1], s_phi[c5 - 1], s_phi[c5 + W5], s_phi[c5 - W5], uc, ue, uw, vc, vn, vs,
-                       adv);
-    s_ch[i] = advect_n(s_c[c5], s_c[c5 + 1], s_c[c5 - 1], s_c[c5 + W5], s_c[c5 - W5], uc, ue, uw, vc, vn, vs, adv);
-    if (DBG && owned(lx, ly, 2)) {
-      const int64_t o = (int64_t)r * nx + (x0 + lx - 2);
-      dbg[7 * nplane + o] = (double)s_ph[i];
-      dbg[8 * nplane + o] = (double)s_ch[i];
-    }
-  }
-  __syncthreads();
-
-  // ---- the centres of mass at n
+  // ---- the centres of mass at n, by the last wavefronts (the very last has nothing else to do here).  Theirs is the
+  // longest chain, and the code is theirs alone (its instructions are fetched for them): they go first
+  if (k0 < nd) __builtin_amdgcn_s_setprio(3);
   for (int k = k0; k < nd; k += NW) {
     if (k != k0) {
       dd0 = drops[I.drop_base + k];
@@ -328,9 +316,10 @@ __global__ __launch_bounds__(NT) void k_tile(int parity, InstDev one, const Tile
         cx0 = q.cen_in[2 * (I.drop_base + k)];
         cy0 = q.cen_in[2 * (I.drop_base + k) + 1];
         tc.load(k);
+        tc.sum(k);
       }
     }
-    if (follow) tc.finish(I, k, cx0, cy0);
+    if (follow) tc.move(I, cx0, cy0);
     if (lane == 0) {
       if (t == I.tile_base[TILING_TILE]) {
         q.cen_out[2 * (I.drop_base + k)] = cx0;
@@ -349,6 +338,52 @@ __global__ __launch_bounds__(NT) void k_tile(int parity, InstDev one, const Tile
       s_src[k] = dd0.active && sdx * sdx + sdy * sdy <= rr * rr;
     }
   }
+  if (k0 < nd) __builtin_amdgcn_s_setprio(0);
+
+  constexpr int S3 = NT - (W2 * H2 + 63) / 64 * 64 - 64;
+  static_assert(S3 >= 0 && OX * OY < NT, "the last wavefront has no part of the collision and of s3");
+  constexpr int FIRST3 = S3 < OX * OY ? S3 : OX * OY;
+  const int adv = I.advection;
+  if (__builtin_amdgcn_readfirstlane(wv) != NW - 1) {
+    // ---- collision (Eqs. 10, 12, 13) on the tile, by the first wavefronts while the others take s3
+    if (const int x = x0 + lx3[0] - 3, y = y0 + ly3[0] - 3; tid < OX * OY && x < nx && y < ny) {
+      P out[9];
+      double sv[9];
+      lb_collide<T, P>(d0, dn0, nn0, ux0, uy0, Fx0, Fy0, lbk, out, sv);
+      const unsigned o = (unsigned)(y * pitch + x) * (unsigned)sizeof(P);
+      for (int k = 0; k < 9; ++k) st_col(fout + k * plane, o, out[k]);
+      if (DBG) {
+        const int64_t g = (int64_t)y * nx + x;
+        dbg[2 * nplane + g] = (double)Fx0;
+        dbg[3 * nplane + g] = (double)Fy0;
+        dbg[4 * nplane + g] = (double)nn0;
+        dbg[5 * nplane + g] = (double)ux0;
+        dbg[6 * nplane + g] = (double)uy0;
+        if (export_all(dbg_inst))
+          for (int k = 0; k < 9; ++k) dbg[(13 + k) * nplane + g] = sv[k];
+      }
+    }
+
+    // ---- s3: advection half-step (Eqs. 16-17) on the tile and two rings
+    for (int i = (tid + NT - FIRST3) % NT; i < W2 * H2; i += NT) {
+      const int ly = i / W2, lx = i - ly * W2;
+      const int c3 = (ly + 1) * W3 + lx + 1, c5 = (ly + 3) * W5 + lx + 3;
+      const int r = y0 + ly - 2;
+      const T uc = s_ux[c3], ue = s_ux[c3 + 1], uw = s_ux[c3 - 1], vc = s_uy[c3];
+      // beyond a plate: the mirror image of the boundary row, with u_y reversed
+      const T vn = (walls && r == ny - 1) ? -vc : s_uy[c3 + W3];
+      const T vs = (walls && r == 0) ? -vc : s_uy[c3 - W3];
+      s_ph[i] = advect_n(s_phi[c5], s_phi[c5 + 1], s_phi[c5 - 1], s_phi[c5 + W5], s_phi[c5 - W5], uc, ue, uw, vc, vn, vs,
+                         adv);
+      s_ch[i] = advect_n(s_c[c5], s_c[c5 + 1], s_c[c5 - 1], s_c[c5 + W5], s_c[c5 - W5], uc, ue, uw, vc, vn, vs, adv);
+      if (DBG && owned(lx, ly, 2)) {
+        const int64_t o = (int64_t)r * nx + (x0 + lx - 2);
+        dbg[7 * nplane + o] = (double)s_ph[i];
+        dbg[8 * nplane + o] = (double)s_ch[i];
+      }
+    }
+  }
+  __syncthreads();
 
   // ---- s4: bracket M of Eq. (18) and X^{n+1/2} on the tile and one ring
   for (int i = tid; i < W1 * H1; i += NT) {
@@ -379,25 +414,22 @@ __global__ __launch_bounds__(NT) void k_tile(int parity, InstDev one, const Tile
   const T Gamma = T(I.Gamma), D = T(I.D), gam = T(I.gamma), c0 = T(I.c0);
   const double tn = (double)(*step + q.ahead);
   const double A = I.A0 * (tn < I.t_star ? tn : I.t_star);
-  constexpr int R0 = (OX * OY + NT - 1) / NT;
-  int kd[R0];
-  double cv0[R0], cv1[R0], cv2[R0];
-#pragma unroll
-  for (int j = 0; j < R0; ++j) {
-    kd[j] = -1;
-    cv0[j] = cv1[j] = cv2[j] = 0.0;
-    const int i = tid + j * NT;
-    const int ly = i / OX, lx = i - ly * OX;
-    const int x = x0 + lx, r = y0 + ly;
-    if (i >= OX * OY || x >= nx || r >= ny) continue;
-    const int m1 = (ly + 1) * W1, m2 = (ly + 2) * W2 + 1;
-    const bool top = walls && r == ny - 1, bot = walls && r == 0;
-    const int u1 = top ? m1 : m1 + W1, d1 = bot ? m1 : m1 - W1, u2 = top ? m2 : m2 + W2, d2 = bot ? m2 : m2 - W2;
-    const T phn = s_ph[m2 + lx + 1] + Gamma * lap9r(s_M + u1, s_M + m1, s_M + d1, lx + 1);
-    const T ch = s_ch[m2 + lx + 1];
-    const T lch = lap9r(s_ch + u2, s_ch + m2, s_ch + d2, lx + 1);
-    const T dv = div9r(s_ch + u2, s_ch + m2, s_ch + d2, D, s_Xh + u1, s_Xh + m1, s_Xh + d1, lx + 1);
-    const double xd = (double)x, yd = (double)r;
+  // phi and the sums by the first OX x OY threads, c by the next
+  static_assert(2 * OX * OY <= NT && OX * OY % 64 == 0, "two threads per node, in wavefronts of their own");
+  const int own = tid < OX * OY ? tid : tid - OX * OY;
+  const int lyo = own / OX, lxo = own - lyo * OX, xo = x0 + lxo, ro = y0 + lyo;
+  const bool valid = tid < 2 * OX * OY && xo < nx && ro < ny;
+  const bool top = walls && ro == ny - 1, bot = walls && ro == 0;
+  const int m1 = (lyo + 1) * W1, m2 = (lyo + 2) * W2 + 1;
+  const int u1 = top ? m1 : m1 + W1, d1 = bot ? m1 : m1 - W1, u2 = top ? m2 : m2 + W2, d2 = bot ? m2 : m2 - W2;
+  const double xd = (double)xo, yd = (double)ro;
+  const unsigned oo = (unsigned)(ro * pitch + xo) * (unsigned)sizeof(T);
+  int kd = -1;
+  double cv0 = 0.0, cv1 = 0.0, cv2 = 0.0;
+  if (valid && tid >= OX * OY) {
+    const T ch = s_ch[m2 + lxo + 1];
+    const T lch = lap9r(s_ch + u2, s_ch + m2, s_ch + d2, lxo + 1);
+    const T dv = div9r(s_ch + u2, s_ch + m2, s_ch + d2, D, s_Xh + u1, s_Xh + m1, s_Xh + d1, lxo + 1);
     int cnt = 0;
     for (int k = 0; k < nd; ++k)
       if (s_src[k]) {
@@ -406,14 +438,12 @@ __global__ __launch_bounds__(NT) void k_tile(int parity, InstDev one, const Tile
       }
     const double src = A * (double)cnt;
     const T cn = (((ch + D * lch) + dv) - gam * (ch - c0)) + T(src);
-    const unsigned o = (unsigned)(r * pitch + x) * (unsigned)sizeof(T);
-    st_col(phi_out, o, phn);
-    st_col(c_out, o, cn);
-    if (DBG && export_all(dbg_inst)) {
-      const int64_t g = (int64_t)r * nx + x;
-      dbg[11 * nplane + g] = (double)phn;
-      dbg[12 * nplane + g] = (double)cn;
-    }
+    st_col(c_out, oo, cn);
+    if (DBG && export_all(dbg_inst)) dbg[12 * nplane + (int64_t)ro * nx + xo] = (double)cn;
+  } else if (valid) {
+    const T phn = s_ph[m2 + lxo + 1] + Gamma * lap9r(s_M + u1, s_M + m1, s_M + d1, lxo + 1);
+    st_col(phi_out, oo, phn);
+    if (DBG && export_all(dbg_inst)) dbg[11 * nplane + (int64_t)ro * nx + xo] = (double)phn;
     const double v = (double)phn;
     if (nd > 0 && v >= 0.0) {
       // nearest centre, the lowest index on ties
@@ -430,34 +460,34 @@ __global__ __launch_bounds__(NT) void k_tile(int parity, InstDev one, const Tile
           by = dy;
         }
       }
-      kd[j] = best;
-      cv0[j] = v;
-      cv1[j] = v * bx;
-      cv2[j] = v * by;
+      kd = best;
+      cv0 = v;
+      cv1 = v * bx;
+      cv2 = v * by;
     }
   }
   if (nd == 0) return;
   if (wv < NWO) {
     uint32_t here = 0u;
     for (int k = 0; k < nd; ++k) {
-      bool mine = false;
-      Dd s[3] = {{0.0, 0.0}, {0.0, 0.0}, {0.0, 0.0}};
-#pragma unroll
-      for (int j = 0; j < R0; ++j)
-        if (kd[j] == k) {
-          mine = true;
-          dd_add(s[0], cv0[j]);
-          dd_add(s[1], cv1[j]);
-          dd_add(s[2], cv2[j]);
-        }
+      const bool mine = kd == k;
       if (__ballot(mine) == 0ull) continue;
       here |= 1u << k;
-      for (int j = 0; j < 3; ++j) s[j] = dd_wave_sum(s[j]);
-      if (lane == 0)
-        for (int j = 0; j < 3; ++j) {
-          s_sum[wv][k][2 * j] = s[j].hi;
-          s_sum[wv][k][2 * j + 1] = s[j].lo;
-        }
+      // as in TileCentre: a row of lanes for each sum, four nodes to a lane
+      s_cv[wv][0][lane] = mine ? cv0 : 0.0;
+      s_cv[wv][1][lane] = mine ? cv1 : 0.0;
+      s_cv[wv][2][lane] = mine ? cv2 : 0.0;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      const int i = lane >> 4;
+      const double* const t = s_cv[wv][min(i, 2)] + (lane & 15);
+      Dd s[1] = {{t[0], 0.0}};
+      for (int u = 1; u < 4; ++u) dd_add(s[0], t[16 * u]);
+      dd_row_sum(s);
+      if (i < 3 && (lane & 15) == 15) {
+        s_sum[wv][k][2 * i] = s[0].hi;
+        s_sum[wv][k][2 * i + 1] = s[0].lo;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
     if (lane == 0) s_here[wv] = here;
   }
@@ -491,7 +521,8 @@ __global__ __launch_bounds__(64) void k_tile_final(int ndrop_total, const InstDe
   TileCentre tc;
   tc.begin(I, q, list);
   tc.load(k);
-  tc.finish(I, k, cx, cy);
+  tc.sum(k);
+  tc.move(I, cx, cy);
   if (threadIdx.x == 0 && count > 0) {
     drops[g].x = cx;
     drops[g].y = cy;
