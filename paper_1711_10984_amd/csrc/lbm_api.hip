@@ -442,7 +442,7 @@ hipError_t enqueue_reduce(lbm_ctx* c, int64_t n, bool write = true) {
     return launch_tile_final(c->stream, c->L.ndrop_total, c->d_inst(), c->d_drops(), c->tile_seq(n), c->d_step(),
                              write ? n : 0);
   return launch_reduce(c->stream, c->path == LBM_PATH_SPLIT ? TILING_SPLIT : TILING_FUSED, c->L.ndrop_total, c->d_inst(),
-                       c->d_drops(), c->d_drops(), c->d_part(), c->d_mask(), c->d_step(), write ? 1 : -1);
+                       c->d_drops(), nullptr, c->d_part(), c->d_mask(), c->d_step(), write ? 1 : -1);
 }
 
 // n steps from the given parity.
@@ -972,7 +972,7 @@ int lbm_step_noalloc(const lbm_config* cfg, void* stream, void* const f[2], void
                                          part, mask, dstep, nullptr, -1,
                                          cf.walls == LBM_WALLS_NONE && cf.advection == LBM_ADV_PAPER);
     });
-    if (e == hipSuccess) e = launch_reduce(st, TILING_FUSED, ndrop, di, dd, dd, part, mask, dstep, 1);
+    if (e == hipSuccess) e = launch_reduce(st, TILING_FUSED, ndrop, di, dd, nullptr, part, mask, dstep, 1);
     if (e != hipSuccess) return fail(LBM_E_HIP, std::string("timestep launch: ") + hipGetErrorString(e));
   }
   if (ndrop > 0) {
@@ -1075,7 +1075,7 @@ int lbm_init_batch(int32_t ninst, const lbm_config* cfgs, void* workspace, size_
     return launch_cm_partials<T>(c->stream, 0, c->nlaunch(), c->d_tiles(), c->d_inst(), reinterpret_cast<T*>(c->pool()),
                                  c->d_drops(), c->d_part(), c->d_mask());
   }));
-  INIT_CHK(launch_reduce(c->stream, TILING_SPLIT, c->L.ndrop_total, c->d_inst(), c->d_drops(), c->d_drops(),
+  INIT_CHK(launch_reduce(c->stream, TILING_SPLIT, c->L.ndrop_total, c->d_inst(), c->d_drops(), nullptr,
                          c->d_part(), c->d_mask(), c->d_step(), 0));
   INIT_CHK(hipStreamSynchronize(c->stream));
 #undef INIT_CHK

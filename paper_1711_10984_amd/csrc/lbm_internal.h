@@ -92,8 +92,9 @@ template <typename T>
 hipError_t launch_cm_partials(hipStream_t s, int parity, int ntiles_launch, const TileDev* tiles,
                               const InstDev* inst, T* buf, const DropDev* drops, double* part,
                               uint64_t* mask);
-hipError_t launch_reduce(hipStream_t s, int tiling, int ndrop_total, const InstDev* inst, const DropDev* drops,
-                         DropDev* out, const double* part, const uint64_t* mask, int64_t* step, int increment);
+// New centres of mass into the table `drops` itself (out null) or, with the rest of each entry, into another one.
+hipError_t launch_reduce(hipStream_t s, int tiling, int ndrop_total, const InstDev* inst, DropDev* drops, DropDev* out,
+                         const double* part, const uint64_t* mask, int64_t* step, int increment);
 // Fused timestep (one launch per step over the strip list); dbg != nullptr also exports the stage planes of
 // instance dbg_inst and steps only that instance (its next state in the inactive half, and its centre-of-mass
 // partials).

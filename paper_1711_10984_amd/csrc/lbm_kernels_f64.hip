@@ -6,10 +6,14 @@
 
 namespace lbm {
 
-hipError_t launch_reduce(hipStream_t s, int tiling, int ndrop_total, const InstDev* inst, const DropDev* drops,
-                         DropDev* out, const double* part, const uint64_t* mask, int64_t* step, int increment) {
-  hipLaunchKernelGGL(k_reduce, dim3(ndrop_total > 0 ? ndrop_total : 1), dim3(NTHREADS), 0, s, tiling,
-                     ndrop_total, inst, drops, out, part, mask, step, increment);
+hipError_t launch_reduce(hipStream_t s, int tiling, int ndrop_total, const InstDev* inst, DropDev* drops, DropDev* out,
+                         const double* part, const uint64_t* mask, int64_t* step, int increment) {
+  const dim3 g(ndrop_total > 0 ? ndrop_total : 1), b(NTHREADS);
+  if (out)
+    hipLaunchKernelGGL((k_reduce<true>), g, b, 0, s, tiling, ndrop_total, inst, drops, out, part, mask, step, increment);
+  else
+    hipLaunchKernelGGL((k_reduce<false>), g, b, 0, s, tiling, ndrop_total, inst, drops, out, part, mask, step,
+                       increment);
   return hipGetLastError();
 }
 
