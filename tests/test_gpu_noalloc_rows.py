@@ -9,6 +9,8 @@ import pytest
 
 from paper_1711_10984_amd import workloads as W
 
+MANY = 100  # droplets: the short strips' partials then exceed the scratch array, and k_step takes the lattice
+
 pytestmark = pytest.mark.gpu
 WT = [4 / 9] + [1 / 9] * 4 + [1 / 36] * 4
 
@@ -43,16 +45,19 @@ def noalloc(lbm, p, phi0, c0, drops, prec, nsteps):
 @pytest.mark.parametrize("prec", [0, 1, 2])
 @pytest.mark.parametrize("nx,ny,walls", [(255, 256, 0), (256, 256, 0), (271, 257, 1), (700, 333, 0), (1000, 1100, 1),
                                          (34560, 208, 0)])
-def test_fields_do_not_depend_on_the_height(nx, ny, walls, prec):
+@pytest.mark.parametrize("ndrop", [5, MANY])
+def test_fields_do_not_depend_on_the_height(nx, ny, walls, prec, ndrop):
     from paper_1711_10984_amd import lbm
     if nx > 30000 and prec != 0:
         pytest.skip("one precision for the largest")
+    if ndrop == MANY and nx < 30000:
+        pytest.skip("fits whatever the height")
     rng = np.random.default_rng(nx + ny)
     p = dict(W.ACTIVE, nx=nx, ny=ny, walls=walls, tau=0.9)
     phi = 0.3 * rng.standard_normal((ny, nx)) - 0.3
     c = 0.05 + 0.01 * rng.standard_normal((ny, nx))
     drops = [dict(x=rng.uniform(0, nx), y=rng.uniform(0, ny), R=ny / 4.0, Rs=ny / 9.0, ex=0.6, ey=-0.8, active=1)
-             for _ in range(5)]
+             for _ in range(ndrop)]
     nsteps = 5
     sim = lbm.Sim([p], [phi], [c], [drops], precision=prec, path=lbm.LBM_PATH_WAVE, graph_steps=0)
     sim.set_seg_rows(64)
