@@ -330,8 +330,12 @@ struct lbm_ctx {
   char* pinned = nullptr;
   size_t pinned_bytes = 0;
   hipEvent_t read_ev[2] = {nullptr, nullptr};
-  hipGraphExec_t exec[2] = {nullptr, nullptr};
-  hipGraph_t graph[2] = {nullptr, nullptr};
+  // graphs of graph_steps steps, by starting parity, and (2 and 3) of LONG_GRAPH times as many for tiled steps: the
+  // last launch of a sequence and the start of the next graph take 8 us, as long as a step.  The long ones are captured
+  // by the second call that could use them, so that a single call does not pay for them.
+  hipGraphExec_t exec[4] = {nullptr, nullptr, nullptr, nullptr};
+  hipGraph_t graph[4] = {nullptr, nullptr, nullptr, nullptr};
+  bool long_asked = false;
   // the last recorded forward pass of lbm_adjoint_forward (see lbm_adjoint_backward)
   struct {
     bool valid = false;
@@ -461,8 +465,10 @@ hipError_t enqueue_steps_any(lbm_ctx* c, int parity, int64_t n) {
   return with_types(c->L.prec, [&](auto t, auto p) { return enqueue_steps<decltype(t), decltype(p)>(c, parity, n); });
 }
 
+constexpr int LONG_GRAPH = 5;
+
 void destroy_graphs(lbm_ctx* c) {
-  for (int p = 0; p < 2; ++p) {
+  for (int p = 0; p < 4; ++p) {
     if (c->exec[p]) (void)hipGraphExecDestroy(c->exec[p]);
     if (c->graph[p]) (void)hipGraphDestroy(c->graph[p]);
     c->exec[p] = nullptr;
@@ -470,9 +476,9 @@ void destroy_graphs(lbm_ctx* c) {
   }
 }
 
-int build_graph(lbm_ctx* c, int parity) {
+int build_graph(lbm_ctx* c, int which) {
   HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed));
-  const hipError_t err = enqueue_steps_any(c, parity, c->graph_steps);
+  const hipError_t err = enqueue_steps_any(c, which & 1, (int64_t)c->graph_steps * (which < 2 ? 1 : LONG_GRAPH));
   hipGraph_t g = nullptr;
   hipError_t e2 = hipStreamEndCapture(c->stream, &g);
   if (err != hipSuccess) {
@@ -480,8 +486,8 @@ int build_graph(lbm_ctx* c, int parity) {
     return fail(LBM_E_HIP, std::string("kernel launch during capture: ") + hipGetErrorString(err));
   }
   if (e2 != hipSuccess) return fail(LBM_E_HIP, std::string("hipStreamEndCapture: ") + hipGetErrorString(e2));
-  c->graph[parity] = g;
-  HIPCHK(hipGraphInstantiate(&c->exec[parity], g, nullptr, nullptr, 0));
+  c->graph[which] = g;
+  HIPCHK(hipGraphInstantiate(&c->exec[which], g, nullptr, nullptr, 0));
   return LBM_OK;
 }
 
@@ -1107,8 +1113,9 @@ int lbm_set_graph(lbm_ctx* c, int32_t steps_per_graph) {
   if (steps_per_graph > 0 && !c->stream) return fail(LBM_E_STATE, "graph replay needs a non-default stream");
   destroy_graphs(c);
   c->graph_steps = steps_per_graph;
-  // capture both graphs now (one per starting parity), so that no later lbm_step pays for a capture
-  for (int p = 0; p < 2 && steps_per_graph > 0; ++p) {
+  // capture the graphs now (one per starting parity), so that no later lbm_step pays for a capture
+  c->long_asked = c->long_asked || (c->tiled() && steps_per_graph > 0);
+  for (int p = 0; p < (c->tiled() ? 4 : 2) && steps_per_graph > 0; ++p) {
     const int rc = build_graph(c, p);
     if (rc != LBM_OK) return rc;
   }
@@ -1121,15 +1128,20 @@ int lbm_step(lbm_ctx* c, int64_t n) {
   Range range("lbm_step");
   int64_t left = n;
   if (c->graph_steps > 0) {
+    const int64_t longer = (int64_t)c->graph_steps * LONG_GRAPH;
+    const bool use_long = c->tiled() && left >= longer && c->long_asked;
+    c->long_asked = c->long_asked || (c->tiled() && left >= longer);
     while (left >= c->graph_steps) {
       Range replay("lbm_step graph replay");
-      if (!c->exec[c->parity]) {
-        int rc = build_graph(c, c->parity);
+      const bool lg = use_long && left >= longer;
+      const int which = c->parity + (lg ? 2 : 0);
+      if (!c->exec[which]) {
+        int rc = build_graph(c, which);
         if (rc != LBM_OK) return rc;
       }
-      HIPCHK(hipGraphLaunch(c->exec[c->parity], c->stream));
-      left -= c->graph_steps;
-      c->step += c->graph_steps;
+      HIPCHK(hipGraphLaunch(c->exec[which], c->stream));
+      left -= lg ? longer : c->graph_steps;
+      c->step += lg ? longer : c->graph_steps;
     }
   }
   const hipError_t e = enqueue_steps_any(c, c->parity, left);
