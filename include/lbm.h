@@ -218,7 +218,9 @@ const int32_t* lbm_tune_widths(void);
  * height) when both_paths != 0, else for the current sweeping path only -- and set the path, width and
  * height of the fastest (the width is then read with lbm_get_strip_width).  Where the fused path can cover the
  * lattices by tiles, that is tried too, without an entry in ms_out; if it is the fastest, LBM_PATH_FUSED is set with
- * the best strips' height and width.
+ * the best strips' height and width.  Where it cannot and the strips are few, shorter ones than LBM_SEG_ROWS_MIN are
+ * tried as well; if they are the fastest they are used, until a height or width is set, and the height returned is the
+ * best of the list.
  * The trial launches read the current state and write only scratch (the inactive halves of the ping-pong
  * buffers, the velocity planes and the centre-of-mass partials): the state, the droplet table and the step
  * counter are unchanged.  Called on the split path with both_paths == 0, nothing is tried.

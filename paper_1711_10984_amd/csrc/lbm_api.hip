@@ -137,6 +137,11 @@ int tile_shape(const std::vector<InstDev>& inst) {
   return -1;
 }
 
+int strip_count(int nx, int ny, int w, int rows) { return ((nx + w - 1) / w) * ((ny + rows - 1) / rows); }
+int strip_bound(int nx, int ny) {
+  return std::max(strip_count(nx, ny, STRIP_W_MIN, SEG_ROWS_MIN), strip_count(nx, ny, FUSED_TX, SHORT_ROWS[0]));
+}
+
 void make_layout(int32_t ninst, const lbm_config* cfgs, const int32_t* ndrop, Layout& L) {
   L.prec = cfgs[0].precision;
   L.elem = L.prec == LBM_FP64 ? 8 : 4;
@@ -156,9 +161,10 @@ void make_layout(int32_t ninst, const lbm_config* cfgs, const int32_t* ndrop, La
     d.tiles_x[TILING_SPLIT] = (c.nx + TILE_X - 1) / TILE_X;
     d.tiles_y[TILING_SPLIT] = (c.ny + TILE_Y - 1) / TILE_Y;
     d.tile_base[TILING_SPLIT] = tile_base;
-    // upper bounds (narrowest strips, shortest segments); see set_segments
-    d.tiles_x[TILING_FUSED] = (c.nx + STRIP_W_MIN - 1) / STRIP_W_MIN;
-    d.tiles_y[TILING_FUSED] = (c.ny + SEG_ROWS_MIN - 1) / SEG_ROWS_MIN;
+    // an upper bound of the strips (the narrowest and shortest that a caller may set, or the widest of SHORT_ROWS); see
+    // set_segments
+    d.tiles_x[TILING_FUSED] = strip_bound(c.nx, c.ny);
+    d.tiles_y[TILING_FUSED] = 1;
     d.tile_base[TILING_FUSED] = seg_base;
     d.drop_base = drop_base;
     const int64_t plane = (int64_t)c.ny * d.pitch;
@@ -268,7 +274,8 @@ bool segment_holds_droplet(const InstDev& d, const std::vector<DropDev>& drops, 
 // XCD gets a contiguous run of strips in natural order (neighbouring strips share that XCD's L2); within
 // its run, the strips that hold droplets (as of `drops`) are dispatched first, so that the longer-running
 // ones do not end the launch.  The launch order does not change any result (partials are stored by natural
-// index).  Fits in the regions sized for STRIP_W_MIN and SEG_ROWS_MIN.
+// index).  The caller sees to it that the strips of every instance are at most strip_bound(), which the regions are
+// sized for.
 void set_segments(Layout& L, int seg_rows, int strip_w, const std::vector<DropDev>& drops) {
   int base = 0;
   int64_t part = 0;
@@ -716,14 +723,19 @@ int read_all_drops(lbm_ctx* c, std::vector<DropDev>& out) {
 }
 
 // Rebuild the strip list for a segment height and strip width (launch order from the current droplet
-// centres) and upload it.
-int apply_segments(lbm_ctx* c, int rows, int width) {
+// centres) and upload it.  shorter: the strips' height where it is not the height the caller sees, one of SHORT_ROWS.
+int apply_segments(lbm_ctx* c, int rows, int width, int shorter = 0) {
+  const int h = shorter ? shorter : rows;
+  for (const InstDev& d : c->L.inst)
+    if (strip_count(d.nx, d.ny, width, h) > strip_bound(d.nx, d.ny))
+      return fail(LBM_E_INVAL, "more strips than the workspace is sized for");
   HIPCHK(hipStreamSynchronize(c->stream));
   destroy_graphs(c);
   std::vector<DropDev> drops;
   int rc = read_all_drops(c, drops);
   if (rc != LBM_OK) return rc;
-  set_segments(c->L, rows, width, drops);
+  set_segments(c->L, h, width, drops);
+  c->L.seg_rows = rows;
   HIPCHK(hipMemcpyAsync(c->d_inst(), c->L.inst.data(), sizeof(InstDev) * c->L.inst.size(), hipMemcpyHostToDevice,
                         c->stream));
   HIPCHK(hipMemcpyAsync(c->d_segs(), c->L.segs.data(), sizeof(TileDev) * c->L.segs.size(), hipMemcpyHostToDevice,
@@ -1431,8 +1443,8 @@ int lbm_autotune(lbm_ctx* c, int32_t launches, int32_t both_paths, int32_t* rows
           best_path = paths[pi];
         }
       }
-  // the split path (two tile kernels) and the tiled fused step, which have no strip height, compete with the
-  // best strips
+  // shorter strips, the split path (two tile kernels) and the tiled fused step, which have no entry among the heights,
+  // compete with the best strips
   auto compete = [&](auto one, double& ms_best) -> int {
     for (int pass = 0; pass < 2; ++pass) {
       hipError_t e = one();
@@ -1447,6 +1459,24 @@ int lbm_autotune(lbm_ctx* c, int32_t launches, int32_t both_paths, int32_t* rows
     }
     return LBM_OK;
   };
+  int best_short = 0;
+  int64_t strips = 0;
+  for (const InstDev& d : c->L.inst) strips += strip_count(d.nx, d.ny, FUSED_TX, SEG_ROWS_MIN);
+  for (int pi = 0; pi < 2 && strips <= SHORT_MOST && c->L.tshape < 0; ++pi) {
+    if (!both_paths && paths[pi] != start_path) continue;
+    c->path = paths[pi];
+    for (int h : SHORT_ROWS) {
+      double ms = 1e300;
+      if (rc == LBM_OK) rc = apply_segments(c, best_rows, FUSED_TX, h);
+      if (rc == LBM_OK) rc = compete([&] { return trial(1); }, ms);
+      if (ms < best_ms) {
+        best_ms = ms;
+        best_short = h;
+        best_w = FUSED_TX;
+        best_path = paths[pi];
+      }
+    }
+  }
   bool best_tile = false;
   if (both_paths && rc == LBM_OK) {
     c->path = LBM_PATH_SPLIT;
@@ -1481,7 +1511,8 @@ int lbm_autotune(lbm_ctx* c, int32_t launches, int32_t both_paths, int32_t* rows
   if (rc != LBM_OK) return rc;
   if ((rc = lbm_set_path(c, best_path)) != LBM_OK) return rc;
   if (best_path == LBM_PATH_FUSED) c->tile = best_tile;
-  if ((rc = apply_segments(c, best_rows, best_w)) != LBM_OK) return rc;
+  if ((rc = apply_segments(c, best_rows, best_w, best_path == LBM_PATH_SPLIT || best_tile ? 0 : best_short)) != LBM_OK)
+    return rc;
   if (rows_out) *rows_out = best_rows;
   if (path_out) *path_out = best_path;
   return LBM_OK;

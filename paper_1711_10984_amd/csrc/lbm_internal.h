@@ -33,6 +33,12 @@ constexpr int SEG_ROWS_DEFAULT = 64;
 // Heights tried by the autotuner (LBM_TUNE_NROWS of them).
 constexpr int32_t TUNE_ROWS[] = {16, 20, 24, 26, 28, 32, 36, 40, 44, 48, 54, 64, 80, 96, 128, 256};
 static_assert(sizeof(TUNE_ROWS) / sizeof(TUNE_ROWS[0]) == LBM_TUNE_NROWS, "tune list length");
+// Shorter strips of full width that the autotuner tries too where 16-row strips are fewer than SHORT_MOST, two
+// wavefronts per SIMD (with more of them, 16 rows are as fast: a batch of 32 lattices, 3968 strips, 85 us either way).
+// One launch, 16 rows or taller and shorter, us: 560 x 560 FP64 41.3 and 35.7, FP32 32.9 and 26.9; 1024 x 1024 FP64 60
+// and 47.5, FP32 39 and 31.5.
+constexpr int32_t SHORT_ROWS[] = {8, 10, 12, 14};
+constexpr int SHORT_MOST = 2048;
 // Tilings: 0 = split-kernel tiles, 1 = fused-kernel strips, 2 = the tiles of the tiled fused step.
 constexpr int TILING_SPLIT = 0;
 constexpr int TILING_FUSED = 1;
