@@ -579,7 +579,7 @@ int need_pinned(lbm_ctx* c, size_t bytes) {
   c->pinned = nullptr;
   c->pinned_bytes = 0;
   void* p = nullptr;
-  HIPCHK(hipHostMalloc(&p, bytes, hipHostMallocCoherent));
+  HIPCHK(hipHostMalloc(&p, bytes, hipHostMallocCoherent | hipHostMallocPortable));
   c->pinned = static_cast<char*>(p);
   c->pinned_bytes = bytes;
   return LBM_OK;
