@@ -1399,7 +1399,10 @@ int lbm_autotune(lbm_ctx* c, int32_t launches, int32_t both_paths, int32_t* rows
   // Trial launches read the current state and write only the inactive half of every ping-pong buffer
   // and the partials; the parity, the droplet table and the step counter are untouched.  Launches of
   // one candidate run back to back; two passes over the candidates (the first also warms clocks and
-  // caches), keeping each candidate's faster pass.
+  // caches), keeping each candidate's faster pass.  The second leaves out those that took more than 1.5 times the
+  // first pass's best, a third to two thirds of them: the first pass was at most 8 % slower than the second for any
+  // candidate (1024 x 1024 FP64 and FP32, 32 lattices in FP32).  Whole call, ms, both passes of all / without those:
+  // 106 / 72, 89 / 57, 88 / 67.
   auto trial = [&](int n) -> hipError_t {
     hipError_t e = hipSuccess;
     for (int rep = 0; rep < n && e == hipSuccess; ++rep)
@@ -1408,12 +1411,14 @@ int lbm_autotune(lbm_ctx* c, int32_t launches, int32_t both_paths, int32_t* rows
     return e;
   };
   for (int pass = 0; pass < 2 && rc == LBM_OK; ++pass) {
+    const double limit = 1.5 * *std::min_element(cand_ms.begin(), cand_ms.end());
     for (int pi = 0; pi < 2 && rc == LBM_OK; ++pi) {
       if (!both_paths && paths[pi] != start_path) continue;
       c->path = paths[pi];
       for (int wi = 0; wi < NW && rc == LBM_OK; ++wi)
         for (int k = 0; k < NR; ++k) {
           if (skip[k]) continue;
+          if (cand_ms[(pi * NW + wi) * NR + k] > limit && pass > 0) continue;
           if ((rc = apply_segments(c, TUNE_ROWS[k], TUNE_WIDTHS[wi])) != LBM_OK) break;
           hipError_t e = trial(1);
           (void)hipEventRecord(e0, c->stream);
