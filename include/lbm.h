@@ -264,7 +264,7 @@ int lbm_time_launches(lbm_ctx* ctx, int32_t launches, double* ms_out);
  *   drops:        device array of `ndrop` lbm_droplet, the current centres of mass r_CM (e.g. from
  *                 lbm_droplets), updated in place with the centres after the run.
  * The state at step `step` is read from f[0], phi[0], c[0]; after nsteps steps (Secs. 2.2-2.3 and the Sec. 4
- * centre update, the wave- or fused-path kernels of lbm_step at strip width 54) the state at step + nsteps is in index
+ * centre update, the wave-path kernels of lbm_step at strip width 54) the state at step + nsteps is in index
  * (nsteps mod 2) of each pair, and the other index holds the state one step earlier (nsteps >= 1).
  * The strip height is 40 for lattices below 256 x 256 nodes and goes by size and precision above (4 to 128).  Results
  * equal those of lbm_step on the same state, at that height bit for bit; at another height the sums of the centres

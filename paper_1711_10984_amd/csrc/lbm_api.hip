@@ -754,7 +754,6 @@ static __device__ __align__(256) unsigned char scratch[LBM_NOALLOC_SCRATCH_BYTES
 constexpr int NOALLOC_MAX_DEVICES = 64;
 constexpr int NOALLOC_ROWS_MIN = 4, NOALLOC_ROWS_MAX = 128;
 constexpr int NOALLOC_ROWS_FIT = 40;  // the height that decides whether a lattice fits the scratch array
-constexpr int NOALLOC_ROWS_FUSED = 64;
 constexpr int SIMDS = 1024;           // 256 compute units
 
 int noalloc_segments(int nx, int ny, int rows) { return ((nx + FUSED_TX - 1) / FUSED_TX) * ((ny + rows - 1) / rows); }
@@ -945,14 +944,7 @@ int lbm_step_noalloc(const lbm_config* cfg, void* stream, void* const f[2], void
     return noalloc_layout(n, (n + 7) / 8 * 8, ndrop);
   };
   d.seg_rows = noalloc_rows(cf.nx, cf.ny, cf.precision);
-  bool fused = false;
-  if (layout_of(d.seg_rows).total > LBM_NOALLOC_SCRATCH_BYTES) {
-    // Large lattices with many droplets, whose short strips' partials do not fit: k_step, which four wavefronts keep
-    // fast on tall strips (4096^2 with 64 droplets: FP32 425 us at 64 rows, k_wave 461 at 40; FP64 770 and 780)
-    fused = d.seg_rows < NOALLOC_ROWS_FUSED && cf.precision != LBM_FP16 &&
-            layout_of(NOALLOC_ROWS_FUSED).total <= LBM_NOALLOC_SCRATCH_BYTES;
-    d.seg_rows = fused ? NOALLOC_ROWS_FUSED : std::max(d.seg_rows, NOALLOC_ROWS_FIT);
-  }
+  if (layout_of(d.seg_rows).total > LBM_NOALLOC_SCRATCH_BYTES) d.seg_rows = std::max(d.seg_rows, NOALLOC_ROWS_FIT);
   d.tiles_x[TILING_FUSED] = (cf.nx + FUSED_TX - 1) / FUSED_TX;
   d.tiles_y[TILING_FUSED] = (cf.ny + d.seg_rows - 1) / d.seg_rows;
   // element offsets of the caller's buffers from f[0] (the pool base of the kernels); 256-byte alignment makes
@@ -994,10 +986,8 @@ int lbm_step_noalloc(const lbm_config* cfg, void* stream, void* const f[2], void
     const int parity = (int)(k & 1);
     hipError_t e = with_types(cf.precision, [&](auto t, auto p) {
       using T = decltype(t);
-      T* const buf = reinterpret_cast<T*>(const_cast<char*>(base));
-      if (fused)
-        return launch_step<T, decltype(p)>(st, parity, nslots, segs, di, buf, dd, part, mask, dstep, nullptr, -1);
-      return launch_wave<T, decltype(p)>(st, parity, nslots, segs, di, buf, dd, part, mask, dstep, nullptr, -1,
+      return launch_wave<T, decltype(p)>(st, parity, nslots, segs, di, reinterpret_cast<T*>(const_cast<char*>(base)), dd,
+                                         part, mask, dstep, nullptr, -1,
                                          cf.walls == LBM_WALLS_NONE && cf.advection == LBM_ADV_PAPER);
     });
     if (e == hipSuccess) e = launch_reduce(st, TILING_FUSED, ndrop, di, dd, nullptr, part, mask, dstep, 1);

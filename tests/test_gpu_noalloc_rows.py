@@ -9,7 +9,7 @@ import pytest
 
 from paper_1711_10984_amd import workloads as W
 
-MANY = 100  # droplets: the short strips' partials then exceed the scratch array, and k_step takes the lattice
+MANY = 100  # droplets: the short strips' partials then exceed the scratch array, and strips of 40 rows take the lattice
 
 pytestmark = pytest.mark.gpu
 WT = [4 / 9] + [1 / 9] * 4 + [1 / 36] * 4
