@@ -766,10 +766,12 @@ int noalloc_waves(int prec) { return prec == LBM_FP64 ? 2 : 3; }
 // iterations x time, for the wavefronts per SIMD that its segments make (an extra one up to the most that are
 // planned for, a further round of them beyond).  Times of an iteration with 1, 2 and 3 wavefronts per SIMD, in us,
 // from launches on 700^2 to 2048^2 lattices.  FP64 leaves a tenth of the slots free: 2048^2 takes 193 us with 1786
-// wavefronts (44 rows), 200 with 1976 (40 rows).  Lattices of several rounds are bound by memory, and there the
-// shortest strips are the best or within 4 % of it: their neighbours read the shared halo rows soon after one
-// another (4096^2 FP32 432 us at 16 rows, 461 at 40, 460 at 80; 4096^2 FP64 759, 780, 801; FP16 storage is bound by
-// arithmetic, and its rounds count throughout: 4096^2 315, 291 and, in two rounds of 54 rows, 287).
+// wavefronts (44 rows), 200 with 1976 (40 rows).  Lattices of several rounds are bound by memory.  In FP32 the shortest
+// strips are the best there: their neighbours read the shared halo rows soon after one another (4096^2 in back-to-back
+// launches 432 us at 16 rows, 461 at 40, 460 at 80; 10 steps with 8 droplets, first call on a new state / repeated: 4590 /
+// 4410 at 16 rows, 4800 / 4610 at 40).  In FP64 they gain only in a long row of launches (759, 780 and 801 us) and lose in
+// short calls (10 steps 8900 / 7900 at 16 rows, 8350 / 7830 at 40), so it stays at 40.  FP16 storage is bound by
+// arithmetic, and its rounds count throughout: 4096^2 315, 291 and, in two rounds of 54 rows, 287.
 // The centres' sums are rounded by strip: lattices below 256 x 256 nodes, whose sweeps leave the chip idle at any
 // height, keep the 40 rows at which lbm_step's centres are the same to the bit.
 int noalloc_rows(int nx, int ny, int prec) {
@@ -778,7 +780,8 @@ int noalloc_rows(int nx, int ny, int prec) {
   const int most = noalloc_waves(prec);
   const double per_round = (prec == LBM_FP64 ? 0.9 : 1.0) * SIMDS;
   constexpr int SHORT = 16;
-  if (prec != LBM_FP16 && noalloc_segments(nx, ny, SHORT) >= 4.5 * most * per_round) return SHORT;
+  if (prec != LBM_FP16 && noalloc_segments(nx, ny, SHORT) >= 4.5 * most * per_round)
+    return prec == LBM_FP32 ? SHORT : NOALLOC_ROWS_FIT;
   int best = NOALLOC_ROWS_FIT;
   double best_cost = 1e300;
   for (int h = NOALLOC_ROWS_MIN; h <= NOALLOC_ROWS_MAX; ++h) {

@@ -46,7 +46,7 @@ SIZES = [(255, 256, 0), (256, 256, 0), (271, 257, 1), (700, 333, 0), (1000, 1100
 
 
 @pytest.mark.parametrize("nx,ny,walls,prec,ndrop", [s + (p, 5) for s in SIZES for p in (0, 1, 2)] +
-                         [(34560, 208, 0, 0, 5), (34560, 208, 0, 0, MANY), (34560, 208, 0, 1, MANY)])
+                         [(34560, 208, 0, 0, 5), (34560, 208, 0, 0, MANY), (34560, 208, 0, 1, MANY), (57456, 208, 0, 1, 5)])
 def test_fields_do_not_depend_on_the_height(nx, ny, walls, prec, ndrop):
     from paper_1711_10984_amd import lbm
     rng = np.random.default_rng(nx + ny)
