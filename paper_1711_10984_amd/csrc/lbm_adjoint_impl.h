@@ -915,7 +915,7 @@ __global__ __launch_bounds__(ADJ_THREADS) void k_adj_total(const double* __restr
   __syncthreads();
   if (threadIdx.x != 0) return;
   for (int w = 1; w < ADJ_THREADS / 64; ++w) dd_add(s[0], red[w]);
-  *out = isfinite(s[0].hi) ? dd_value(s[0]) : s[0].hi;
+  *out = dd_value(s[0]);
 }
 
 template <typename T>

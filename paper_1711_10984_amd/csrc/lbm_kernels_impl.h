@@ -311,7 +311,8 @@ __device__ __forceinline__ void dd_add(Dd& s, const Dd& v) {
   dd_add(s, v.hi);
   s.lo += v.lo;
 }
-__device__ __forceinline__ double dd_value(const Dd& s) { return s.hi + s.lo; }
+// Where a sum overflows or meets a non-finite value, hi is what a plain sum gives and lo is undefined.
+__device__ __forceinline__ double dd_value(const Dd& s) { return isfinite(s.hi) ? s.hi + s.lo : s.hi; }
 // v of another lane by DPP (0 where the control has no source or masks the row).
 template <int CTRL, int ROWS>
 __device__ __forceinline__ double dpp_get(double v) {
@@ -1124,9 +1125,8 @@ __global__ __launch_bounds__(NTHREADS) void k_obs_final(const InstDev* __restric
     else
       for (int i = 0; i < 3; ++i) dd_add(s[i], s_sum[w][i]);
   }
-  // where a sum overflows or meets a non-finite value, hi is what a plain sum gives and lo is undefined
   double v[3];
-  for (int i = 0; i < 3; ++i) v[i] = isfinite(s[i].hi) ? dd_value(s[i]) : s[i].hi;
+  for (int i = 0; i < 3; ++i) v[i] = dd_value(s[i]);
   if (b < 6) {
     res[b] = v[0];
   } else {
