@@ -320,6 +320,54 @@ void set_segments(Layout& L, int seg_rows, int strip_w, const std::vector<DropDe
 }
 
 
+// Page-locked host memory for read-backs, in blocks of two sizes: a droplet table or observables, and two chunks of
+// fields.  A call takes a block of its own and gives it back, so that calls on one context from several threads do
+// not meet in it; up to READ_KEPT blocks of a size are kept for the next calls.
+// Read-backs of more than READ_CHUNK bytes go in chunks, through the two halves of a block: the host copies one chunk
+// out while the kernel fills the other half.
+constexpr size_t READ_CHUNK = 512u << 10;
+constexpr size_t READ_HEAD = 64;  // bytes before a chunk's values: its flag of non-finite ones
+constexpr int READ_SIZES = 2, READ_KEPT = 4;
+constexpr size_t READ_BLOCK[READ_SIZES] = {16u << 10, 2 * (READ_CHUNK + ALIGN)};
+static_assert(sizeof(DropDev) * MAXDROP <= READ_BLOCK[0] && sizeof(double) * (6 + 5 * MAXDROP) <= READ_BLOCK[0] &&
+              READ_HEAD <= ALIGN, "what the blocks hold");
+
+class ReadBlocks {
+ public:
+  ~ReadBlocks() {
+    for (int s = 0; s < READ_SIZES; ++s)
+      while (n_[s] > 0) (void)hipHostFree(kept_[s][--n_[s]]);
+  }
+  hipError_t take(int size, char** out) {
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      if (n_[size] > 0) {
+        *out = kept_[size][--n_[size]];
+        return hipSuccess;
+      }
+    }
+    void* p = nullptr;
+    const hipError_t e = hipHostMalloc(&p, READ_BLOCK[size], hipHostMallocCoherent | hipHostMallocPortable);
+    *out = static_cast<char*>(p);
+    return e;
+  }
+  void give(int size, char* p) {
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      if (n_[size] < READ_KEPT) {
+        kept_[size][n_[size]++] = p;
+        return;
+      }
+    }
+    (void)hipHostFree(p);
+  }
+
+ private:
+  std::mutex mu_;
+  char* kept_[READ_SIZES][READ_KEPT] = {};
+  int n_[READ_SIZES] = {};
+};
+
 }  // namespace
 
 struct lbm_ctx {
@@ -332,11 +380,7 @@ struct lbm_ctx {
   int graph_steps = 0;
   int path = LBM_PATH_FUSED;
   bool tile = false;  // the fused path takes its tiled kernel
-  // page-locked host memory that read-backs go through: allocated by the first of them, grown to what they need (at
-  // most 2 x READ_CHUNK and a little), freed with the context
-  char* pinned = nullptr;
-  size_t pinned_bytes = 0;
-  hipEvent_t read_ev[2] = {nullptr, nullptr};
+  ReadBlocks read;
   // graphs of graph_steps steps, by starting parity, and (2 and 3) of LONG_GRAPH times as many for tiled steps: the
   // last launch of a sequence and the start of the next graph take 8 us, as long as a step.  The long ones are captured
   // by the second call that could use them, so that a single call does not pay for them.
@@ -566,26 +610,60 @@ int run_diag(lbm_ctx* c, int inst) {
   return LBM_OK;
 }
 
-// Read-backs of more than READ_CHUNK bytes go in chunks, through the two halves of the page-locked memory: the host
-// copies one chunk out while the kernel fills the next.  Small chunks, because the memory is locked at 0.4 ms per MB by
-// a context's first read-back (2 MB chunks add 1.7 ms to it, and save 0.06 ms of a 256 x 256 read-back).
-constexpr size_t READ_CHUNK = 512u << 10;
-constexpr size_t READ_HEAD = 64;  // bytes before a chunk's values: its flag of non-finite ones
+// A call's block of page-locked memory, on the context's stream.
+class ReadBuf {
+ public:
+  explicit ReadBuf(lbm_ctx* c) : c_(c) {}
+  ReadBuf(const ReadBuf&) = delete;
+  ReadBuf& operator=(const ReadBuf&) = delete;
+  // A call that ends early leaves work on the stream that writes to the block: it is waited for.  If that fails, the
+  // block is not used again.
+  ~ReadBuf() {
+    if (!mem_ || (pending_ && hipStreamSynchronize(c_->stream) != hipSuccess)) return;
+    c_->read.give(size_, mem_);
+  }
+  int take(size_t bytes) {
+    size_ = bytes <= READ_BLOCK[0] ? 0 : 1;
+    HIPCHK(c_->read.take(size_, &mem_));
+    return LBM_OK;
+  }
+  // The block, for work that is about to be enqueued.
+  char* fill() {
+    pending_ = true;
+    return mem_;
+  }
+  // Waits for all work of the stream.
+  int wait() {
+    HIPCHK(hipStreamSynchronize(c_->stream));
+    pending_ = false;
+    return LBM_OK;
+  }
+  const char* data() const { return mem_; }
 
-int need_pinned(lbm_ctx* c, size_t bytes) {
-  if (bytes <= c->pinned_bytes) return LBM_OK;
-  bytes = align_up(bytes, 16384);  // a droplet table's worth at least
-  if (c->pinned) HIPCHK(hipHostFree(c->pinned));
-  c->pinned = nullptr;
-  c->pinned_bytes = 0;
-  void* p = nullptr;
-  HIPCHK(hipHostMalloc(&p, bytes, hipHostMallocCoherent | hipHostMallocPortable));
-  c->pinned = static_cast<char*>(p);
-  c->pinned_bytes = bytes;
-  return LBM_OK;
-}
+ private:
+  lbm_ctx* c_;
+  char* mem_ = nullptr;
+  int size_ = 0;
+  bool pending_ = false;
+};
 
-// Nodes of a chunk of a read-back of np planes, and the page-locked bytes that the read-back needs.
+// One event for each half of a block: the host waits for a chunk while the kernel of the next one is already on its
+// way (waiting for the stream between chunks takes 12 us more for each: 512 x 256 FP64, all fields).
+struct ReadEvents {
+  hipEvent_t e[2] = {nullptr, nullptr};
+  hipError_t create() {
+    hipError_t rc = hipSuccess;
+    for (hipEvent_t& v : e)
+      if (rc == hipSuccess) rc = hipEventCreateWithFlags(&v, hipEventDisableTiming);
+    return rc;
+  }
+  ~ReadEvents() {
+    for (hipEvent_t v : e)
+      if (v) (void)hipEventDestroy(v);
+  }
+};
+
+// Nodes of a chunk of a read-back of np planes, and the bytes of one with its head.
 int64_t read_chunk(int64_t nodes, int np) {
   const size_t node_bytes = sizeof(double) * np;
   return (size_t)nodes * node_bytes <= READ_CHUNK ? nodes : (int64_t)(READ_CHUNK / node_bytes);
@@ -593,7 +671,6 @@ int64_t read_chunk(int64_t nodes, int np) {
 size_t read_half(int64_t nodes, int np) {
   return align_up(READ_HEAD + (size_t)read_chunk(nodes, np) * sizeof(double) * np, ALIGN);
 }
-size_t read_bytes(int64_t nodes, int np) { return (read_chunk(nodes, np) < nodes ? 2 : 1) * read_half(nodes, np); }
 
 // np planes of `nodes` doubles to the caller's arrays dst, by launch(first, count, values, flag): it fills the planes'
 // nodes [first, first + count), one plane after another, and sets the flag where a value is not finite.
@@ -601,26 +678,27 @@ template <class F>
 int read_planes(lbm_ctx* c, int64_t nodes, int np, double* const* dst, bool& finite, F launch) {
   const int64_t per = read_chunk(nodes, np), chunks = (nodes + per - 1) / per;
   const size_t half = read_half(nodes, np);
-  const int rc = need_pinned(c, read_bytes(nodes, np));
+  ReadBuf buf(c);
+  ReadEvents ev;
+  int rc = buf.take((chunks > 1 ? 2 : 1) * half);
   if (rc != LBM_OK) return rc;
-  for (int k = 0; chunks > 1 && k < 2; ++k)
-    if (!c->read_ev[k]) HIPCHK(hipEventCreateWithFlags(&c->read_ev[k], hipEventDisableTiming));
+  if (chunks > 1) HIPCHK(ev.create());
   finite = true;
   for (int64_t k = 0; k <= chunks; ++k) {
     if (k < chunks) {
-      char* const h = c->pinned + (k & 1) * half;
+      char* const h = buf.fill() + (k & 1) * half;
       const int64_t first = k * per;
       *reinterpret_cast<uint32_t*>(h) = 0u;
       HIPCHK(launch(first, std::min(per, nodes - first), reinterpret_cast<double*>(h + READ_HEAD),
                     reinterpret_cast<uint32_t*>(h)));
-      if (chunks > 1) HIPCHK(hipEventRecord(c->read_ev[k & 1], c->stream));
+      if (chunks > 1) HIPCHK(hipEventRecord(ev.e[k & 1], c->stream));
     }
     if (k == 0) continue;
-    if (chunks > 1)
-      HIPCHK(hipEventSynchronize(c->read_ev[(k - 1) & 1]));
-    else
-      HIPCHK(hipStreamSynchronize(c->stream));
-    const char* const h = c->pinned + ((k - 1) & 1) * half;
+    if (k < chunks)
+      HIPCHK(hipEventSynchronize(ev.e[(k - 1) & 1]));
+    else if ((rc = buf.wait()) != LBM_OK)
+      return rc;
+    const char* const h = buf.data() + ((k - 1) & 1) * half;
     const int64_t first = (k - 1) * per, count = std::min(per, nodes - first);
     const double* v = reinterpret_cast<const double*>(h + READ_HEAD);
     for (int j = 0; j < np; ++j, v += count) memcpy(dst[j] + first, v, sizeof(double) * (size_t)count);
@@ -705,11 +783,12 @@ int read_drops(lbm_ctx* c, int inst, std::vector<DropDev>& out) {
   out.resize(d.ndrop);
   if (d.ndrop == 0) return LBM_OK;
   const size_t bytes = sizeof(DropDev) * d.ndrop;
-  const int rc = need_pinned(c, bytes);
+  ReadBuf buf(c);
+  int rc = buf.take(bytes);
   if (rc != LBM_OK) return rc;
-  HIPCHK(hipMemcpyAsync(c->pinned, c->d_drops() + d.drop_base, bytes, hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(hipStreamSynchronize(c->stream));
-  memcpy(out.data(), c->pinned, bytes);
+  HIPCHK(hipMemcpyAsync(buf.fill(), c->d_drops() + d.drop_base, bytes, hipMemcpyDeviceToHost, c->stream));
+  if ((rc = buf.wait()) != LBM_OK) return rc;
+  memcpy(out.data(), buf.data(), bytes);
   return LBM_OK;
 }
 
@@ -1194,8 +1273,8 @@ int lbm_observables(lbm_ctx* c, int32_t inst, lbm_obs* obs, double* drop_out) {
   if (rc != LBM_OK) return rc;
   if (!obs) return fail(LBM_E_INVAL, "obs must not be NULL");
   const int nd = c->L.inst[inst].ndrop;
-  if ((rc = need_pinned(c, sizeof(double) * (6 + 5 * (size_t)nd))) != LBM_OK) return rc;
-  const double* const r = reinterpret_cast<const double*>(c->pinned);
+  ReadBuf buf(c);
+  if ((rc = buf.take(sizeof(double) * (6 + 5 * (size_t)nd))) != LBM_OK) return rc;
   hipError_t e = with_types(c->L.prec, [&](auto t, auto p) {
     using T = decltype(t);
     return launch_obs<T, decltype(p)>(c->stream, c->parity, c->nlaunch(), c->d_tiles(), c->d_inst(),
@@ -1204,9 +1283,10 @@ int lbm_observables(lbm_ctx* c, int32_t inst, lbm_obs* obs, double* drop_out) {
   });
   if (e == hipSuccess)
     e = launch_obs_final(c->stream, c->d_inst(), inst, nd, c->d_drops(), c->d_obs(), c->L.obs_stride,
-                         reinterpret_cast<double*>(c->pinned));
+                         reinterpret_cast<double*>(buf.fill()));
   if (e != hipSuccess) return fail(LBM_E_HIP, std::string("observables launch: ") + hipGetErrorString(e));
-  HIPCHK(hipStreamSynchronize(c->stream));
+  if ((rc = buf.wait()) != LBM_OK) return rc;
+  const double* const r = reinterpret_cast<const double*>(buf.data());
   obs->step = c->step;
   obs->mass = r[0];
   obs->sum_phi = r[1];
@@ -1538,9 +1618,6 @@ int32_t lbm_get_path(const lbm_ctx* c) { return c ? c->path : -1; }
 void lbm_destroy(lbm_ctx* c) {
   if (!c) return;
   destroy_graphs(c);
-  if (c->pinned) (void)hipHostFree(c->pinned);
-  for (hipEvent_t e : c->read_ev)
-    if (e) (void)hipEventDestroy(e);
   delete c;
 }
 
@@ -1696,7 +1773,8 @@ int adj_backward(lbm_ctx* c, const AdjLayout& A, char* w, double* dA0, double* d
   const int64_t n0 = c->adj.n0, N = c->adj.nsteps, M = A.nodes;
   const int every = c->adj.every, drop = c->adj.drop, nd = d.ndrop;
   int rc;
-  if ((rc = need_pinned(c, read_bytes(A.nodes, 1))) != LBM_OK) return rc;  // what the gradient's read-back needs
+  ReadBuf buf(c);  // the seed's sum of phi, dA0
+  if ((rc = buf.take(2 * sizeof(double))) != LBM_OK) return rc;
   if ((rc = adj_save(c, A, w + A.off_final)) != LBM_OK) return rc;
   const int parity = c->parity;  // of the final state, which comes back at the end
   char* const segs = w + A.off_seg;
@@ -1724,7 +1802,6 @@ int adj_backward(lbm_ctx* c, const AdjLayout& A, char* w, double* dA0, double* d
   T* tmp = adj + 22 * M;
   double* const sw = reinterpret_cast<double*>(w + A.off_part);  // the seed's sum of phi
   double* const part = sw + 1;                                   // its partial sums, then per-block dA0 totals
-  double* const result = reinterpret_cast<double*>(c->pinned);  // that sum, dA0
   AdjModel m;
   m.nx = d.nx;
   m.ny = d.ny;
@@ -1805,12 +1882,13 @@ int adj_backward(lbm_ctx* c, const AdjLayout& A, char* w, double* dA0, double* d
       cur ^= 1;
     }
   }
+  double* const result = reinterpret_cast<double*>(buf.fill());
   HIPCHK(hipMemcpyAsync(result, sw, sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(launch_adjoint_total(c->stream, part, A.nparts, result + 1));
   // back to the state at the end of the forward pass
   c->parity = parity;
   if ((rc = adj_load(c, A, w + A.off_final, n0 + N, nullptr)) != LBM_OK) return rc;
-  HIPCHK(hipStreamSynchronize(c->stream));
+  if ((rc = buf.wait()) != LBM_OK) return rc;
   if (!(result[0] > 0.0)) return fail(LBM_E_STATE, "the droplet has no nodes with phi >= 0 at the end of the run");
   if (dA0) *dA0 = result[1];
   if (!dc0) return LBM_OK;
@@ -1843,10 +1921,10 @@ int lbm_adjoint_forward(lbm_ctx* c, void* ws, size_t bytes, int32_t drop, int64_
   if (bytes < A.total) return fail(LBM_E_NOMEM, "adjoint workspace too small (see lbm_adjoint_bytes)");
   char* w = static_cast<char*>(ws);
   const InstDev& d = c->L.inst[0];
-  if ((rc = need_pinned(c, read_bytes(A.nodes, 1))) != LBM_OK) return rc;  // what the gradient's read-back needs
-  volatile double* const at = reinterpret_cast<double*>(c->pinned);  // x of the droplet before and after
+  ReadBuf buf(c);  // x of the droplet before and after
+  if ((rc = buf.take(2 * sizeof(double))) != LBM_OK) return rc;
   auto read_x = [&](int i) {
-    return hipMemcpyAsync(c->pinned + i * sizeof(double), &(c->d_drops() + drop)->x, sizeof(double),
+    return hipMemcpyAsync(buf.fill() + i * sizeof(double), &(c->d_drops() + drop)->x, sizeof(double),
                           hipMemcpyDeviceToHost, c->stream);
   };
   HIPCHK(read_x(0));
@@ -1860,7 +1938,8 @@ int lbm_adjoint_forward(lbm_ctx* c, void* ws, size_t bytes, int32_t drop, int64_
     if ((rc = lbm_step(c, std::min<int64_t>(every, nsteps - k))) != LBM_OK) return rc;
   }
   HIPCHK(read_x(1));
-  HIPCHK(hipStreamSynchronize(c->stream));
+  if ((rc = buf.wait()) != LBM_OK) return rc;
+  const double* const at = reinterpret_cast<const double*>(buf.data());
   double dx = at[1] - at[0];
   if (dx >= 0.5 * d.nx) dx -= d.nx;
   if (dx < -0.5 * d.nx) dx += d.nx;
