@@ -21,10 +21,14 @@
  *   Batched contexts hold several independent lattices ("instances"); host arrays for
  *   a batch are the instances' arrays concatenated in instance order.
  *   Device memory belongs to the caller: the library carves all its buffers out of one
- *   caller-allocated workspace and never allocates or frees device memory itself
- *   (hipGraph objects and hipEvents are the only HIP objects it creates).  The HIP
+ *   caller-allocated workspace and never allocates or frees device memory itself.
+ *   The HIP objects it creates are hipGraph objects, hipEvents and the page-locked host
+ *   memory that read-backs go through (at most 1.1 MB for each call that runs at once;
+ *   4.2 MB of it are kept for the next calls, 1.1 MB once no context is left).  The HIP
  *   stream also belongs to the caller; all work is enqueued on it.  Host arrays belong
  *   to the caller and are only read or written during the call.
+ *   Calls that read a context (lbm_fields, lbm_observables, lbm_droplets) may run on several
+ *   threads at once; calls that change one (steps, settings, the reverse mode) may not.
  *   Every function returns LBM_OK (0) or a negative error code; nothing is thrown across
  *   the ABI.  lbm_last_error() returns a thread-local description of the last failure.
  *   lbm_step() does not synchronise; device-side problems (non-finite values, B(c) <= 0)

@@ -321,8 +321,11 @@ void set_segments(Layout& L, int seg_rows, int strip_w, const std::vector<DropDe
 
 
 // Page-locked host memory for read-backs, in blocks of two sizes: a droplet table or observables, and two chunks of
-// fields.  A call takes a block of its own and gives it back, so that calls on one context from several threads do
-// not meet in it; up to READ_KEPT blocks of a size are kept for the next calls.
+// fields.  A call takes a block of its own and gives it back, so that calls from several threads do not meet in it.
+// The blocks are the process's: a context's own would be locked by its first read-back and freed with it, which a
+// program that reads each context once never earns back (64 x 64, first lbm_droplets, lbm_fields and lbm_destroy of a
+// new context, us: 16, 62 and 1 with the process's blocks, 44, 350 and 260 with the context's).  Up to READ_KEPT blocks
+// of a size wait for the next calls, and one of each once no context is left.
 // Read-backs of more than READ_CHUNK bytes go in chunks, through the two halves of a block: the host copies one chunk
 // out while the kernel fills the other half.
 constexpr size_t READ_CHUNK = 512u << 10;
@@ -334,9 +337,24 @@ static_assert(sizeof(DropDev) * MAXDROP <= READ_BLOCK[0] && sizeof(double) * (6 
 
 class ReadBlocks {
  public:
-  ~ReadBlocks() {
-    for (int s = 0; s < READ_SIZES; ++s)
-      while (n_[s] > 0) (void)hipHostFree(kept_[s][--n_[s]]);
+  static ReadBlocks& get() {
+    static ReadBlocks* const all = new ReadBlocks;  // never destroyed: the runtime may be gone by then
+    return *all;
+  }
+  void add_context() {
+    std::lock_guard<std::mutex> lock(mu_);
+    ++contexts_;
+  }
+  void drop_context() {
+    char* spare[READ_SIZES * READ_KEPT];
+    int n = 0;
+    {
+      std::lock_guard<std::mutex> lock(mu_);
+      if (--contexts_ > 0) return;
+      for (int s = 0; s < READ_SIZES; ++s)
+        while (n_[s] > 1) spare[n++] = kept_[s][--n_[s]];
+    }
+    while (n > 0) (void)hipHostFree(spare[--n]);
   }
   hipError_t take(int size, char** out) {
     {
@@ -354,7 +372,7 @@ class ReadBlocks {
   void give(int size, char* p) {
     {
       std::lock_guard<std::mutex> lock(mu_);
-      if (n_[size] < READ_KEPT) {
+      if (n_[size] < (contexts_ > 0 ? READ_KEPT : 1)) {
         kept_[size][n_[size]++] = p;
         return;
       }
@@ -366,6 +384,7 @@ class ReadBlocks {
   std::mutex mu_;
   char* kept_[READ_SIZES][READ_KEPT] = {};
   int n_[READ_SIZES] = {};
+  int64_t contexts_ = 0;
 };
 
 }  // namespace
@@ -380,7 +399,6 @@ struct lbm_ctx {
   int graph_steps = 0;
   int path = LBM_PATH_FUSED;
   bool tile = false;  // the fused path takes its tiled kernel
-  ReadBlocks read;
   // graphs of graph_steps steps, by starting parity, and (2 and 3) of LONG_GRAPH times as many for tiled steps: the
   // last launch of a sequence and the start of the next graph take 8 us, as long as a step.  The long ones are captured
   // by the second call that could use them, so that a single call does not pay for them.
@@ -620,11 +638,11 @@ class ReadBuf {
   // block is not used again.
   ~ReadBuf() {
     if (!mem_ || (pending_ && hipStreamSynchronize(c_->stream) != hipSuccess)) return;
-    c_->read.give(size_, mem_);
+    ReadBlocks::get().give(size_, mem_);
   }
   int take(size_t bytes) {
     size_ = bytes <= READ_BLOCK[0] ? 0 : 1;
-    HIPCHK(c_->read.take(size_, &mem_));
+    HIPCHK(ReadBlocks::get().take(size_, &mem_));
     return LBM_OK;
   }
   // The block, for work that is about to be enqueued.
@@ -1179,6 +1197,7 @@ int lbm_init_batch(int32_t ninst, const lbm_config* cfgs, void* workspace, size_
                          c->d_part(), c->d_mask(), c->d_step(), 0));
   INIT_CHK(hipStreamSynchronize(c->stream));
 #undef INIT_CHK
+  ReadBlocks::get().add_context();
   *out = c;
   g_err.clear();
   return LBM_OK;
@@ -1619,6 +1638,7 @@ void lbm_destroy(lbm_ctx* c) {
   if (!c) return;
   destroy_graphs(c);
   delete c;
+  ReadBlocks::get().drop_context();
 }
 
 const char* lbm_last_error(void) { return g_err.c_str(); }
