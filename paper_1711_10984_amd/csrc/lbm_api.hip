@@ -1727,11 +1727,17 @@ AdjLayout adj_layout(const lbm_ctx* c, int64_t nsteps, int every) {
   A.off_fwd = off;
   off = align_up(off + sizeof(double) * ADJ_FWD_PLANES * (size_t)every * (size_t)A.nodes, ALIGN);
   A.off_adj = off;   off = align_up(off + c->L.elem * (size_t)(22 + ADJ_TMP_PLANES) * A.nodes, ALIGN);
-  A.off_part = off;  
+  A.off_part = off;
   off = align_up(off + sizeof(double) * (1 + (size_t)std::max(A.nparts, adj_blocks(d.nx, d.ny))), ALIGN);
   A.off_inst = off;  off = align_up(off + sizeof(InstDev) * (size_t)every, ALIGN);
-  A.total = off;
+  A.total = off + ALIGN;  // the caller's pointer need not be aligned, see adj_base
   return A;
+}
+
+// The first aligned byte of a workspace.  The recompute's descriptions count its planes in elements from the context's
+// pool, which needs a whole number of them between the two.
+char* adj_base(void* ws) {
+  return reinterpret_cast<char*>(align_up(reinterpret_cast<uintptr_t>(ws), ALIGN));
 }
 
 // Copy the state of the single lattice (current buffers, droplet table, step counter) to or from a whole
@@ -1939,7 +1945,7 @@ int lbm_adjoint_forward(lbm_ctx* c, void* ws, size_t bytes, int32_t drop, int64_
   if (!ws) return fail(LBM_E_INVAL, "adjoint workspace must not be NULL");
   const AdjLayout A = adj_layout(c, nsteps, every);
   if (bytes < A.total) return fail(LBM_E_NOMEM, "adjoint workspace too small (see lbm_adjoint_bytes)");
-  char* w = static_cast<char*>(ws);
+  char* w = adj_base(ws);
   const InstDev& d = c->L.inst[0];
   ReadBuf buf(c);  // x of the droplet before and after
   if ((rc = buf.take(2 * sizeof(double))) != LBM_OK) return rc;
@@ -1977,7 +1983,7 @@ int lbm_adjoint_backward(lbm_ctx* c, void* ws, size_t bytes, double* dJ_dA0, dou
   if (!ws) return fail(LBM_E_INVAL, "adjoint workspace must not be NULL");
   const AdjLayout A = adj_layout(c, c->adj.nsteps, c->adj.every);
   if (bytes < A.total) return fail(LBM_E_NOMEM, "adjoint workspace too small (see lbm_adjoint_bytes)");
-  char* w = static_cast<char*>(ws);
+  char* w = adj_base(ws);
   return c->L.prec == LBM_FP64 ? adj_backward<double>(c, A, w, dJ_dA0, dJ_dc0)
                                : adj_backward<float>(c, A, w, dJ_dA0, dJ_dc0);
 }
