@@ -293,7 +293,7 @@ def adjoint_measure(precision, nsteps=2000, every=100, repeats=2, n=256):
     w = W.c2_single_active(n=n)
     best_f, best_b = 1e300, 1e300
     for _ in range(repeats):
-        sim = lbm.Sim([w.param_dict()], [w.phi0], [w.c0], [w.drop_dicts()], precision=precision, graph_steps=20)
+        sim = lbm.Sim([w.param_dict()], [w.phi0], [w.c0], [w.drop_dicts()], precision=precision)
         rows, path, _ = sim.autotune(10, both_paths=True)
         width = sim.strip_width
         sim.sync()

@@ -149,8 +149,8 @@ int lbm_step(lbm_ctx* ctx, int64_t n);
  * one by one when 0.  Default: 20 on a non-default stream, 0 on the null stream.  The two graphs (one per
  * parity of the starting step) are captured by this call; changing the path, strip height or width drops
  * them, and the next lbm_step captures them again.  lbm_step replays whole graphs while at least
- * steps_per_graph steps remain and launches the rest one by one.  Small lattices (the tiled step) have graphs of five
- * times as many steps too, for calls that long: captured here as well, by default with the second such call. */
+ * steps_per_graph steps remain and launches the rest one by one.  Until this call, small lattices (the tiled step)
+ * have graphs of 100 steps too, for calls that long: captured by the second such call. */
 int lbm_set_graph(lbm_ctx* ctx, int32_t steps_per_graph);
 
 /* Wait for the context's stream. */

@@ -401,10 +401,11 @@ struct lbm_ctx {
   bool tile = false;  // the fused path takes its tiled kernel
   // graphs of graph_steps steps, by starting parity, and (2 and 3) of LONG_GRAPH times as many for tiled steps: the
   // last launch of a sequence and the start of the next graph take 8 us, as long as a step.  The long ones are captured
-  // by the second call that could use them, so that a single call does not pay for them.
+  // by the second call that could use them, so that a single call does not pay for them; a caller who sets the size of
+  // the graphs gets graphs of that size alone, captured then.
   hipGraphExec_t exec[4] = {nullptr, nullptr, nullptr, nullptr};
   hipGraph_t graph[4] = {nullptr, nullptr, nullptr, nullptr};
-  bool long_asked = false;
+  bool long_graphs = true, long_asked = false;
   // the last recorded forward pass of lbm_adjoint_forward (see lbm_adjoint_backward)
   struct {
     bool valid = false;
@@ -1217,8 +1218,8 @@ int lbm_set_graph(lbm_ctx* c, int32_t steps_per_graph) {
   destroy_graphs(c);
   c->graph_steps = steps_per_graph;
   // capture the graphs now (one per starting parity), so that no later lbm_step pays for a capture
-  c->long_asked = c->long_asked || (c->tiled() && steps_per_graph > 0);
-  for (int p = 0; p < (c->tiled() ? 4 : 2) && steps_per_graph > 0; ++p) {
+  c->long_graphs = false;
+  for (int p = 0; p < 2 && steps_per_graph > 0; ++p) {
     const int rc = build_graph(c, p);
     if (rc != LBM_OK) return rc;
   }
@@ -1232,8 +1233,8 @@ int lbm_step(lbm_ctx* c, int64_t n) {
   int64_t left = n;
   if (c->graph_steps > 0) {
     const int64_t longer = (int64_t)c->graph_steps * LONG_GRAPH;
-    const bool use_long = c->tiled() && left >= longer && c->long_asked;
-    c->long_asked = c->long_asked || (c->tiled() && left >= longer);
+    const bool could = c->tiled() && c->long_graphs && left >= longer, use_long = could && c->long_asked;
+    c->long_asked = c->long_asked || could;
     while (left >= c->graph_steps) {
       Range replay("lbm_step graph replay");
       const bool lg = use_long && left >= longer;

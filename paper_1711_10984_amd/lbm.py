@@ -491,7 +491,7 @@ def _make_com_displacement():
         def forward(ctx, A0, psi0, params, phi0, drops, nsteps, every, drop, precision, path):
             p = dict(params, A0=float(A0.detach().cpu()))
             c0 = np.ascontiguousarray(psi0.detach().cpu().numpy(), dtype=np.float64)
-            sim = Sim([p], [phi0], [c0], [drops], precision=precision, graph_steps=20,
+            sim = Sim([p], [phi0], [c0], [drops], precision=precision,
                       path=LBM_PATH_FUSED if path < 0 else path)
             if path < 0:
                 sim.autotune(10, both_paths=True)
