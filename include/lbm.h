@@ -142,7 +142,9 @@ int lbm_init(const lbm_config* cfg, void* workspace, size_t workspace_bytes, voi
              const lbm_droplet* drops, int64_t step, lbm_ctx** out);
 
 /* Advance every instance by n >= 0 timesteps n -> n+1 (Sec. 2.2-2.3, Eqs. 10-19, then the
- * centre-of-mass update of Sec. 4).  Asynchronous on the context's stream. */
+ * centre-of-mass update of Sec. 4).  Asynchronous on the context's stream.  Where a launch fails (LBM_E_HIP), the
+ * steps enqueued whole before it count (lbm_get_step); if a context's state cannot be kept whole, calls that need it
+ * return LBM_E_STATE from then on. */
 int lbm_step(lbm_ctx* ctx, int64_t n);
 
 /* Replay the timestep through hipGraphs of `steps_per_graph` steps (even, >= 2), or launch kernels

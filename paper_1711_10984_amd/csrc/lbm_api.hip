@@ -396,6 +396,7 @@ struct lbm_ctx {
   hipStream_t stream = nullptr;
   int parity = 0;
   int64_t step = 0;
+  bool lost = false;  // a failed launch left fields and droplet table of different steps
   int graph_steps = 0;
   int path = LBM_PATH_FUSED;
   bool tile = false;  // the fused path takes its tiled kernel
@@ -519,20 +520,28 @@ hipError_t enqueue_reduce(lbm_ctx* c, int64_t n, bool write = true) {
                        c->d_drops(), nullptr, c->d_part(), c->d_mask(), c->d_step(), write ? 1 : -1);
 }
 
-// n steps from the given parity.
+// n steps from the given parity.  If a launch fails, `done` tells how many steps were enqueued whole: they stand, with
+// the table and the counter, and the state before the failed one is intact.
 template <typename T, typename P>
-hipError_t enqueue_steps(lbm_ctx* c, int parity, int64_t n) {
+hipError_t enqueue_steps(lbm_ctx* c, int parity, int64_t n, int64_t& done) {
   hipError_t e = hipSuccess;
-  for (int64_t k = 0; k < n && e == hipSuccess; ++k, parity ^= 1) {
-    e = c->path == LBM_PATH_SPLIT ? launch_split<T, P>(c, parity) : launch_sweep<T, P>(c, parity, nullptr, -1, k);
+  for (done = 0; done < n; ++done, parity ^= 1) {
+    e = c->path == LBM_PATH_SPLIT ? launch_split<T, P>(c, parity) : launch_sweep<T, P>(c, parity, nullptr, -1, done);
     if (e == hipSuccess && !c->tiled()) e = enqueue_reduce(c, 1);
+    if (e != hipSuccess) break;
   }
-  if (e == hipSuccess && c->tiled() && n > 0) e = enqueue_reduce(c, n);
-  return e;
+  if (!c->tiled() || done == 0) return e;
+  const hipError_t f = enqueue_reduce(c, done);
+  if (f == hipSuccess) return e;
+  // without it the table and the counter belong to the sequence's start, whose fields the second step overwrote
+  c->lost = c->lost || done > 1;
+  done = 0;
+  return e == hipSuccess ? f : e;
 }
 
-hipError_t enqueue_steps_any(lbm_ctx* c, int parity, int64_t n) {
-  return with_types(c->L.prec, [&](auto t, auto p) { return enqueue_steps<decltype(t), decltype(p)>(c, parity, n); });
+hipError_t enqueue_steps_any(lbm_ctx* c, int parity, int64_t n, int64_t& done) {
+  return with_types(c->L.prec,
+                    [&](auto t, auto p) { return enqueue_steps<decltype(t), decltype(p)>(c, parity, n, done); });
 }
 
 constexpr int LONG_GRAPH = 5;
@@ -548,7 +557,10 @@ void destroy_graphs(lbm_ctx* c) {
 
 int build_graph(lbm_ctx* c, int which) {
   HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed));
-  const hipError_t err = enqueue_steps_any(c, which & 1, (int64_t)c->graph_steps * (which < 2 ? 1 : LONG_GRAPH));
+  int64_t done;  // nothing runs yet: a failure here leaves the state as it is
+  const bool lost = c->lost;
+  const hipError_t err = enqueue_steps_any(c, which & 1, (int64_t)c->graph_steps * (which < 2 ? 1 : LONG_GRAPH), done);
+  c->lost = lost;
   hipGraph_t g = nullptr;
   hipError_t e2 = hipStreamEndCapture(c->stream, &g);
   if (err != hipSuccess) {
@@ -612,10 +624,12 @@ int upload_instance(lbm_ctx* c, int i, const double* phi0, const double* c0, con
   return LBM_OK;
 }
 
+int fail_lost() { return fail(LBM_E_STATE, "a failed launch left the context's state incomplete"); }
+
 int check_inst(lbm_ctx* c, int32_t inst) {
   if (!c) return fail(LBM_E_INVAL, "null context");
   if (inst < 0 || inst >= (int)c->L.inst.size()) return fail(LBM_E_INVAL, "instance index out of range");
-  return LBM_OK;
+  return c->lost ? fail_lost() : LBM_OK;
 }
 
 // n, u planes of an instance from the current state (Eq. 11 with the force of Eq. 14).
@@ -1229,6 +1243,7 @@ int lbm_set_graph(lbm_ctx* c, int32_t steps_per_graph) {
 int lbm_step(lbm_ctx* c, int64_t n) {
   if (!c) return fail(LBM_E_INVAL, "null context");
   if (n < 0) return fail(LBM_E_INVAL, "n must be >= 0");
+  if (c->lost) return fail_lost();
   Range range("lbm_step");
   int64_t left = n;
   if (c->graph_steps > 0) {
@@ -1248,10 +1263,11 @@ int lbm_step(lbm_ctx* c, int64_t n) {
       c->step += lg ? longer : c->graph_steps;
     }
   }
-  const hipError_t e = enqueue_steps_any(c, c->parity, left);
+  int64_t done;
+  const hipError_t e = enqueue_steps_any(c, c->parity, left, done);
+  c->parity ^= (int)(done & 1);
+  c->step += done;
   if (e != hipSuccess) return fail(LBM_E_HIP, std::string("timestep launch: ") + hipGetErrorString(e));
-  c->parity ^= (int)(left & 1);
-  c->step += left;
   return LBM_OK;
 }
 

@@ -22,6 +22,7 @@ static struct {
 static int nkernels;
 static long launches, fail_first = -1, fail_count, host_allocs, host_live;
 static dim last_grid;
+static int last_int;
 
 /* ---- for the tests */
 void stub_reset(void) {
@@ -41,6 +42,8 @@ long stub_launched(const char* part) {
   return n;
 }
 unsigned stub_last_grid(void) { return last_grid.x; }
+/* first argument of the last launch, where that is an int */
+int stub_last_int(void) { return last_int; }
 long stub_host_allocs(void) { return host_allocs; }
 long stub_host_live(void) { return host_live; }
 
@@ -76,11 +79,12 @@ err __hipPopCallConfiguration(dim* grid, dim* block, size_t* shared, void** stre
   return OK;
 }
 err hipLaunchKernel(const void* fn, dim grid, dim block, void** args, size_t shared, void* stream) {
-  (void)block, (void)args, (void)shared, (void)stream;
+  (void)block, (void)shared, (void)stream;
   pthread_mutex_lock(&mu);
   const long at = launches++;
   const int bad = fail_first >= 0 && at >= fail_first && at < fail_first + fail_count;
   last_grid = grid;
+  last_int = *(const int*)args[0];
   for (int i = 0; i < nkernels && !bad; ++i)
     if (kernels[i].fn == fn) ++kernels[i].count;
   pthread_mutex_unlock(&mu);
