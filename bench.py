@@ -170,6 +170,8 @@ def measure(workloads, precision, steps, warmup, graph_steps, label, prof_steps,
     # device time per launch of each kernel: back-to-back launches replayed from a graph (state unchanged)
     device_ms = sim.time_launches(prof_steps)
     per_kernel = sim.time_kernels(prof_steps)  # hipEvents around each eager launch (gaps included)
+    # what ran: tiles and strips below the heights that can be set have no height and name of the path's own
+    running = {"kernel": sim.running_kernel, "rows": sim.running_rows}
     sim.close()
     mlups = nodes * steps / (ms * 1e-3) / 1e6
     dom = max((k for k in device_ms if k in VALUES_PER_NODE), key=lambda k: device_ms[k])
@@ -183,16 +185,17 @@ def measure(workloads, precision, steps, warmup, graph_steps, label, prof_steps,
     step_bytes = alg_bytes_per_node("step", precision) * nodes
     step_gbs = step_bytes / (ms * 1e-3 / steps) / 1e9
     prec = PREC_NAMES[precision]
-    traffic = measured_traffic(dom, label, prec, strip_w, seg_rows)
-    note(f"{label} {prec}: {mlups:.0f} MLUPS, {PATH_NAMES[path]} kernel, height {seg_rows}")
+    ran = running["kernel"] if dom in ("k_step", "k_wave") else dom
+    traffic = measured_traffic(ran, label, prec, strip_w, running["rows"] or None)
+    note(f"{label} {prec}: {mlups:.0f} MLUPS, {ran} kernel, height {running['rows'] or None}")
     return {
         "mlups": mlups, "ms_per_step": ms / steps, "wall_s": wall, "nodes": nodes, "precision": prec,
         "median_of_5": {"ms_per_step": ms / steps, "mlups": mlups, "ms_per_step_each": [m / steps for m in more],
                         "first_timing_ms_per_step": first_ms / steps},
         "graph": {"steps_per_graph": gsize, "graph_replayed_steps": steps - steps % gsize if gsize else 0},
         "kernel_ms": per_kernel, "device_ms_per_launch": device_ms, "seg_rows": seg_rows, "strip_width": strip_w,
-        "autotune_ms": tune_ms, "path": PATH_NAMES[path],
-        "roofline": {"bound": "hbm", "kernel": dom, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
+        "autotune_ms": tune_ms, "path": PATH_NAMES[path], "running": running,
+        "roofline": {"bound": "hbm", "kernel": ran, "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "alg_bytes_per_launch": alg_bytes, "avg_launch_ms": dom_ms, "avg_launch_from": dom_from},
         "step_roofline": {"alg_bytes_per_step": step_bytes, "achieved": round(step_gbs, 1),
@@ -294,8 +297,8 @@ def adjoint_measure(precision, nsteps=2000, every=100, repeats=2, n=256):
     best_f, best_b = 1e300, 1e300
     for _ in range(repeats):
         sim = lbm.Sim([w.param_dict()], [w.phi0], [w.c0], [w.drop_dicts()], precision=precision)
-        rows, path, _ = sim.autotune(10, both_paths=True)
-        width = sim.strip_width
+        _, path, _ = sim.autotune(10, both_paths=True)
+        width, kernel, rows = sim.strip_width, sim.running_kernel, sim.running_rows
         sim.sync()
         t0 = time.perf_counter()
         sim.adjoint_forward(0, nsteps, every)
@@ -306,8 +309,8 @@ def adjoint_measure(precision, nsteps=2000, every=100, repeats=2, n=256):
         best_f, best_b = min(best_f, t1 - t0), min(best_b, t2 - t1)
     note(f"reverse mode {PREC_NAMES[precision]}: backward {best_b / nsteps * 1e3:.3f} ms/step")
     return {"workload": f"{w.name}, {nsteps} steps, checkpoint every {every}", "nodes": w.nodes,
-            "path": PATH_NAMES[path], "seg_rows": rows if path != 1 else None,
-            "strip_width": width if path != 1 else None,
+            "path": PATH_NAMES[path], "kernel": kernel, "seg_rows": rows or None,
+            "strip_width": width if rows else None,
             "forward_ms_per_step": round(best_f / nsteps * 1e3, 5),
             "backward_ms_per_step": round(best_b / nsteps * 1e3, 5),
             "backward_mlups": round(w.nodes * nsteps / best_b / 1e6, 1),
@@ -544,14 +547,15 @@ def main():
         "kernel_ms": main_res["kernel_ms"],
         "device_ms_per_launch": main_res["device_ms_per_launch"],
         "autotune": {"seg_rows": main_res["seg_rows"], "strip_width": main_res["strip_width"],
-                     "path": main_res["path"],
+                     "path": main_res["path"], "running": main_res["running"],
                      "ms_per_launch": main_res["autotune_ms"]},
         "variants": {k: {"mlups": round(v["mlups"], 1), "ms_per_step": round(v["ms_per_step"], 5),
                          "nodes": v["nodes"], "precision": v["precision"], "gain_over_fp64": v["gain_over_fp64"],
                          "roofline": v["roofline"], "step_roofline": v["step_roofline"],
                          "kernel_ms": v["kernel_ms"], "device_ms_per_launch": v["device_ms_per_launch"],
                          "median_of_5": v["median_of_5"], "graph": v["graph"],
-                         "seg_rows": v["seg_rows"], "strip_width": v["strip_width"], "path": v["path"]}
+                         "seg_rows": v["seg_rows"], "strip_width": v["strip_width"], "path": v["path"],
+                         "running": v["running"]}
                      for k, v in variants.items()},
         "kernel_source_hash": kernel_source_hash(),
     }

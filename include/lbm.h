@@ -226,7 +226,7 @@ const int32_t* lbm_tune_widths(void);
  * lattices by tiles, that is tried too, without an entry in ms_out; if it is the fastest, LBM_PATH_FUSED is set with
  * the best strips' height and width.  Where it cannot and the strips are few, shorter ones than LBM_SEG_ROWS_MIN are
  * tried as well; if they are the fastest they are used, until a height or width is set, and the height returned is the
- * best of the list.
+ * best of the list (lbm_running_rows tells theirs).
  * The trial launches read the current state and write only scratch (the inactive halves of the ping-pong
  * buffers, the velocity planes and the centre-of-mass partials): the state, the droplet table and the step
  * counter are unchanged.  Called on the split path with both_paths == 0, nothing is tried.
@@ -237,15 +237,14 @@ int lbm_autotune(lbm_ctx* ctx, int32_t launches, int32_t both_paths, int32_t* ro
                  double* ms_out);
 
 /* Average device time per launch (ms) of each kernel of the timestep over n eagerly launched steps,
- * measured with hipEvents on the context's stream.  Fused path: ms_out = {k_step, k_reduce, 0};
- * wave path: {k_wave, k_reduce, 0}; split path: {k_lb, k_fd, k_reduce}.  Advances the state by n steps.  Synchronous. */
+ * measured with hipEvents on the context's stream.  Fused path: ms_out = {k_step, k_reduce, 0}, on tiles
+ * {k_tile, k_tile_final, 0}; wave path: {k_wave, k_reduce, 0}; split path: {k_lb, k_fd, k_reduce}.  Advances the state by n steps.  Synchronous. */
 int lbm_time_kernels(lbm_ctx* ctx, int64_t n, double* ms_out);
 
 /* Device time per launch (ms) of the timestep's main kernels, without the gaps that events or host launches
  * between kernels add: `launches` back-to-back launches of each kernel, captured in a hipGraph, replayed once to
  * warm up and once between two hipEvents on the context's stream (non-default; LBM_E_STATE otherwise), total
- * time / launches.  Fused path: ms_out = {k_step, k_reduce, 0}; wave path: {k_wave, k_reduce, 0}; split path:
- * {k_lb, k_fd, k_reduce}.  Like the autotuner's trials, the launches read the current state and write only
+ * time / launches.  ms_out as lbm_time_kernels has it.  Like the autotuner's trials, the launches read the current state and write only
  * scratch (the inactive halves of the ping-pong buffers, the velocity planes and the centre-of-mass partials;
  * k_reduce runs in a mode that computes the droplet sums and writes nothing): the state, the droplet table and
  * the step counter are unchanged.  Synchronous. */
@@ -303,8 +302,15 @@ int lbm_adjoint_forward(lbm_ctx* ctx, void* ws, size_t bytes, int32_t drop, int6
  * The context is left at n0 + nsteps.  May be called again.  Synchronous. */
 int lbm_adjoint_backward(lbm_ctx* ctx, void* ws, size_t bytes, double* dJ_dA0, double* dJ_dc0);
 
-/* Name of kernel `which` (0..2) of lbm_time_kernels for a path (static string, "" if none). */
+/* Name of kernel `which` (0..2) of lbm_time_kernels for a path (static string, "" if none); the fused path's are those
+ * of its strips. */
 const char* lbm_kernel_name(int32_t path, int32_t which);
+
+/* What the context's next step runs: the name of kernel `which` (0..2) of lbm_time_kernels and lbm_time_launches
+ * ("k_tile" and "k_tile_final" where the fused path takes tiles, else as lbm_kernel_name), and the rows of the strips
+ * that it sweeps (0 on tiles and on the split path), also where the autotuner chose strips below LBM_SEG_ROWS_MIN. */
+const char* lbm_running_kernel(const lbm_ctx* ctx, int32_t which);
+int32_t lbm_running_rows(const lbm_ctx* ctx);
 
 /* Release the context (graphs, events, host bookkeeping).  The workspace is not freed. */
 void lbm_destroy(lbm_ctx* ctx);

@@ -1658,6 +1658,16 @@ void lbm_destroy(lbm_ctx* c) {
   ReadBlocks::get().drop_context();
 }
 
+const char* lbm_running_kernel(const lbm_ctx* c, int32_t which) {
+  if (!c) return "";
+  if (c->tiled()) return which == 0 ? "k_tile" : which == 1 ? "k_tile_final" : "";
+  return lbm_kernel_name(c->path, which);
+}
+
+int32_t lbm_running_rows(const lbm_ctx* c) {
+  return !c ? -1 : c->path == LBM_PATH_SPLIT || c->tiled() ? 0 : c->L.inst[0].seg_rows;
+}
+
 const char* lbm_last_error(void) { return g_err.c_str(); }
 
 }  // extern "C"

@@ -32,7 +32,7 @@ EXPORTED = ["lbm_workspace_bytes", "lbm_init_batch", "lbm_init", "lbm_step", "lb
             "lbm_time_kernels", "lbm_time_launches", "lbm_kernel_name", "lbm_set_path", "lbm_get_path", "lbm_set_seg_rows",
             "lbm_get_seg_rows", "lbm_set_strip_width", "lbm_get_strip_width", "lbm_tune_rows", "lbm_tune_widths",
             "lbm_autotune", "lbm_step_noalloc", "lbm_adjoint_bytes", "lbm_adjoint_forward",
-            "lbm_adjoint_backward", "lbm_destroy", "lbm_last_error"]
+            "lbm_adjoint_backward", "lbm_running_kernel", "lbm_running_rows", "lbm_destroy", "lbm_last_error"]
 LBM_SEG_ROWS_MIN, LBM_SEG_ROWS_MAX, LBM_TUNE_NROWS = 16, 4096, 16
 LBM_STRIP_W_MIN, LBM_STRIP_W_MAX, LBM_TUNE_NWIDTHS = 32, 54, 1
 LBM_NOALLOC_SCRATCH_BYTES = 16 << 20
@@ -101,6 +101,10 @@ def load_library(path: Optional[str] = None):
     lib.lbm_time_launches.argtypes = [vp, C.c_int32, dp]
     lib.lbm_kernel_name.argtypes = [C.c_int32, C.c_int32]
     lib.lbm_kernel_name.restype = C.c_char_p
+    lib.lbm_running_kernel.argtypes = [vp, C.c_int32]
+    lib.lbm_running_kernel.restype = C.c_char_p
+    lib.lbm_running_rows.argtypes = [vp]
+    lib.lbm_running_rows.restype = C.c_int32
     lib.lbm_set_path.argtypes = [vp, C.c_int32]
     lib.lbm_get_path.argtypes = [vp]
     lib.lbm_get_path.restype = C.c_int32
@@ -255,6 +259,14 @@ def lbm_adjoint_backward(ctx: int, ws: int, nbytes: int, shape):
 
 def lbm_kernel_name(path: int, which: int) -> str:
     return load_library().lbm_kernel_name(path, which).decode()
+
+
+def lbm_running_kernel(ctx: int, which: int) -> str:
+    return load_library().lbm_running_kernel(C.c_void_p(ctx), int(which)).decode()
+
+
+def lbm_running_rows(ctx: int) -> int:
+    return int(load_library().lbm_running_rows(C.c_void_p(ctx)))
 
 
 def lbm_set_path(ctx: int, path: int) -> None:
@@ -435,6 +447,16 @@ class Sim:
 
     def set_seg_rows(self, rows: int) -> None:
         lbm_set_seg_rows(self.ctx, rows)
+
+    @property
+    def running_kernel(self) -> str:
+        """The main kernel of the next step (on tiles and strips its only one but for the centres of mass)."""
+        return lbm_running_kernel(self.ctx, 0)
+
+    @property
+    def running_rows(self) -> int:
+        """Rows of the strips that the next step sweeps (0 on tiles and on the split path)."""
+        return lbm_running_rows(self.ctx)
 
     @property
     def strip_width(self) -> int:

@@ -22,6 +22,7 @@ static struct {
 static int nkernels;
 static long launches, fail_first = -1, fail_count, host_allocs, host_live;
 static dim last_grid;
+static unsigned fast_grid;
 static int last_int;
 
 /* ---- for the tests */
@@ -42,6 +43,8 @@ long stub_launched(const char* part) {
   return n;
 }
 unsigned stub_last_grid(void) { return last_grid.x; }
+/* events say that time passes ten times as fast after a launch of so many workgroups */
+void stub_fast_grid(unsigned n) { fast_grid = n; }
 /* first argument of the last launch, where that is an int */
 int stub_last_int(void) { return last_int; }
 long stub_host_allocs(void) { return host_allocs; }
@@ -196,7 +199,7 @@ err hipEventSynchronize(void* e) {
 }
 err hipEventElapsedTime(float* ms, void* a, void* b) {
   (void)a, (void)b;
-  *ms = 1.0f;
+  *ms = fast_grid && last_grid.x == fast_grid ? 0.1f : 1.0f;
   return OK;
 }
 int roctxRangePushA(const char* s) {
