@@ -211,6 +211,10 @@ int32_t lbm_get_seg_rows(const lbm_ctx* ctx);
 int lbm_set_strip_width(lbm_ctx* ctx, int32_t width);
 int32_t lbm_get_strip_width(const lbm_ctx* ctx);
 
+/* Test hook: strips of `rows` rows and the widest width, as the autotuner may choose them below LBM_SEG_ROWS_MIN (from 8
+ * rows; LBM_E_INVAL below).  lbm_get_seg_rows keeps its value.  Synchronous. */
+int lbm_debug_strips(lbm_ctx* ctx, int32_t rows);
+
 /* The LBM_TUNE_NROWS segment heights tried by lbm_autotune, ascending (static array). */
 #define LBM_TUNE_NROWS 16
 const int32_t* lbm_tune_rows(void);

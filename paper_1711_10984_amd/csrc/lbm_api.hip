@@ -1464,6 +1464,15 @@ int lbm_set_strip_width(lbm_ctx* c, int32_t width) {
   return rc;
 }
 
+int lbm_debug_strips(lbm_ctx* c, int32_t rows) {
+  if (!c) return fail(LBM_E_INVAL, "null context");
+  if (rows < SHORT_ROWS[0] || rows > SEG_ROWS_MAX)
+    return fail(LBM_E_INVAL, "strips of " + std::to_string(SHORT_ROWS[0]) + " to " + std::to_string(SEG_ROWS_MAX) + " rows");
+  const int rc = apply_segments(c, c->L.seg_rows, FUSED_TX, rows);
+  if (rc == LBM_OK) c->tile = false;
+  return rc;
+}
+
 int32_t lbm_get_strip_width(const lbm_ctx* c) { return c ? c->L.strip_w : -1; }
 
 const int32_t* lbm_tune_widths(void) { return TUNE_WIDTHS; }

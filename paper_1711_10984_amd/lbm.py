@@ -32,7 +32,8 @@ EXPORTED = ["lbm_workspace_bytes", "lbm_init_batch", "lbm_init", "lbm_step", "lb
             "lbm_time_kernels", "lbm_time_launches", "lbm_kernel_name", "lbm_set_path", "lbm_get_path", "lbm_set_seg_rows",
             "lbm_get_seg_rows", "lbm_set_strip_width", "lbm_get_strip_width", "lbm_tune_rows", "lbm_tune_widths",
             "lbm_autotune", "lbm_step_noalloc", "lbm_adjoint_bytes", "lbm_adjoint_forward",
-            "lbm_adjoint_backward", "lbm_running_kernel", "lbm_running_rows", "lbm_destroy", "lbm_last_error"]
+            "lbm_adjoint_backward", "lbm_running_kernel", "lbm_running_rows",
+            "lbm_debug_strips", "lbm_destroy", "lbm_last_error"]
 LBM_SEG_ROWS_MIN, LBM_SEG_ROWS_MAX, LBM_TUNE_NROWS = 16, 4096, 16
 LBM_STRIP_W_MIN, LBM_STRIP_W_MAX, LBM_TUNE_NWIDTHS = 32, 54, 1
 LBM_NOALLOC_SCRATCH_BYTES = 16 << 20
@@ -101,6 +102,7 @@ def load_library(path: Optional[str] = None):
     lib.lbm_time_launches.argtypes = [vp, C.c_int32, dp]
     lib.lbm_kernel_name.argtypes = [C.c_int32, C.c_int32]
     lib.lbm_kernel_name.restype = C.c_char_p
+    lib.lbm_debug_strips.argtypes = [vp, C.c_int32]
     lib.lbm_running_kernel.argtypes = [vp, C.c_int32]
     lib.lbm_running_kernel.restype = C.c_char_p
     lib.lbm_running_rows.argtypes = [vp]
@@ -283,6 +285,10 @@ def lbm_set_seg_rows(ctx: int, rows: int) -> None:
 
 def lbm_get_seg_rows(ctx: int) -> int:
     return int(load_library().lbm_get_seg_rows(C.c_void_p(ctx)))
+
+
+def lbm_debug_strips(ctx: int, rows: int) -> None:
+    _check(load_library().lbm_debug_strips(C.c_void_p(ctx), int(rows)))
 
 
 def lbm_set_strip_width(ctx: int, width: int) -> None:
