@@ -275,13 +275,16 @@ int lbm_time_launches(lbm_ctx* ctx, int32_t launches, double* ms_out);
  * The state at step `step` is read from f[0], phi[0], c[0]; after nsteps steps (Secs. 2.2-2.3 and the Sec. 4
  * centre update, the wave-path kernels of lbm_step at strip width 54) the state at step + nsteps is in index
  * (nsteps mod 2) of each pair, and the other index holds the state one step earlier (nsteps >= 1).
- * The strip height is 40 for lattices below 256 x 256 nodes and goes by size and precision above (4 to 128).  Results
- * equal those of lbm_step on the same state, at that height bit for bit; at another height the sums of the centres
- * of mass are rounded in another order.  Errors: LBM_E_INVAL (configuration as for
+ * Results equal those of lbm_step on the same state on the wave path at strip width 54 and the height that
+ * lbm_noalloc_rows tells, bit for bit; at another height the fields are the same and the sums of the centres of mass
+ * are rounded in another order.  Errors: LBM_E_INVAL (configuration as for
  * lbm_init, NULL or misaligned buffers, step or nsteps < 0), LBM_E_NOMEM (scratch too small), LBM_E_HIP. */
 #define LBM_NOALLOC_SCRATCH_BYTES (16u << 20)
 int lbm_step_noalloc(const lbm_config* cfg, void* stream, void* const f[2], void* const phi[2], void* const c[2],
                      int32_t ndrop, lbm_droplet* drops, int64_t step, int64_t nsteps);
+/* Rows of the strips that lbm_step_noalloc sweeps for a lattice with ndrop droplets: 40 below 256 x 256 nodes, by size
+ * and precision above (4 to 128).  A negative error code where it would refuse them (LBM_E_INVAL, LBM_E_NOMEM). */
+int32_t lbm_noalloc_rows(const lbm_config* cfg, int32_t ndrop);
 
 /* ---- Reverse mode (the derivative of a droplet's displacement; Sec. 4 centre of mass) ----
  * The loss is J = x_CM(n0 + nsteps) - x_CM(n0) of droplet `drop` (minimum image in x, so |J| < nx/2), and the

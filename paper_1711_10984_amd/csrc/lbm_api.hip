@@ -884,8 +884,9 @@ int noalloc_waves(int prec) { return prec == LBM_FP64 ? 2 : 3; }
 // 4410 at 16 rows, 4800 / 4610 at 40).  In FP64 they gain only in a long row of launches (759, 780 and 801 us) and lose in
 // short calls (10 steps 8900 / 7900 at 16 rows, 8350 / 7830 at 40), so it stays at 40.  FP16 storage is bound by
 // arithmetic, and its rounds count throughout: 4096^2 315, 291 and, in two rounds of 54 rows, 287.
-// The centres' sums are rounded by strip: lattices below 256 x 256 nodes, whose sweeps leave the chip idle at any
-// height, keep the 40 rows at which lbm_step's centres are the same to the bit.
+// The centres' sums are rounded by strip, so the height decides their last bits.  Lattices below 256 x 256 nodes keep 40
+// rows for that alone: a program that compares them with lbm_step's at that height finds the same bits as ever.  It costs
+// them a good deal (250 x 250 FP64 105 us a step, 28 at the 4 rows that 256 x 256 takes; FP32 86 and 24).
 int noalloc_rows(int nx, int ny, int prec) {
   if ((int64_t)nx * ny < 256 * 256) return NOALLOC_ROWS_FIT;
   static constexpr double ITER[3][3] = {{2.1, 3.4, 3.4}, {1.6, 1.65, 1.97}, {1.5, 1.6, 1.97}};
@@ -942,6 +943,23 @@ NoallocLayout noalloc_layout(int nsegs, int nslots, int ndrop) {
   L.part = off;  off = align_up(off + sizeof(double) * 3 * (size_t)nsegs * (size_t)std::max(1, ndrop), ALIGN);
   L.total = off;
   return L;
+}
+
+NoallocLayout noalloc_layout(const lbm_config& c, int32_t ndrop, int rows) {
+  const int n = noalloc_segments(c.nx, c.ny, rows);
+  return noalloc_layout(n, (n + 7) / 8 * 8, ndrop);
+}
+
+// The height that a lattice gets: the rule's, or a taller one where only that fits the scratch array.
+int noalloc_height(const lbm_config& c, int32_t ndrop, int& rows) {
+  const size_t need = noalloc_layout(c, ndrop, NOALLOC_ROWS_FIT).total;
+  if (need > LBM_NOALLOC_SCRATCH_BYTES)
+    return fail(LBM_E_NOMEM, "this lattice and droplet count need " + std::to_string(need) +
+                                 " bytes of scratch, more than LBM_NOALLOC_SCRATCH_BYTES (" +
+                                 std::to_string((size_t)LBM_NOALLOC_SCRATCH_BYTES) + ")");
+  rows = noalloc_rows(c.nx, c.ny, c.precision);
+  if (noalloc_layout(c, ndrop, rows).total > LBM_NOALLOC_SCRATCH_BYTES) rows = std::max(rows, NOALLOC_ROWS_FIT);
+  return LBM_OK;
 }
 
 // Fills the scratch regions: instance description, step counter, droplet table (from the caller's), the presence
@@ -1031,6 +1049,14 @@ __global__ __launch_bounds__(NTHREADS) void k_noalloc_centres(const DropDev* __r
 
 extern "C" {
 
+int32_t lbm_noalloc_rows(const lbm_config* cfg, int32_t ndrop) {
+  if (!cfg) return fail(LBM_E_INVAL, "cfg must not be NULL");
+  int rows = 0;
+  int rc = validate(1, cfg, &ndrop);
+  if (rc == LBM_OK) rc = noalloc_height(*cfg, ndrop, rows);
+  return rc == LBM_OK ? rows : rc;
+}
+
 int lbm_step_noalloc(const lbm_config* cfg, void* stream, void* const f[2], void* const phi[2], void* const c[2],
                      int32_t ndrop, lbm_droplet* drops, int64_t step, int64_t nsteps) {
   if (!cfg) return fail(LBM_E_INVAL, "cfg must not be NULL");
@@ -1053,13 +1079,7 @@ int lbm_step_noalloc(const lbm_config* cfg, void* stream, void* const f[2], void
   d.pstride = (int64_t)cf.nx * cf.ny;
   d.ndrop = ndrop;
   d.strip_w = FUSED_TX;
-  // taller strips than the rule's where only those fit the scratch array
-  auto layout_of = [&](int rows) {
-    const int n = noalloc_segments(cf.nx, cf.ny, rows);
-    return noalloc_layout(n, (n + 7) / 8 * 8, ndrop);
-  };
-  d.seg_rows = noalloc_rows(cf.nx, cf.ny, cf.precision);
-  if (layout_of(d.seg_rows).total > LBM_NOALLOC_SCRATCH_BYTES) d.seg_rows = std::max(d.seg_rows, NOALLOC_ROWS_FIT);
+  if ((rc = noalloc_height(cf, ndrop, d.seg_rows)) != LBM_OK) return rc;
   d.tiles_x[TILING_FUSED] = (cf.nx + FUSED_TX - 1) / FUSED_TX;
   d.tiles_y[TILING_FUSED] = (cf.ny + d.seg_rows - 1) / d.seg_rows;
   // element offsets of the caller's buffers from f[0] (the pool base of the kernels); 256-byte alignment makes
@@ -1076,11 +1096,6 @@ int lbm_step_noalloc(const lbm_config* cfg, void* stream, void* const f[2], void
   const int nsegs = d.tiles_x[TILING_FUSED] * d.tiles_y[TILING_FUSED];
   const int nslots = (nsegs + 7) / 8 * 8;
   const NoallocLayout L = noalloc_layout(nsegs, nslots, ndrop);
-  const size_t need = layout_of(NOALLOC_ROWS_FIT).total;
-  if (need > LBM_NOALLOC_SCRATCH_BYTES)
-    return fail(LBM_E_NOMEM, "this lattice and droplet count need " + std::to_string(need) +
-                                 " bytes of scratch, more than LBM_NOALLOC_SCRATCH_BYTES (" +
-                                 std::to_string((size_t)LBM_NOALLOC_SCRATCH_BYTES) + ")");
   void* sp = nullptr;
   if ((rc = scratch_on_current_device(&sp)) != LBM_OK) return rc;
   char* s = static_cast<char*>(sp);

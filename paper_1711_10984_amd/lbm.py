@@ -33,7 +33,7 @@ EXPORTED = ["lbm_workspace_bytes", "lbm_init_batch", "lbm_init", "lbm_step", "lb
             "lbm_get_seg_rows", "lbm_set_strip_width", "lbm_get_strip_width", "lbm_tune_rows", "lbm_tune_widths",
             "lbm_autotune", "lbm_step_noalloc", "lbm_adjoint_bytes", "lbm_adjoint_forward",
             "lbm_adjoint_backward", "lbm_running_kernel", "lbm_running_rows",
-            "lbm_debug_strips", "lbm_destroy", "lbm_last_error"]
+            "lbm_debug_strips", "lbm_noalloc_rows", "lbm_destroy", "lbm_last_error"]
 LBM_SEG_ROWS_MIN, LBM_SEG_ROWS_MAX, LBM_TUNE_NROWS = 16, 4096, 16
 LBM_STRIP_W_MIN, LBM_STRIP_W_MAX, LBM_TUNE_NWIDTHS = 32, 54, 1
 LBM_NOALLOC_SCRATCH_BYTES = 16 << 20
@@ -123,6 +123,8 @@ def load_library(path: Optional[str] = None):
     lib.lbm_autotune.argtypes = [vp, C.c_int32, C.c_int32, C.POINTER(C.c_int32), C.POINTER(C.c_int32), dp]
     lib.lbm_step_noalloc.argtypes = [C.POINTER(lbm_config), vp, C.POINTER(vp), C.POINTER(vp), C.POINTER(vp), C.c_int32,
                                      vp, C.c_int64, C.c_int64]
+    lib.lbm_noalloc_rows.argtypes = [C.POINTER(lbm_config), C.c_int32]
+    lib.lbm_noalloc_rows.restype = C.c_int32
     lib.lbm_adjoint_bytes.argtypes = [vp, C.c_int64, C.c_int32, C.POINTER(C.c_size_t)]
     lib.lbm_adjoint_forward.argtypes = [vp, vp, C.c_size_t, C.c_int32, C.c_int64, C.c_int32, dp]
     lib.lbm_adjoint_backward.argtypes = [vp, vp, C.c_size_t, dp, dp]
@@ -337,6 +339,14 @@ def lbm_step_noalloc(cfg: lbm_config, stream_ptr: int, f_ptrs, phi_ptrs, c_ptrs,
     return int(load_library().lbm_step_noalloc(C.byref(cfg), C.c_void_p(stream_ptr), pair(f_ptrs), pair(phi_ptrs),
                                                pair(c_ptrs), int(ndrop), C.c_void_p(drops_ptr), int(step),
                                                int(nsteps)))
+
+
+def lbm_noalloc_rows(cfg: lbm_config, ndrop: int) -> int:
+    """Strip height of lbm_step_noalloc for this lattice; raises where it would refuse it."""
+    rows = int(load_library().lbm_noalloc_rows(C.byref(cfg), int(ndrop)))
+    if rows < 0:
+        _check(rows)
+    return rows
 
 
 def lbm_destroy(ctx: int) -> None:
