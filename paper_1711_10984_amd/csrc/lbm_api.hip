@@ -878,12 +878,14 @@ int noalloc_waves(int prec) { return prec == LBM_FP64 ? 2 : 3; }
 // iterations x time, for the wavefronts per SIMD that its segments make (an extra one up to the most that are
 // planned for, a further round of them beyond).  Times of an iteration with 1, 2 and 3 wavefronts per SIMD, in us,
 // from launches on 700^2 to 2048^2 lattices.  FP64 leaves a tenth of the slots free: 2048^2 takes 193 us with 1786
-// wavefronts (44 rows), 200 with 1976 (40 rows).  Lattices of several rounds are bound by memory.  In FP32 the shortest
-// strips are the best there: their neighbours read the shared halo rows soon after one another (4096^2 in back-to-back
-// launches 432 us at 16 rows, 461 at 40, 460 at 80; 10 steps with 8 droplets, first call on a new state / repeated: 4590 /
-// 4410 at 16 rows, 4800 / 4610 at 40).  In FP64 they gain only in a long row of launches (759, 780 and 801 us) and lose in
-// short calls (10 steps 8900 / 7900 at 16 rows, 8350 / 7830 at 40), so it stays at 40.  FP16 storage is bound by
-// arithmetic, and its rounds count throughout: 4096^2 315, 291 and, in two rounds of 54 rows, 287.
+// wavefronts (44 rows), 200 with 1976 (40 rows).  FP16 storage is bound by arithmetic, and its rounds count throughout:
+// 4096^2 315, 291 and, in two rounds of 54 rows, 287.  Lattices of MANY_ROUNDS in 16-row strips are bound by memory.  In
+// FP32 the shortest strips are the best there: their neighbours read the shared halo rows soon after one another.  In
+// FP64 they gain only in a long row of launches (4096^2 759, 780 and 801 us at 16, 40 and 80 rows) and lose in short calls
+// (10 steps with 8 droplets, first call on a new state / repeated: 8900 / 7900 at 16 rows, 8350 / 7830 at 40), so it stays
+// at 40.  The line lies where the two sides meet; us a step in calls of 10, repeated, the model's height / the fixed one:
+// FP32 3200^2 (3.9 rounds) 269 / 278, 3600^2 (4.9) 334 / 337, 3800^2 (5.5) 374 / 381, 4096^2 (6.3) 458 / 441;
+// FP64 2700^2 (4.6) 348 / 362, 2900^2 (5.3) 400 / 399, 3200^2 (6.5) 498 / 491.
 // The centres' sums are rounded by strip, so the height decides their last bits.  Lattices below 256 x 256 nodes keep 40
 // rows for that alone: a program that compares them with lbm_step's at that height finds the same bits as ever.  It costs
 // them a good deal (250 x 250 FP64 105 us a step, 28 at the 4 rows that 256 x 256 takes; FP32 86 and 24).
@@ -893,7 +895,8 @@ int noalloc_rows(int nx, int ny, int prec) {
   const int most = noalloc_waves(prec);
   const double per_round = (prec == LBM_FP64 ? 0.9 : 1.0) * SIMDS;
   constexpr int SHORT = 16;
-  if (prec != LBM_FP16 && noalloc_segments(nx, ny, SHORT) >= 4.5 * most * per_round)
+  constexpr double MANY_ROUNDS = 5.5;
+  if (prec != LBM_FP16 && noalloc_segments(nx, ny, SHORT) >= MANY_ROUNDS * most * per_round)
     return prec == LBM_FP32 ? SHORT : NOALLOC_ROWS_FIT;
   int best = NOALLOC_ROWS_FIT;
   double best_cost = 1e300;

@@ -1,7 +1,7 @@
 """lbm_step_noalloc and lbm_step on strips of the height that lbm_noalloc_rows tells: the same bits, centres included.
 
 The sizes: the fixed height, the lowest that strips of a context can have (8 rows), heights below and above 16, remainders
-of a strip in x and y, plates, in each storage type; 40 rows because shorter strips' sums of 100 droplets do not fit."""
+of a strip in x and y, plates, in each storage type; 40 rows because shorter strips' sums of 60 droplets do not fit."""
 import numpy as np
 import pytest
 
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("nx,ny,walls,prec,ndrop", [(255, 256, 0, 0, 5), (251, 200, 1, 2, 5), (600, 600, 0, 0, 5),
                                                     (700, 701, 1, 0, 5), (900, 901, 0, 0, 5), (900, 901, 1, 1, 5),
                                                     (900, 901, 0, 2, 5), (1300, 1301, 0, 0, 5), (1300, 1301, 0, 1, 5),
-                                                    (1300, 1301, 1, 2, 5), (57456, 208, 0, 1, 100)])
+                                                    (1300, 1301, 1, 2, 5), (70200, 208, 0, 1, 5), (70200, 208, 0, 1, 60)])
 def test_the_same_bits_at_the_same_height(nx, ny, walls, prec, ndrop):
     from paper_1711_10984_amd import lbm
     rng = np.random.default_rng(nx + ny + prec)

@@ -19,8 +19,16 @@ def test_range():
 
 
 def test_forty_rows_where_short_strips_exceed_the_scratch_array():
-    assert rows(57456, 208, 1, 5) == 16 and rows(57456, 208, 1, 100) == 40
+    assert rows(70200, 208, 1, 5) == 16 and rows(70200, 208, 1, 60) == 40
     assert rows(4096, 4096, 1, 8) == 16 and rows(4096, 4096, 1, 64) == 40
+
+
+def test_fixed_heights_where_the_strips_make_many_rounds():
+    """5.5 rounds of 3 x 1024 wavefronts in FP32 and of 0.9 x 2 x 1024 in FP64, in strips of 54 x 16."""
+    for prec, wavefronts, fixed in ((0, 1843.2, 40), (1, 3072, 16)):
+        for n in range(2200, 4400, 37):
+            rounds = -(-n // 54) * -(-n // 16) / wavefronts
+            assert (rows(n, n, prec, 1) == fixed) == (rounds >= 5.5), (prec, n)
 
 
 def test_what_is_refused():
