@@ -1713,10 +1713,9 @@ struct AdjLayout {
 };
 
 constexpr int ADJ_TMP_PLANES = 4;  // intermediate adjoints of one backward step
-// The adjoint step reads the first ADJ_FWD_PLANES stage planes of the forward step (mu .. X^{n+1/2}), and the
-// recompute exports only those: the record of an interval holds ADJ_FWD_PLANES planes per step.
+// The adjoint step reads ADJ_FWD_PLANES stage planes of the forward step, and the recompute exports only those: the
+// record of an interval holds ADJ_FWD_PLANES planes per step.
 constexpr int ADJ_FWD_PLANES = ADJ_EXPORT_PLANES;
-static_assert(ADJ_FWD_PLANES <= LBM_NSTAGE, "stage planes of the adjoint's forward record");
 
 // Up to five byte ranges (multiples of 8 bytes) copied by one launch.
 struct CopyList {
@@ -1811,7 +1810,7 @@ int adj_save(lbm_ctx* c, const AdjLayout& A, char* slot) {
 }
 
 // A whole slot back into the current buffers, or (sslot not null) its phi and c into a segment slot and only the
-// populations into the current buffers.  The droplet table goes to the context, and to the segment slot.
+// populations into the current buffers.  The droplet table goes to the context, or to the segment slot.
 int adj_load(lbm_ctx* c, const AdjLayout& A, const char* slot, int64_t step, char* sslot) {
   const InstDev& d = c->L.inst[0];
   char* pool = static_cast<char*>(c->pool());
@@ -1875,7 +1874,7 @@ int adj_backward(lbm_ctx* c, const AdjLayout& A, char* w, double* dA0, double* d
   auto fwd_at = [&](int64_t j) {
     const double* f = fwd_rec(j);
     return AdjFwd{f + 0 * M, f + 1 * M, f + 2 * M, f + 3 * M, f + 4 * M,
-                  f + 5 * M, f + 6 * M, f + 7 * M, f + 8 * M, f + 10 * M};  // plane 9 (M) is not read
+                  f + 5 * M, f + 6 * M, f + 7 * M, f + 8 * M, f + 9 * M};
   };
   T* adj = reinterpret_cast<T*>(w + A.off_adj);
   T* lam[2] = {adj, adj + 11 * M};  // adjoint state (f 9 planes, phi, c) at n and at n + 1

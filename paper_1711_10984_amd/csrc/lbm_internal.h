@@ -83,9 +83,9 @@ struct TileDev {
 // T is the arithmetic (and field) type, P the population storage type (T itself, or _Float16 deviations
 // from w_i n0 with T = float).  `buf` is the typed base pointer of the field pool, `parity` selects the
 // current buffers.  Modes: 0 step, 1 step + stage export, 2 diagnostics (n, u) of instance dbg_inst only.  An export
-// names its instance in dbg_inst: inst exports all LBM_NSTAGE planes, -2 - inst (export_planes()) only the first ADJ_EXPORT_PLANES
-// (mu .. X^{n+1/2}, M's left as it was), which the reverse mode reads.
-constexpr int ADJ_EXPORT_PLANES = 11;
+// names its instance in dbg_inst: inst exports all LBM_NSTAGE planes, -2 - inst (export_planes()) only the
+// ADJ_EXPORT_PLANES that the reverse mode reads (mu .. c^{n+1/2}, and X^{n+1/2} in the place of M).
+constexpr int ADJ_EXPORT_PLANES = 10;
 inline int export_planes(int inst, bool all) { return all ? inst : -2 - inst; }
 template <typename T, typename P>
 hipError_t launch_lb(hipStream_t s, int mode, int parity, int ntiles_launch, const TileDev* tiles,

@@ -405,7 +405,7 @@ __global__ __launch_bounds__(NT) void k_tile(int parity, InstDev one, const Tile
     if (DBG && owned(lx, ly, 1)) {
       const int64_t o = (int64_t)r * nx + (x0 + lx - 1);
       if (export_all(dbg_inst)) dbg[9 * nplane + o] = (double)M;
-      dbg[10 * nplane + o] = (double)Xh;
+      dbg[plane_Xh(dbg_inst) * nplane + o] = (double)Xh;
     }
   }
   __syncthreads();
