@@ -1374,7 +1374,12 @@ int lbm_debug_stage(lbm_ctx* c, int32_t inst, double* out) {
                             [&](auto t, auto p) { return debug_launch<decltype(t), decltype(p)>(c, inst, c->d_dbg()); });
   if (e != hipSuccess) return fail(LBM_E_HIP, std::string("stage launch: ") + hipGetErrorString(e));
   const size_t n = (size_t)d.nx * d.ny;
-  HIPCHK(hipMemcpyAsync(out, c->d_dbg(), sizeof(double) * LBM_NSTAGE * n, hipMemcpyDeviceToHost, c->stream));
+  const struct {
+    int from, to, count;
+  } parts[] = {{0, 0, 9}, {PLANE_M, 9, 1}, {PLANE_XH, 10, 1}, {11, 11, LBM_NSTAGE - 11}};
+  for (const auto& p : parts)
+    HIPCHK(hipMemcpyAsync(out + p.to * n, c->d_dbg() + p.from * n, sizeof(double) * p.count * n, hipMemcpyDeviceToHost,
+                          c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   return LBM_OK;
 }

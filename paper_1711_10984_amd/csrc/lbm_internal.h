@@ -84,8 +84,9 @@ struct TileDev {
 // from w_i n0 with T = float).  `buf` is the typed base pointer of the field pool, `parity` selects the
 // current buffers.  Modes: 0 step, 1 step + stage export, 2 diagnostics (n, u) of instance dbg_inst only.  An export
 // names its instance in dbg_inst: inst exports all LBM_NSTAGE planes, -2 - inst (export_planes()) only the
-// ADJ_EXPORT_PLANES that the reverse mode reads (mu .. c^{n+1/2}, and X^{n+1/2} in the place of M).
-constexpr int ADJ_EXPORT_PLANES = 10;
+// first ADJ_EXPORT_PLANES, which the reverse mode reads (mu .. c^{n+1/2}, X^{n+1/2}).  M is exported behind X^{n+1/2}
+// for that; lbm_debug_stage gives the two in the order of the stages.
+constexpr int ADJ_EXPORT_PLANES = 10, PLANE_XH = 9, PLANE_M = 10;
 inline int export_planes(int inst, bool all) { return all ? inst : -2 - inst; }
 template <typename T, typename P>
 hipError_t launch_lb(hipStream_t s, int mode, int parity, int ntiles_launch, const TileDev* tiles,

@@ -532,10 +532,9 @@ __device__ void tile_cm_sums(const InstDev& I, int t_local, int t_global, const 
 // ------------------------------------------------------------------------------------------------
 // k_lb: mu, X, F; pull + moments; collision.  MODE 0: step, 1: step + stage planes, 2: n and u of dbg_inst only.
 // Export launches name their instance in dbg_inst: inst for all LBM_NSTAGE stage planes, -2 - inst for the
-// planes mu .. c^{n+1/2} and X^{n+1/2}, in the place of M, which is what the reverse mode reads.
+// first ADJ_EXPORT_PLANES only (mu .. c^{n+1/2}, X^{n+1/2}), which is what the reverse mode reads.
 __device__ __forceinline__ int export_inst(int dbg_inst) { return dbg_inst >= 0 ? dbg_inst : -2 - dbg_inst; }
 __device__ __forceinline__ bool export_all(int dbg_inst) { return dbg_inst >= 0; }
-__device__ __forceinline__ int plane_Xh(int dbg_inst) { return export_all(dbg_inst) ? 10 : ADJ_EXPORT_PLANES - 1; }
 
 template <typename T, typename P, int MODE>
 __global__ __launch_bounds__(NTHREADS) void k_lb(int parity, const TileDev* __restrict__ tiles,
@@ -766,8 +765,8 @@ __global__ __launch_bounds__(NTHREADS) void k_fd(int parity, const TileDev* __re
       const int64_t q = (int64_t)y * nx + x;
       dbg[7 * nplane + q] = (double)s_ph[i2];
       dbg[8 * nplane + q] = (double)ch;
-      if (export_all(dbg_inst)) dbg[9 * nplane + q] = (double)s_M[i1];
-      dbg[plane_Xh(dbg_inst) * nplane + q] = (double)s_Xh[i1];
+      if (export_all(dbg_inst)) dbg[PLANE_M * nplane + q] = (double)s_M[i1];
+      dbg[PLANE_XH * nplane + q] = (double)s_Xh[i1];
       if (export_all(dbg_inst)) {
         dbg[11 * nplane + q] = (double)phn;
         dbg[12 * nplane + q] = (double)cn;
@@ -1471,8 +1470,8 @@ __global__ __launch_bounds__(NTHREADS) void k_step(int parity, const TileDev* __
         r_Xh[sm][lane] = Xh;
         if (DBG && own_col && r >= y0 && r < yend) {
           const int64_t q = (int64_t)r * nx + (x0 + col);
-          if (export_all(dbg_inst)) dbg[9 * nplane + q] = (double)M;
-          dbg[plane_Xh(dbg_inst) * nplane + q] = (double)Xh;
+          if (export_all(dbg_inst)) dbg[PLANE_M * nplane + q] = (double)M;
+          dbg[PLANE_XH * nplane + q] = (double)Xh;
         }
       }
     }
@@ -2167,8 +2166,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
       XH4 = halfB1 * (gphx * gphx + gphy * gphy);
       if (DBG && own_col && q - 4 >= y0 && q - 4 < yend) {
         const int64_t qq = (int64_t)(q - 4) * nx + (x0 + col);
-        if (export_all(dbg_inst)) dbg[9 * nplane + qq] = (double)M4;
-        dbg[plane_Xh(dbg_inst) * nplane + qq] = (double)XH4;
+        if (export_all(dbg_inst)) dbg[PLANE_M * nplane + qq] = (double)M4;
+        dbg[PLANE_XH * nplane + qq] = (double)XH4;
       }
     }
     // ---- s5: phi^{n+1}, c^{n+1} (Eqs. 18, 19) at row q - 5 and centre-of-mass contributions

@@ -404,8 +404,8 @@ __global__ __launch_bounds__(NT) void k_tile(int parity, InstDev one, const Tile
     s_Xh[i] = Xh;
     if (DBG && owned(lx, ly, 1)) {
       const int64_t o = (int64_t)r * nx + (x0 + lx - 1);
-      if (export_all(dbg_inst)) dbg[9 * nplane + o] = (double)M;
-      dbg[plane_Xh(dbg_inst) * nplane + o] = (double)Xh;
+      if (export_all(dbg_inst)) dbg[PLANE_M * nplane + o] = (double)M;
+      dbg[PLANE_XH * nplane + o] = (double)Xh;
     }
   }
   __syncthreads();
