@@ -545,6 +545,8 @@ hipError_t enqueue_steps_any(lbm_ctx* c, int parity, int64_t n, int64_t& done) {
 }
 
 constexpr int LONG_GRAPH = 5;
+// Steps launched one by one go in sequences of at most so many: a tiled step knows its number in the sequence in 32 bits.
+constexpr int64_t SEQUENCE_MOST = 1 << 20;
 
 void destroy_graphs(lbm_ctx* c) {
   for (int p = 0; p < 4; ++p) {
@@ -1281,11 +1283,15 @@ int lbm_step(lbm_ctx* c, int64_t n) {
       c->step += lg ? longer : c->graph_steps;
     }
   }
-  int64_t done;
-  const hipError_t e = enqueue_steps_any(c, c->parity, left, done);
-  c->parity ^= (int)(done & 1);
-  c->step += done;
-  if (e != hipSuccess) return fail(LBM_E_HIP, std::string("timestep launch: ") + hipGetErrorString(e));
+  while (left > 0) {
+    const int64_t n_now = std::min(left, SEQUENCE_MOST);
+    int64_t done;
+    const hipError_t e = enqueue_steps_any(c, c->parity, n_now, done);
+    c->parity ^= (int)(done & 1);
+    c->step += done;
+    left -= n_now;
+    if (e != hipSuccess) return fail(LBM_E_HIP, std::string("timestep launch: ") + hipGetErrorString(e));
+  }
   return LBM_OK;
 }
 

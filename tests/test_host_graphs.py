@@ -31,3 +31,15 @@ def test_default_graphs_of_long_calls_wait_for_the_second_one(monkeypatch):
     assert captured == [20, 100, 0, 0]
     assert lbm.lbm_get_step(ctx.h) == 460
     ctx.close()
+
+
+def test_long_rows_of_single_launches_go_in_sequences(monkeypatch):
+    """A tiled step counts the steps before it in its sequence in 32 bits: a sequence ends after 2^20 steps."""
+    lbm, lib = stubbed(monkeypatch)
+    ctx = Context(lbm, [(64, 48)], [[dict(x=30.0, y=20.0, R=8.0, Rs=3.0, active=1)]], stream=0)
+    lib.stub_reset()
+    n = (1 << 20) + 3
+    lbm.lbm_step(ctx.h, n)
+    assert lib.stub_launched(b"6k_tile") == n and lib.stub_launched(b"k_tile_final") == 2
+    assert lbm.lbm_get_step(ctx.h) == n
+    ctx.close()
