@@ -33,15 +33,6 @@ constexpr int ADJ_HX = ADJ_TILE_X + 2, ADJ_HN = ADJ_HX * (ADJ_TILE_Y + 2);
 static_assert(ADJ_TILE_X == 64, "one wavefront per tile row");
 static_assert(ADJ_HN <= 2 * ADJ_THREADS, "two staged values per thread");
 
-// Workgroups are dealt to the eight XCDs in turn (workgroup b runs on XCD b mod 8), and each XCD has an L2 of
-// its own.  Relabelled so that each XCD takes one contiguous run of the lattice's tiles, a tile's rows above
-// and below are mostly read by blocks of the same XCD, from its L2.  A bijection of [0, gridDim.x).
-__device__ __forceinline__ int xcd_block() {
-  const int nb = gridDim.x, b = blockIdx.x;
-  const int q = nb >> 3, r = nb & 7, x = b & 7;
-  return x * q + min(x, r) + (b >> 3);
-}
-
 // This thread's node (x, y) and frame index l, and the plane offsets of the (one or two) values it stages.
 // Frame row j + 1, column i + 1 holds node (x0 + i, y0 + j) of the tile at (x0, y0); the halo holds the
 // periodic neighbours in x, and in y the periodic neighbours or, with walls, the boundary rows that mirror the

@@ -269,6 +269,15 @@ __device__ __forceinline__ void lb_collide(const T (&d)[9], T dn, T nn, T ux, T 
   }
 }
 
+// Workgroups are dealt to the eight XCDs in turn (workgroup b runs on XCD b mod 8), and each XCD has an L2 of
+// its own.  Relabelled so that each XCD takes one contiguous run of the lattice's tiles, a tile's rows above
+// and below are mostly read by blocks of the same XCD, from its L2.  A bijection of [0, gridDim.x).
+__device__ __forceinline__ int xcd_block() {
+  const int nb = gridDim.x, b = blockIdx.x;
+  const int q = nb >> 3, r = nb & 7, x = b & 7;
+  return x * q + min(x, r) + (b >> 3);
+}
+
 // Index v within one lattice width of [0, n), wrapped.
 __device__ __forceinline__ int near_index(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
 
@@ -297,8 +306,10 @@ __device__ __forceinline__ void inner_first(int i, int& lx, int& ly) {
   }
 }
 
-// A sum in twice the working precision: hi + lo, with the rounding errors of hi's additions in lo.  The sums of
-// the same numbers in another order give the same double, so results do not depend on the tiling.
+// A sum in twice the working precision: hi + lo, with the rounding errors of hi's additions (Knuth's two-sum) in lo, which
+// is itself a plain sum.  The order of N additions moves hi + lo by about N^2 2^-106 of the terms' magnitudes before the
+// last rounding, so that sums of the same numbers differ between tilings only where they lie that near the middle of two
+// doubles.
 struct Dd {
   double hi, lo;
 };

@@ -29,8 +29,8 @@ namespace {
 
 // The centre of mass of droplet k of an instance from its tiles' sums, by one wavefront, in parts so that each runs
 // while the wavefront would wait for others: begin() loads the tiles' presence bits, load() lists the tiles that hold
-// the droplet and loads the sums of the first 64 of them, sum() adds up, move() gives the centre.  Tiles are taken TILE_CHUNK at a time; one chunk
-// covers every lattice whose tiles fit the chip at once.  Each of the three sums has a row of 16 lanes (the last row
+// the droplet and loads the sums of the first 64 of them, sum() adds up, move() gives the centre.  Tiles are taken
+// TILE_CHUNK at a time; one chunk covers every lattice whose tiles fit the chip at once.  Each of the three sums has a row of 16 lanes (the last row
 // repeats the third), one tile's entry to a lane: additions in twice the working precision are chains of dependent
 // FP64 operations, and all three sums over all 64 lanes took the whole stage beside them (1.4 us) and more.
 constexpr int TILE_UNR = 4, TILE_CHUNK = 64 * TILE_UNR;
@@ -150,8 +150,7 @@ __global__ __launch_bounds__(NT) void k_tile(int parity, InstDev one, const Tile
   }
   const InstDev& I = MULTI ? insts[inst] : one;
   if constexpr (!MULTI) {
-    const int nb = gridDim.x, b = blockIdx.x, per = nb >> 3, rest = nb & 7, x = b & 7;
-    t = x * per + min(x, rest) + (b >> 3);
+    t = xcd_block();
     const int ty = t / I.tiles_x[TILING_TILE];
     x0 = (t - ty * I.tiles_x[TILING_TILE]) * OX;
     y0 = ty * OY;
