@@ -395,6 +395,7 @@ __device__ __forceinline__ void adj_collide(const AdjModel& m, const T (&fsb)[9]
   const T usq = u * u + v * v;
   T nb = T(0), ub = uxb, vb = uyb;
   Fxb = Fyb = T(0);
+#pragma unroll
   for (int i = 0; i < 9; ++i) {
     const T ex = T(EX9[i]), ey = T(EY9[i]);
     const T eu = ex * u + ey * v, eF = ex * Fx + ey * Fy;
@@ -414,6 +415,7 @@ __device__ __forceinline__ void adj_collide(const AdjModel& m, const T (&fsb)[9]
   Fxb += T(0.5) * mxb;
   Fyb += T(0.5) * myb;
   nb -= (ub * u + vb * v) / nn;
+#pragma unroll
   for (int i = 0; i < 9; ++i) fb[i] = ((T(1) - omega) * fsb[i] + nb) + (T(EX9[i]) * mxb + T(EY9[i]) * myb);
 }
 
@@ -446,12 +448,14 @@ __global__ __launch_bounds__(ADJ_THREADS) void k_adj3(AdjModel m, AdjFwd f, AdjP
   const int EX9[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1}, EY9[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
   const int OPP9[9] = {0, 3, 4, 1, 2, 7, 8, 5, 6};
   T fsb[9], fb[9], Fxb, Fyb;
+#pragma unroll
   for (int i = 0; i < 9; ++i) {
     const int ty = k.y + EY9[i];
     fsb[i] = m.walls && (ty < 0 || ty >= m.ny) ? p.fb1[(size_t)OPP9[i] * N + idx]
                                                : p.fb1[(size_t)i * N + k.d(EX9[i], EY9[i])];
   }
   adj_collide<T>(m, fsb, T(f.n[idx]), ux(0, 0), uy(0, 0), T(f.Fx[idx]), T(f.Fy[idx]), uxb, uyb, fb, Fxb, Fyb);
+#pragma unroll
   for (int i = 0; i < 9; ++i) p.fb[(size_t)i * N + idx] = fb[i];
   p.Fxb[idx] = Fxb;
   p.Fyb[idx] = Fyb;
@@ -765,6 +769,7 @@ __global__ __launch_bounds__(NT) void k_adj_tile(AdjModel m, AdjFwd f, AdjPlanes
 #pragma unroll
     for (int which = 0; which < 2; ++which) adj_advect<T>(k, ux, uy, s_g + which * N3, s_o + which * N3, gb[which], uxb, uyb);
     T fsb[9], fb[9], Fxb, Fyb;
+#pragma unroll
     for (int i = 0; i < 9; ++i) fsb[i] = g2[j][i];
     adj_collide<T>(m, fsb, g2[j][9], ux(0, 0), uy(0, 0), g2[j][10], g2[j][11], uxb, uyb, fb, Fxb, Fyb);
     s_Fxb[ly * W2 + lx] = Fxb;
@@ -774,6 +779,7 @@ __global__ __launch_bounds__(NT) void k_adj_tile(AdjModel m, AdjFwd f, AdjPlanes
       cbv[j < R0 ? j : 0] = gb[1];
       const int x = x0 + lx - 2;
       if (x < nx && r < ny)
+#pragma unroll
         for (int i = 0; i < 9; ++i) p.fb[(size_t)i * N + (size_t)r * nx + x] = fb[i];
     }
   }
