@@ -71,9 +71,9 @@ constexpr int ADJ_OX = 16, ADJ_OY = 16, ADJ_NT = 512;
 constexpr int ADJ_RINGS = 5;  // a lattice is at least a tile and its rings on one side wide and high
 inline int adj_tiles(int nx, int ny) { return ((nx + ADJ_OX - 1) / ADJ_OX) * ((ny + ADJ_OY - 1) / ADJ_OY); }
 // One workgroup per compute unit at most: beyond, the rings' arithmetic costs more than the launches and planes saved.
-// A backward step with its recomputed step, us, tiles / three launches: 200 x 200 FP64 26.0 / 37.0, 256 x 256 27.2 / 32.4
-// (FP32 24.0 / 29.0); beyond, 300 x 300 45.0 / 43.3, 400 x 400 68.6 / 60.5, 512 x 512 92.3 / 76.7 (FP32 61.8 / 58.8),
-// 1024 x 1024 345 / 255.
+// A backward step with its recomputed step, us, tiles / three launches: 200 x 200 FP64 24.4 / 35.3, 256 x 256 25.7 / 32.1
+// (FP32 22.5 / 28.6); beyond, 300 x 300 40.0 / 40.2, 400 x 400 61.5 / 55.7, 512 x 512 82.7 / 70.2 (FP32 52.5 / 53.1),
+// 1024 x 1024 311 / 238.
 inline bool adj_tiled(int nx, int ny) {
   return nx >= ADJ_OX + ADJ_RINGS && ny >= ADJ_OY + ADJ_RINGS && adj_tiles(nx, ny) <= 256;
 }
