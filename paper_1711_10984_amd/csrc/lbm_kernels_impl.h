@@ -422,6 +422,13 @@ struct DropShared {
   unsigned long long mask[MASK_WORDS];
 };
 
+// A droplet may be the nearest of a box if its smallest squared distance is within the limit that the smallest of the
+// largest distances sets.  Distances are at most FAR, and a limit that is no number admits every droplet, so that there is
+// always a candidate: a centre may be no number after an overflow, and between plates infinite or any number.
+constexpr double FAR = 1e300;
+__device__ __forceinline__ double near_d2(double dx, double dy) { return fmin(dx * dx + dy * dy, FAR); }
+__device__ __forceinline__ bool may_be_nearest(double mind2, double lim) { return !(mind2 > lim); }
+
 // Conservative culling for the box [bx0, bx1] x [by0, by1]: a droplet is a nearest-centre candidate
 // unless its distance to every node of the box exceeds the largest distance of some other droplet's
 // centre to the box; a production disk is a candidate if it may reach the box.  Exact decisions are
@@ -433,14 +440,14 @@ __device__ void cull_droplets(const InstDev& I, const DropDev* __restrict__ drop
   const double Lx = I.nx, Ly = I.yper;
   const double xm = 0.5 * (bx0 + bx1), ym = 0.5 * (by0 + by1);
   const double hx = 0.5 * (bx1 - bx0), hy = 0.5 * (by1 - by0);
-  double my_min_max = 1e300;
+  double my_min_max = FAR;
   for (int k = tid; k < nd; k += NTHREADS) {
     const DropDev d = drops[I.drop_base + k];
     const double ddx = fabs(minimg(xm - d.x, Lx)), ddy = fabs(minimg(ym - d.y, Ly));
     const double ux = ddx + hx, uy = ddy + hy;
     my_min_max = fmin(my_min_max, ux * ux + uy * uy);
     const double lx = fmax(0.0, ddx - hx), ly = fmax(0.0, ddy - hy);
-    sh.mind2[k] = lx * lx + ly * ly;
+    sh.mind2[k] = near_d2(lx, ly);
     unsigned char sf = 0;
     if (d.active) {
       const double px = d.x + (d.R - d.Rs) * d.ex, py = d.y + (d.R - d.Rs) * d.ey;
@@ -456,7 +463,7 @@ __device__ void cull_droplets(const InstDev& I, const DropDev* __restrict__ drop
     int nn = 0, ns = 0;
     const double lim = thr * (1.0 + 1e-12) + 1e-6;
     for (int k = 0; k < nd; ++k) {
-      if (sh.mind2[k] <= lim) sh.near_list[nn++] = k;
+      if (may_be_nearest(sh.mind2[k], lim)) sh.near_list[nn++] = k;
       if (sh.src_flag[k]) sh.src_list[ns++] = k;
     }
     sh.n_near = nn;
@@ -1267,7 +1274,7 @@ __global__ __launch_bounds__(NTHREADS) void k_step(int parity, const TileDev* __
     const double Lx = nx, Ly = I.yper;
     const double xm = 0.5 * (x0 + xend - 1), ym = 0.5 * (y0 + yend - 1);
     const double hx = 0.5 * (xend - 1 - x0), hy = 0.5 * (yend - 1 - y0);
-    double maxd2 = 1e300, mind2 = 1e300;
+    double maxd2 = FAR, mind2 = FAR;
     bool srcf = false;
     if (tid < nd) {
       const DropDev d = drops[I.drop_base + tid];
@@ -1275,7 +1282,7 @@ __global__ __launch_bounds__(NTHREADS) void k_step(int parity, const TileDev* __
       const double ux = ddx + hx, uy = ddy + hy;
       maxd2 = ux * ux + uy * uy;
       const double lx = fmax(0.0, ddx - hx), ly = fmax(0.0, ddy - hy);
-      mind2 = lx * lx + ly * ly;
+      mind2 = near_d2(lx, ly);
       if (d.active) {
         const double px = d.x + (d.R - d.Rs) * d.ex, py = d.y + (d.R - d.Rs) * d.ey;
         const double sdx = fmax(0.0, fabs(minimg(xm - px, Lx)) - hx);
@@ -1290,7 +1297,7 @@ __global__ __launch_bounds__(NTHREADS) void k_step(int parity, const TileDev* __
     __syncthreads();
     thr = fmin(fmin(sh.red[0][0], sh.red[1][0]), fmin(sh.red[2][0], sh.red[3][0]));
     const double lim = thr * (1.0 + 1e-12) + 1e-6;
-    const unsigned long long nb = __ballot(tid < nd && mind2 <= lim);
+    const unsigned long long nb = __ballot(tid < nd && may_be_nearest(mind2, lim));
     const unsigned long long sb = __ballot(srcf);
     if (lane == 0) {
       sh.near_mask[wv] = nb;
@@ -1925,10 +1932,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
     const double hx = 0.5 * (xend - 1 - x0), hy = 0.5 * (yend - 1 - y0);
     double mind2[MASK_WORDS];
     bool srcf[MASK_WORDS];
-    double thr = 1e300;
+    double thr = FAR;
     for (int w = 0; w < MASK_WORDS; ++w) {
       const int k = w * 64 + lane;
-      mind2[w] = 1e300;
+      mind2[w] = FAR;
       srcf[w] = false;
       if (k < nd) {
         const DropDev d = drops[I.drop_base + k];
@@ -1936,7 +1943,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
         const double ux = ddx + hx, uy = ddy + hy;
         thr = fmin(thr, ux * ux + uy * uy);
         const double lx = fmax(0.0, ddx - hx), ly = fmax(0.0, ddy - hy);
-        mind2[w] = lx * lx + ly * ly;
+        mind2[w] = near_d2(lx, ly);
         if (d.active) {
           const double px = d.x + (d.R - d.Rs) * d.ex, py = d.y + (d.R - d.Rs) * d.ey;
           const double sdx = fmax(0.0, fabs(minimg(xm - px, Lx)) - hx);
@@ -1949,7 +1956,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
     for (int o = 32; o > 0; o >>= 1) thr = fmin(thr, __shfl_xor(thr, o, 64));
     const double lim = thr * (1.0 + 1e-12) + 1e-6;
     for (int w = 0; w < MASK_WORDS; ++w) {
-      const unsigned long long nb = __ballot(w * 64 + lane < nd && mind2[w] <= lim);
+      const unsigned long long nb = __ballot(w * 64 + lane < nd && may_be_nearest(mind2[w], lim));
       const unsigned long long sb = __ballot(srcf[w]);
       if (lane == w) {
         s_near[w] = nb;
