@@ -1380,13 +1380,9 @@ int lbm_debug_stage(lbm_ctx* c, int32_t inst, double* out) {
                             [&](auto t, auto p) { return debug_launch<decltype(t), decltype(p)>(c, inst, c->d_dbg()); });
   if (e != hipSuccess) return fail(LBM_E_HIP, std::string("stage launch: ") + hipGetErrorString(e));
   const size_t n = (size_t)d.nx * d.ny;
-  const struct {
-    int from, to, count;
-  } parts[] = {{0, 0, 9}, {PLANE_M, 9, 1}, {PLANE_XH, 10, 1}, {11, 11, LBM_NSTAGE - 11}};
-  for (const auto& p : parts)
-    HIPCHK(hipMemcpyAsync(out + p.to * n, c->d_dbg() + p.from * n, sizeof(double) * p.count * n, hipMemcpyDeviceToHost,
-                          c->stream));
+  HIPCHK(hipMemcpyAsync(out, c->d_dbg(), sizeof(double) * LBM_NSTAGE * n, hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
+  std::swap_ranges(out + PLANE_XH * n, out + (PLANE_XH + 1) * n, out + PLANE_M * n);
   return LBM_OK;
 }
 
