@@ -44,3 +44,17 @@ def test_strips_that_the_autotuner_shortened(monkeypatch):
     lbm.lbm_set_seg_rows(ctx.h, rows)
     assert lbm.lbm_running_rows(ctx.h) == rows
     ctx.close()
+
+
+def test_short_strips_that_cut_the_lattice_alike_are_tried_once(monkeypatch):
+    """16 rows are one strip of every listed height, and two strips of 8 rows as of 10, 12 and 14."""
+    lbm, lib = stubbed(monkeypatch)
+    counts = []
+    for nx, ny in ((16, 16), (16, 8)):
+        ctx = Context(lbm, [(nx, ny)], [[]], stream=0)
+        lib.stub_reset()
+        lbm.lbm_autotune(ctx.h, 2)
+        # two kernels, two passes of one launch and two more for each height
+        counts.append(lib.stub_launched(b"6k_step") + lib.stub_launched(b"6k_wave"))
+        ctx.close()
+    assert counts == [2 * 2 * 3 * 2, 2 * 2 * 3]
