@@ -971,7 +971,12 @@ int noalloc_height(const lbm_config& c, int32_t ndrop, int& rows) {
 // masks cleared, and the strip list in the XCD-aware order of set_segments: block j < 8 lists the run of natural
 // strips [j * chunk, (j + 1) * chunk) in the slots j, j + 8, ..., those near a droplet first if `order` is set (as
 // set_segments does: the longer-running strips do not end the launch).  Any table gives a permutation of the strips.
+// The order needs each strip's distance to the droplets once, in FP32, by all threads of a block. With the distances taken
+// in both passes, in FP64 and by one thread a strip the kernel took 18.6 us with 64 droplets and 86.3 us with 256 (2048x2048
+// FP32, 3002 and 1976 strips); 8.3 and 12.4 us now. An FP32 distance may put a strip on the other side of the line: only the order
+// of the blocks changes, never a result.
 constexpr int SETUP_THREADS = 1024;
+constexpr int SETUP_STRIPS = SETUP_THREADS / 2;  // of a run that is ordered, at most
 __global__ __launch_bounds__(SETUP_THREADS) void k_noalloc_setup(InstDev inst, int64_t step, NoallocLayout L, int nsegs,
                                                                  int chunk, int ndrop, int order,
                                                                  const lbm_droplet* __restrict__ drops,
@@ -992,37 +997,48 @@ __global__ __launch_bounds__(SETUP_THREADS) void k_noalloc_setup(InstDev inst, i
   }
   if (blockIdx.x >= 8) return;
   constexpr int NW = SETUP_THREADS / 64;
-  __shared__ double s_drop[MAXDROP][3];  // centre and reach
+  __shared__ float s_drop[MAXDROP][3];  // centre and reach
+  __shared__ bool s_near[SETUP_STRIPS];
   __shared__ int s_count[NW], s_done;
-  if (order)
-    for (int k = tid; k < ndrop; k += SETUP_THREADS) {
-      s_drop[k][0] = drops[k].x;
-      s_drop[k][1] = drops[k].y;
-      s_drop[k][2] = drops[k].R + 2.0;
-    }
-  if (tid == 0) s_done = 0;
-  __syncthreads();
   const int tx = inst.tiles_x[TILING_FUSED];
   const int t0 = blockIdx.x * chunk, t1 = min(nsegs, t0 + chunk);
   TileDev* const run = reinterpret_cast<TileDev*>(s + L.segs) + blockIdx.x;  // every eighth slot
+  auto strip = [&](int t) { return TileDev{0, (t % tx) * inst.strip_w, (t / tx) * inst.seg_rows, t}; };
+  if (tid == 0) s_done = 0;
+  if (order) {
+    for (int k = tid; k < ndrop; k += SETUP_THREADS) {
+      s_drop[k][0] = (float)drops[k].x;
+      s_drop[k][1] = (float)drops[k].y;
+      s_drop[k][2] = (float)drops[k].R + 2.0f;
+    }
+    __syncthreads();
+    // each strip by as many neighbouring lanes as there are threads for
+    int lanes = 64;
+    while (lanes * chunk > SETUP_THREADS) lanes >>= 1;
+    const int t = t0 + tid / lanes;
+    bool near = false;
+    if (t < t1) {
+      const TileDev e = strip(t);
+      const int x1 = min(e.x0 + inst.strip_w, inst.nx) - 1, y1 = min(e.y0 + inst.seg_rows, inst.ny) - 1;
+      const float xm = 0.5f * (e.x0 + x1), ym = 0.5f * (e.y0 + y1), hx = 0.5f * (x1 - e.x0), hy = 0.5f * (y1 - e.y0);
+      for (int k = tid % lanes; k < ndrop && !near; k += lanes) {
+        float dx = fabsf(xm - s_drop[k][0]), dy = fabsf(ym - s_drop[k][1]);
+        if (dx > 0.5f * inst.nx) dx = inst.nx - dx;
+        if (!inst.walls && dy > 0.5f * inst.ny) dy = inst.ny - dy;
+        dx = fmaxf(0.0f, dx - hx);
+        dy = fmaxf(0.0f, dy - hy);
+        near = dx * dx + dy * dy <= s_drop[k][2] * s_drop[k][2];
+      }
+    }
+    const unsigned long long group = (lanes == 64 ? ~0ull : (1ull << lanes) - 1ull) << (lane / lanes * lanes);
+    near = (__ballot(near) & group) != 0ull;
+    if (t < t1 && tid % lanes == 0) s_near[t - t0] = near;
+  }
+  __syncthreads();
   for (int pass = order ? 0 : 1; pass < 2; ++pass) {
     for (int base = t0; base < t1; base += SETUP_THREADS) {
       const int t = base + tid;
-      const TileDev e{0, (t % tx) * inst.strip_w, (t / tx) * inst.seg_rows, t};
-      bool near = false;
-      if (order && t < t1) {
-        const int x1 = min(e.x0 + inst.strip_w, inst.nx) - 1, y1 = min(e.y0 + inst.seg_rows, inst.ny) - 1;
-        const double xm = 0.5 * (e.x0 + x1), ym = 0.5 * (e.y0 + y1), hx = 0.5 * (x1 - e.x0), hy = 0.5 * (y1 - e.y0);
-        for (int k = 0; k < ndrop && !near; ++k) {
-          double dx = fabs(xm - s_drop[k][0]), dy = fabs(ym - s_drop[k][1]);
-          if (dx > 0.5 * inst.nx) dx = inst.nx - dx;
-          if (!inst.walls && dy > 0.5 * inst.ny) dy = inst.ny - dy;
-          dx = fmax(0.0, dx - hx);
-          dy = fmax(0.0, dy - hy);
-          near = dx * dx + dy * dy <= s_drop[k][2] * s_drop[k][2];
-        }
-      }
-      const bool mine = t < t1 && (!order || near == (pass == 0));
+      const bool mine = t < t1 && (!order || s_near[t - t0] == (pass == 0));
       const unsigned long long b = __ballot(mine);
       if (lane == 0) s_count[wv] = __popcll(b);
       __syncthreads();
@@ -1031,7 +1047,7 @@ __global__ __launch_bounds__(SETUP_THREADS) void k_noalloc_setup(InstDev inst, i
         at += w < wv ? s_count[w] : 0;
         all += s_count[w];
       }
-      if (mine) run[(size_t)at * 8] = e;
+      if (mine) run[(size_t)at * 8] = strip(t);
       __syncthreads();
       if (tid == 0) s_done += all;
       __syncthreads();
@@ -1106,7 +1122,8 @@ int lbm_step_noalloc(const lbm_config* cfg, void* stream, void* const f[2], void
   char* s = static_cast<char*>(sp);
   hipStream_t st = static_cast<hipStream_t>(stream);
   // with strips for a second round and more, the order within a run no longer decides how the launch ends
-  const bool order = ndrop > 0 && nsegs <= 4 * SIMDS;
+  const bool order = ndrop > 0 && nslots / 8 <= SETUP_STRIPS;
+  static_assert(8 * SETUP_STRIPS == 4 * SIMDS, "four wavefronts per SIMD");
   const int blocks = std::max(8, (nsegs * MASK_WORDS + SETUP_THREADS - 1) / SETUP_THREADS);
   hipLaunchKernelGGL(k_noalloc_setup, dim3(blocks), dim3(SETUP_THREADS), 0, st, d, step, L, nsegs, nslots / 8, ndrop,
                      order ? 1 : 0, drops, s);
