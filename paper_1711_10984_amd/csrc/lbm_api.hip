@@ -971,10 +971,10 @@ int noalloc_height(const lbm_config& c, int32_t ndrop, int& rows) {
 // masks cleared, and the strip list in the XCD-aware order of set_segments: block j < 8 lists the run of natural
 // strips [j * chunk, (j + 1) * chunk) in the slots j, j + 8, ..., those near a droplet first if `order` is set (as
 // set_segments does: the longer-running strips do not end the launch).  Any table gives a permutation of the strips.
-// The order needs each strip's distance to the droplets once, in FP32, by all threads of a block. With the distances taken
-// in both passes, in FP64 and by one thread a strip the kernel took 18.6 us with 64 droplets and 86.3 us with 256 (2048x2048
-// FP32, 3002 and 1976 strips); 8.3 and 12.4 us now. An FP32 distance may put a strip on the other side of the line: only the order
-// of the blocks changes, never a result.
+// The order needs each strip's distance to the droplets once, in FP32, by all threads of a block.  With the distances
+// taken in both passes, in FP64 and by one thread a strip the kernel took 18.6 us with 64 droplets and 86.3 us with 256
+// (2048x2048 FP32, 3002 and 1976 strips); 8.3 and 12.4 us now.  An FP32 distance may put a strip on the other side of
+// the line: only the order of the blocks changes, never a result.
 constexpr int SETUP_THREADS = 1024;
 constexpr int SETUP_STRIPS = SETUP_THREADS / 2;  // of a run that is ordered, at most
 __global__ __launch_bounds__(SETUP_THREADS) void k_noalloc_setup(InstDev inst, int64_t step, NoallocLayout L, int nsegs,
